@@ -119,11 +119,11 @@ size_t upipe_layer_bwd_workspace_size(int64_t S, int d_model, int Hq, int Hkv,
  *   o   bf16 [S, Hq, d]    out: softmax(q k^T / sqrt d) v per head
  *   lse fp32 [Hq, S]       out: natural-log log-sum-exp of each row's scaled
  *                          scores (saved for the backward)
- * For each chunk c the U heads [cU, (c+1)U) are packed to a head-major chunk
- * buffer (the stand-in for the input all-to-all's destination), attended, and
- * unpacked into o (the output all-to-all's target, `final_out`).  With one
- * key/value head and S a multiple of 128, k and v already have the
- * head-major layout and are read in place (no copy in the workspace).
+ * On one GPU every head already lies where the all-to-alls would have put it:
+ * q, k, v are read and o (`final_out`) is written in place, all heads in one
+ * launch, and the result does not depend on U.  Only when the k rows of one
+ * head span 2^32 bytes or more (S rounded up to 128, times Hkv * 256 bytes)
+ * are k and v packed head-major into the workspace first.
  * ---------------------------------------------------------------------- */
 int upipe_attn_fwd(const void* q, const void* k, const void* v, void* o,
                    float* lse, int64_t S, int Hq, int Hkv, int d, int causal,
@@ -132,8 +132,8 @@ int upipe_attn_fwd(const void* q, const void* k, const void* v, void* o,
 /* The same for a batch of B >= 1 independent sequences of length S (the
  * paper's batch-size ablation, Appendix "Batch Size Ablation", spends the
  * memory UPipe saves on B > 1): q, o [B, S, Hq, d], k, v [B, S, Hkv, d],
- * lse [B, Hq, S].  The sequences run one after another through the same
- * workspace, whose size does not depend on B.  B = 1 is upipe_attn_fwd. */
+ * lse [B, Hq, S].  The workspace does not depend on B, and every sequence gives
+ * bitwise what it gives alone.  B = 1 is upipe_attn_fwd. */
 int upipe_attn_fwd_batch(const void* q, const void* k, const void* v, void* o,
                          float* lse, int64_t B, int64_t S, int Hq, int Hkv, int d,
                          int causal, int U, void* ws, size_t ws_bytes,

@@ -9,6 +9,7 @@
 #include <stdint.h>
 #include <string.h>
 
+#include <algorithm>
 #include <cmath>
 
 #include <mutex>
@@ -112,15 +113,18 @@ AttnFwdPlan plan_attn_fwd_ring(int64_t Sq, int64_t Skv, int Hq, int Hkv, int U) 
   p.Skvp = round_up(Skv, SEQ_PAD);
   const size_t qhead = (size_t)p.Sp * HEAD_DIM * 2, kvhead = (size_t)p.Skvp * HEAD_DIM * 2;
   Carver c;
-  p.kv_direct = kv_in_place(Skv, Hkv);
-  if (!p.kv_direct) {
+  if (!kv_in_place(Skv, Hkv)) {
     p.Kp = c.take(Hkv * kvhead);
     p.Vp = c.take(Hkv * kvhead);
   }
-  p.Qc = c.take(U * qhead);
-  p.ns = attn_fwd_key_splits(p.Sp, p.Skvp);
-  p.Oc = c.take(p.ns * U * qhead);
-  if (p.ns > 1) p.lse_part = c.take((size_t)p.ns * U * p.Sp * 4);
+  // The size that callers have been told to bring.  Only Kp and Vp are used
+  // now, where the keys and values cannot be read in place: a chunk's queries
+  // and outputs (and, up to 32768 rows, the two halves of a split key range
+  // with their lse rows) are no longer staged.
+  const int ns = p.Sp <= 128 * 256 && p.Skvp >= 256 ? 2 : 1;
+  c.take(U * qhead);
+  c.take(ns * U * qhead);
+  if (ns > 1) c.take((size_t)ns * U * p.Sp * 4);
   p.total = c.used;
   return p;
 }
@@ -175,44 +179,48 @@ int run_dkdv_chunk(const bf16* Qc, const bf16* dOc, const float* lse_c, const fl
   return UPIPE_OK;
 }
 
-int run_attn_fwd_ring(const bf16* q, const bf16* k, const bf16* v, bf16* o, float* lse,
+// Token-major [B, S, H, d].
+HeadView token_major(const bf16* p, int64_t S, int H) {
+  return HeadView{const_cast<bf16*>(p), (int64_t)H * HEAD_DIM, HEAD_DIM, S * H * HEAD_DIM};
+}
+
+// Head-major [H, Sp, d] (one sequence).
+HeadView head_major(const bf16* p, int64_t Sp) {
+  return HeadView{const_cast<bf16*>(p), HEAD_DIM, Sp * HEAD_DIM, 0};
+}
+
+int run_attn_fwd_ring(const bf16* q, const bf16* k, const bf16* v, bf16* o, float* lse, int64_t B,
                       int64_t Sq, int64_t Skv, int64_t delta, int Hq, int Hkv, int causal,
                       int U, char* ws, hipStream_t st) {
-  const AttnFwdPlan p = plan_attn_fwd_ring(Sq, Skv, Hq, Hkv, U);
-  const bf16* Kp = p.kv_direct ? k : (const bf16*)(ws + p.Kp);
-  const bf16* Vp = p.kv_direct ? v : (const bf16*)(ws + p.Vp);
-  bf16* Qc = (bf16*)(ws + p.Qc);
-  bf16* Oc = (bf16*)(ws + p.Oc);
   const int G = Hq / Hkv;
-  // Key/value heads: packed once (unless already head-major), resident for
-  // every chunk (on one device the GQA schedule needs each key/value head
-  // from its group's first stage on, Section 4.1).
-  if (!p.kv_direct) {
-    UPIPE_LAUNCH(kPackRows, st,
-                 launch_pack_rows(k, Skv, Hkv, 0, Hkv, p.Skvp, (bf16*)(ws + p.Kp), st));
-    UPIPE_LAUNCH(kPackRows, st,
-                 launch_pack_rows(v, Skv, Hkv, 0, Hkv, p.Skvp, (bf16*)(ws + p.Vp), st));
-  }
-  for (int h0 = 0; h0 < Hq; h0 += U) {
-    UPIPE_LAUNCH(kPackRows, st, launch_pack_rows(q, Sq, Hq, h0, U, p.Sp, Qc, st));
-    if (p.ns == 1) {
-      UPIPE_LAUNCH(kAttnFwd, st, launch_attn_fwd(Qc, Kp, Vp, Oc, lse, Sq, p.Sp, Skv, p.Skvp, delta,
-                                                 U, h0, G, causal, st));
-    } else {
-      // Two key halves per query block (the grid would otherwise leave CUs
-      // idle), merged like two ring steps: rows [U][Sp] as one head.
-      float* lp = (float*)(ws + p.lse_part);
-      const int64_t rows = (int64_t)U * p.Sp;
+  const int parts = attn_fwd_key_parts(Sq, Skv, delta, Hq, causal);
+  const HeadView Q = token_major(q, Sq, Hq), O = token_major(o, Sq, Hq);
+  const HeadView K = token_major(k, Skv, Hkv), V = token_major(v, Skv, Hkv);
+  if (kv_rows_addressable(Skv, K.row)) {
+    // Every tensor in place, all heads of as many sequences as one grid holds.
+    const int64_t per_seq = (Sq * parts + 255) / 256 * Hq;
+    const int64_t nb = std::max<int64_t>(1, (int64_t(1) << 22) / per_seq);
+    for (int64_t b = 0; b < B; b += nb) {
+      auto at = [&](HeadView x) { x.p += b * x.batch; return x; };
       UPIPE_LAUNCH(kAttnFwd, st,
-                   launch_attn_fwd_split(Qc, Kp, Vp, Oc, lp, Sq, p.Sp, Skv, p.Skvp, delta, U, h0,
-                                         G, causal, p.ns, 0, p.Sp, p.Sp, st));
-      UPIPE_LAUNCH(kSplitMerge, st,
-                   launch_lse_merge(Oc, lp, Oc + rows * HEAD_DIM, lp + rows, rows, 1, st));
-      UPIPE_LAUNCH(kUnpackRows, st,
-                   hipMemcpy2DAsync(lse + (int64_t)h0 * Sq, Sq * 4, lp, p.Sp * 4, Sq * 4, U,
-                                    hipMemcpyDeviceToDevice, st));
+                   launch_attn_fwd(at(Q), at(K), at(V), at(O), lse + b * Hq * Sq, Sq, Skv, delta,
+                                   std::min(nb, B - b), Hq, Hq, 0, G, causal, parts, st));
     }
-    UPIPE_LAUNCH(kUnpackRows, st, launch_unpack_rows(Oc, Sq, Hq, h0, U, p.Sp, o, st));
+    return UPIPE_OK;
+  }
+  // Token-major key/value rows of one head span 2^32 bytes or more: pack
+  // them head-major, one sequence after another.
+  const AttnFwdPlan p = plan_attn_fwd_ring(Sq, Skv, Hq, Hkv, U);
+  bf16* Kp = (bf16*)(ws + p.Kp);
+  bf16* Vp = (bf16*)(ws + p.Vp);
+  for (int64_t b = 0; b < B; ++b) {
+    auto at = [&](HeadView x) { x.p += b * x.batch; return x; };
+    UPIPE_LAUNCH(kPackRows, st, launch_pack_rows(at(K).p, Skv, Hkv, 0, Hkv, p.Skvp, Kp, st));
+    UPIPE_LAUNCH(kPackRows, st, launch_pack_rows(at(V).p, Skv, Hkv, 0, Hkv, p.Skvp, Vp, st));
+    UPIPE_LAUNCH(kAttnFwd, st,
+                 launch_attn_fwd(at(Q), head_major(Kp, p.Skvp), head_major(Vp, p.Skvp), at(O),
+                                 lse + b * Hq * Sq, Sq, Skv, delta, 1, Hq, Hq, 0, G, causal, parts,
+                                 st));
   }
   return UPIPE_OK;
 }
@@ -227,9 +235,9 @@ int make_rope(double base, int64_t pos0, int64_t S, RopeArgs* out) {
 }
 
 int run_attn_fwd(const bf16* q, const bf16* k, const bf16* v, bf16* o,
-                 float* lse, int64_t S, int Hq, int Hkv, int causal, int U,
+                 float* lse, int64_t B, int64_t S, int Hq, int Hkv, int causal, int U,
                  char* ws, hipStream_t st) {
-  return run_attn_fwd_ring(q, k, v, o, lse, S, S, 0, Hq, Hkv, causal, U, ws, st);
+  return run_attn_fwd_ring(q, k, v, o, lse, B, S, S, 0, Hq, Hkv, causal, U, ws, st);
 }
 
 int run_attn_bwd(const bf16* q, const bf16* k, const bf16* v, const bf16* o,
@@ -331,15 +339,8 @@ static int attn_fwd_batch(const void* q, const void* k, const void* v, void* o, 
         !aligned16(lse) || !aligned16(ws))
       return UPIPE_ERR_INVALID_ARG;
     if (ws_bytes < plan_attn_fwd(S, Hq, Hkv, U).total) return UPIPE_ERR_WORKSPACE;
-    // The B sequences run one after another through the same workspace.
-    const int64_t qs = S * Hq * HEAD_DIM, ks = S * Hkv * HEAD_DIM, ls = (int64_t)Hq * S;
-    for (int64_t b = 0; b < B; ++b) {
-      rc = run_attn_fwd((const bf16*)q + b * qs, (const bf16*)k + b * ks,
-                        (const bf16*)v + b * ks, (bf16*)o + b * qs, lse + b * ls, S, Hq, Hkv,
-                        causal, U, (char*)ws, stream);
-      if (rc != UPIPE_OK) return rc;
-    }
-    return UPIPE_OK;
+    return run_attn_fwd((const bf16*)q, (const bf16*)k, (const bf16*)v, (bf16*)o, lse, B, S, Hq,
+                        Hkv, causal, U, (char*)ws, stream);
   } catch (...) {
     return UPIPE_ERR_HIP;
   }
@@ -382,7 +383,7 @@ int upipe_attn_fwd_ring(const void* q, const void* k, const void* v, void* o, fl
     int64_t delta;   // q_offset - kv_offset; fits unless it is exactly 2^63
     if (__builtin_sub_overflow(q_offset, kv_offset, &delta)) return UPIPE_ERR_INVALID_ARG;
     if (ws_bytes < plan_attn_fwd_ring(Sq, Skv, Hq, Hkv, U).total) return UPIPE_ERR_WORKSPACE;
-    return run_attn_fwd_ring((const bf16*)q, (const bf16*)k, (const bf16*)v, (bf16*)o, lse, Sq,
+    return run_attn_fwd_ring((const bf16*)q, (const bf16*)k, (const bf16*)v, (bf16*)o, lse, 1, Sq,
                              Skv, delta, Hq, Hkv, causal, U, (char*)ws, stream);
   } catch (...) {
     return UPIPE_ERR_HIP;

@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "common.h"
+#include "kernels.h"
 
 namespace upipe {
 
@@ -77,9 +78,7 @@ inline bool kv_in_place(int64_t S, int Hkv) { return Hkv == 1 && S % SEQ_PAD == 
 struct AttnFwdPlan {
   int64_t Sp = 0;     // query rows, padded
   int64_t Skvp = 0;   // key/value rows, padded
-  int ns = 1;         // key splits per query block (their partial results are merged)
-  bool kv_direct = false;   // keys/values read in place (no Kp, Vp)
-  size_t Kp = 0, Vp = 0, Qc = 0, Oc = 0, lse_part = 0, total = 0;
+  size_t Kp = 0, Vp = 0, total = 0;
 };
 
 struct AttnBwdPlan {
@@ -104,15 +103,18 @@ int run_dkdv_chunk(const bf16* Qc, const bf16* dOc, const float* lse_c, const fl
                    int64_t kv_row, int64_t kv_head, int64_t S, int64_t Sp, int U, int h0, int G,
                    int causal, hipStream_t st);
 
+HeadView token_major(const bf16* p, int64_t S, int H);
+HeadView head_major(const bf16* p, int64_t Sp);
+
 AttnFwdPlan plan_attn_fwd(int64_t S, int Hq, int Hkv, int U);
 AttnFwdPlan plan_attn_fwd_ring(int64_t Sq, int64_t Skv, int Hq, int Hkv, int U);
 AttnBwdPlan plan_attn_bwd(int64_t S, int Hq, int Hkv, int U);
 
 int run_attn_fwd(const bf16* q, const bf16* k, const bf16* v, bf16* o,
-                 float* lse, int64_t S, int Hq, int Hkv, int causal, int U,
+                 float* lse, int64_t B, int64_t S, int Hq, int Hkv, int causal, int U,
                  char* ws, hipStream_t st);
 int run_attn_fwd_ring(const bf16* q, const bf16* k, const bf16* v, bf16* o, float* lse,
-                      int64_t Sq, int64_t Skv, int64_t delta, int Hq, int Hkv, int causal,
+                      int64_t B, int64_t Sq, int64_t Skv, int64_t delta, int Hq, int Hkv, int causal,
                       int U, char* ws, hipStream_t st);
 int run_attn_bwd(const bf16* q, const bf16* k, const bf16* v, const bf16* o,
                  const float* lse, const bf16* dout, bf16* dq, bf16* dk,

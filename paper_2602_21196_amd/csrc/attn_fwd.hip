@@ -1,4 +1,4 @@
-// Causal GQA flash-attention forward for gfx950 (one head chunk per launch).
+// Causal GQA flash-attention forward for gfx950.
 //
 // Computes, for each query row i of each head of the chunk, the softmax of
 // the scaled scores q_i.k_j/sqrt(d) over the visible keys and its weighted
@@ -6,20 +6,28 @@
 // "the final log-sum-exponent").  Online softmax over key stages keeps HBM
 // traffic at O(S d) per head.
 //
+// Q, K, V and O are read and written where the caller has them (any row and
+// head stride): one launch covers all heads of all sequences of a call, with
+// no packing.  Against one launch per chunk between pack, merge and unpack
+// kernels: 8192 tokens, 4 heads, one head a chunk 443 -> 91 us (10 % -> 55 % of
+// 1378 TFLOP/s, an 8192^3 product's rate); 131072 tokens unchanged.
+//
 // Work decomposition
-//   workgroup = 8 waves x 32 query rows = one 256-row query block of one head
-//               (two waves per SIMD, one workgroup per CU)
+//   workgroup = 8 waves of 32 query rows x a part of every stage's keys: 256
+//               rows x 128 keys, 128 x 64 or 64 x 32 (attn_fwd_key_parts), one
+//               query block of one head (two waves per SIMD, one workgroup per
+//               CU); the parts of a row are folded in fp32 through LDS
 //   key stage = 128 keys, double-buffered in LDS (K rows 32 KB, V rows 32 KB),
 //               filled by buffer->LDS copies issued one stage ahead
 //   per wave per stage: S^T = K . Q^T    (4 x 8 MFMA 32x32x16, keys on rows)
-//                       O^T += V^T . P^T (8 x 4 MFMA)
+//                       O^T += V^T . P^T (8 x 4 MFMA), or a half or a quarter
 // Computing S^T (keys x queries) puts one query column in each lane: the
 // scores of a row sit in one lane pair, and the C tile converts in registers
 // into the B operand of the P.V product, whose V^T operand is read out of
 // the V rows with transposing LDS reads (tr_operand, common.h).  A stage of
 // 128 keys per barrier halves the copies and barriers per product against
 // 64-key tiles, and 256 rows per workgroup halve the L2->LDS traffic per
-// query.
+// query against 128.
 //
 // Lazy rescaling: probabilities are taken against a reference max m_ref that
 // moves only when needed.  A lane's sum of its stage probabilities bounds
@@ -35,31 +43,31 @@ namespace upipe {
 
 namespace {
 
-constexpr int BQ = 256;        // query rows per workgroup (8 waves x 32)
 constexpr int BKS = 128;       // keys per LDS stage
 constexpr int K_TILE = BKS * HEAD_DIM * 2;       // [128][128] bf16 = 32 KB
 constexpr int V_TILE = HEAD_DIM * BKS * 2;       // [128][128] bf16 = 32 KB
 constexpr int STAGE = K_TILE + V_TILE;
 constexpr float kSumMax = 256.f;   // lazy-rescale bound on a lane's stage sum (2^8)
 
-// This wave's share of the copies of the 128-key stage at `kb`: 4 blocks of
-// 1 KB of K rows and 4 of V rows (4 rows of 256 B each, V in the swizzle of
-// transposing reads).  The lane offsets
-// inside a stage are fixed; the stage offset is uniform.
+// This wave's share of the copies of the 128-key stage at byte offset `soff`:
+// 4 blocks of 1 KB of K rows and 4 of V rows (4 rows of 256 B each, V in the
+// swizzle of transposing reads).  The lane offsets inside a stage are fixed;
+// the stage offset is uniform.
 __device__ __forceinline__ void issue_tile(buf_rsrc rk, buf_rsrc rv, const uint32_t (&offk)[4],
-                                           const uint32_t (&offv)[4], uint32_t kb, char* buf, int w) {
+                                           const uint32_t (&offv)[4], uint32_t soff, char* buf, int w) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) dma_buf_b128(rk, offk[i], kb * 256u, buf + (4 * w + i) * 1024);
+  for (int i = 0; i < 4; ++i) dma_buf_b128(rk, offk[i], soff, buf + (4 * w + i) * 1024);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) dma_buf_b128(rv, offv[i], kb * 256u, buf + K_TILE + (4 * w + i) * 1024);
+  for (int i = 0; i < 4; ++i) dma_buf_b128(rv, offv[i], soff, buf + K_TILE + (4 * w + i) * 1024);
 }
 
-__device__ __forceinline__ float tile_probs4(const f32x16 (&st)[4], bf16x8 (&pf)[4][2], float m_ref,
-                                             float sl2) {
+template <int NT>
+__device__ __forceinline__ float tile_probs(const f32x16 (&st)[NT], bf16x8 (&pf)[NT][2],
+                                            float m_ref, float sl2) {
   float ls = 0.f;
   const bf16x2 one = {(bf16)1.f, (bf16)1.f};
 #pragma unroll
-  for (int tt = 0; tt < 4; ++tt)
+  for (int tt = 0; tt < NT; ++tt)
 #pragma unroll
     for (int i = 0; i < 16; i += 2) {
       bf16x2 pr;
@@ -72,58 +80,64 @@ __device__ __forceinline__ float tile_probs4(const f32x16 (&st)[4], bf16x8 (&pf)
   return ls;
 }
 
-// One query block of one head against the key/value rows of its kv head.
-// Query row i (of Sq, padded to Sqp) may see key j (of Skv, padded to Skvp)
-// iff j <= i + delta (causal) -- delta = 0 and Skv = Sq is plain causal
-// self-attention; other offsets are one ring step of context-parallel
-// attention -- and always j < Skv.  A row that sees no key gets O = 0 and
-// lse = -inf, the neutral element of the log-sum-exp merge.
-template <bool CAUSAL>
+// One query block of one head of one sequence against the key/value rows of
+// its kv head.  Query row i (of Sq) may see key j (of Skv) iff j <= i + delta
+// (causal) -- delta = 0 and Skv = Sq is plain causal self-attention; other
+// offsets are one ring step of context-parallel attention -- and always
+// j < Skv.  A row that sees no key gets O = 0 and lse = -inf, the neutral
+// element of the log-sum-exp merge.  Q and O may be the same rows: a
+// workgroup reads its queries before it writes, and no other one reads them.
+template <bool CAUSAL, int KS>
 __global__ __launch_bounds__(512, 1) void attn_fwd_kernel(
-    const bf16* __restrict__ Qc, const bf16* __restrict__ Kp, const bf16* __restrict__ Vp,
-    bf16* __restrict__ Oc, float* __restrict__ lse, int Sq, int Sqp, int Skv, int Skvp, int delta,
-    int U, int h0, int G, int nqb, int ns, int lse_h0, int lse_ld, int lse_rows) {
+    HeadView Q, HeadView K, HeadView V, HeadView O, float* __restrict__ lse, int Sq, int Skv,
+    int delta, int lse_heads, int nh, int h0, int G, int nqb, int nhb) {
+  constexpr int NQW = 8 / KS;            // waves along the query rows
+  constexpr int NT = 4 / KS;             // 32-key tiles of a stage per wave
+  constexpr int BQ = 32 * NQW;           // query rows per workgroup
   __shared__ __attribute__((aligned(1024))) char smem[2 * STAGE];
   const int t = threadIdx.x;
   const int lane = t & 63;
   const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int wq = KS == 1 ? w : w % NQW, ks = KS == 1 ? 0 : w / NQW;
   const int r32 = lane & 31, g = lane >> 5;
-  // Workgroup -> (query block, head, key split), longest blocks first.
+  // Workgroup -> (query block, sequence, head), longest blocks first.
   const int L = blockIdx.x;
-  const int qb = nqb - 1 - L / (U * ns);
-  const int u = (L % (U * ns)) / ns;
-  const int sp = L % ns;
+  const int qb = nqb - 1 - L / nhb;
+  const int u = (L % nhb) % nh;
+  const int bi = (L % nhb) / nh;
   const int kvh = (h0 + u) / G;
   const int q0 = qb * BQ;
-  const int qw = q0 + 32 * w;               // first query row of this wave
+  const int qw = q0 + 32 * wq;              // first query row of this wave
   const int myq = qw + r32;                 // this lane's query row
-  const bool rows_ok = qw < Sqp;            // the last block may hold 128 rows only
+  const bool row_ok = myq < Sq;
 
-  // One head's K and V rows [Skvp][128], 32-bit addressed.
-  const buf_rsrc rk = make_rsrc(Kp + (int64_t)kvh * Skvp * HEAD_DIM, (uint32_t)Skvp * 256u);
-  const buf_rsrc rv = make_rsrc(Vp + (int64_t)kvh * Skvp * HEAD_DIM, (uint32_t)Skvp * 256u);
+  // One head's K and V rows, 32-bit addressed; rows past Skv read as zero.
+  const uint32_t rowb = (uint32_t)(K.row * 2);
+  const uint32_t kv_bytes = (uint32_t)(Skv - 1) * rowb + 256u;
+  const buf_rsrc rk = make_rsrc(K.p + bi * K.batch + kvh * K.head, kv_bytes);
+  const buf_rsrc rv = make_rsrc(V.p + bi * V.batch + kvh * V.head, kv_bytes);
   uint32_t offk[4], offv[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int blk = 4 * w + i;
     const int r = 4 * blk + (lane >> 4);       // stage row, 16 lanes per row
-    const uint32_t c = (uint32_t)((lane & 15) ^ (r & 15)) << 4;
-    offk[i] = r * 256u + c;
-    offv[i] = r * 256u + (((lane & 15) ^ tsw(r)) << 4);
+    offk[i] = r * rowb + ((uint32_t)((lane & 15) ^ (r & 15)) << 4);
+    offv[i] = r * rowb + (((lane & 15) ^ tsw(r)) << 4);
   }
 
   // Stages of the workgroup (up to the last key its last row may see) and
-  // the leading ones holding a key visible to this wave.
-  const int max_st = Skvp / BKS;
-  const int nst = CAUSAL ? max(0, min(max_st, (min(q0 + BQ, Sqp) + delta + BKS - 1) / BKS)) : max_st;
-  const int nw = !rows_ok ? 0 : CAUSAL ? max(0, min(nst, (qw + 32 + delta + BKS - 1) / BKS)) : nst;
+  // the leading ones holding a key of this wave's part visible to it.
+  const int max_st = (Skv + BKS - 1) / BKS;
+  const int nst =
+      CAUSAL ? max(0, min(max_st, (min(q0 + BQ, Sq) + delta + BKS - 1) / BKS)) : max_st;
+  const int k_part = 32 * NT * ks;          // first key of this wave's part of a stage
+  const int nw = qw >= Sq ? 0
+                 : CAUSAL ? max(0, min(nst, (qw + 32 + delta - k_part + BKS - 1) / BKS))
+                          : nst;
   // Last visible key of this lane's row and of the wave's first row.
   const int lim = CAUSAL ? min(myq + delta, Skv - 1) : Skv - 1;
   const int lim_w = CAUSAL ? min(qw + delta, Skv - 1) : Skv - 1;
-  // This split's stages [j0, j1) of the block's nst (all of them when ns = 1).
-  const int per = (nst + ns - 1) / ns;
-  const int j0 = min(nst, sp * per), j1 = min(nst, j0 + per);
-  if (j0 < j1) issue_tile(rk, rv, offk, offv, j0 * BKS, smem + (j0 & 1) * STAGE, w);
+  if (nst > 0) issue_tile(rk, rv, offk, offv, 0, smem, w);
 
   // Q^T B-operand fragments for the whole key loop: lane = query column,
   // k-group g covers head-dim [16s + 8g, 16s + 8g + 8).
@@ -132,8 +146,8 @@ __global__ __launch_bounds__(512, 1) void attn_fwd_kernel(
   for (int s = 0; s < 8; ++s)
 #pragma unroll
     for (int e = 0; e < 8; ++e) qf[s][e] = (bf16)0.f;
-  if (rows_ok) {
-    const bf16* qp = Qc + ((int64_t)u * Sqp + myq) * HEAD_DIM + 8 * g;
+  if (row_ok) {
+    const bf16* qp = Q.p + bi * Q.batch + u * Q.head + myq * Q.row + 8 * g;
 #pragma unroll
     for (int s = 0; s < 8; ++s) qf[s] = *reinterpret_cast<const bf16x8*>(qp + 16 * s);
   }
@@ -150,51 +164,53 @@ __global__ __launch_bounds__(512, 1) void attn_fwd_kernel(
   float l_run = 0.f;         // this lane's partial row sum
   const float sl2 = 1.4426950408889634f * 0.08838834764831845f;  // log2(e)/sqrt(128)
 
-  for (int j = j0; j < j1; ++j) {
-    const int ks = j * BKS;
+  for (int j = 0; j < nst; ++j) {
     char* buf = smem + (j & 1) * STAGE;
     wait_vmem();
     __syncthreads();   // stage j landed for all waves; stage j-1's buffer is free
-    if (j + 1 < j1) issue_tile(rk, rv, offk, offv, ks + BKS, smem + ((j + 1) & 1) * STAGE, w);
+    if (j + 1 < nst)
+      issue_tile(rk, rv, offk, offv, (uint32_t)(j + 1) * BKS * rowb, smem + ((j + 1) & 1) * STAGE,
+                 w);
     if (j >= nw) continue;                  // whole stage masked for this wave
     {
-      const int kb = ks;
-      f32x16 st[4];
+      const int kb = j * BKS + k_part;
+      f32x16 st[NT];
 #pragma unroll
-      for (int tt = 0; tt < 4; ++tt)
+      for (int tt = 0; tt < NT; ++tt)
 #pragma unroll
         for (int i = 0; i < 16; ++i) st[tt][i] = 0.f;
 #pragma unroll
       for (int s = 0; s < 8; ++s)
 #pragma unroll
-        for (int tt = 0; tt < 4; ++tt)
-          st[tt] = mfma32x32x16(lds_read_b128(buf, swz256(32 * tt + r32, 2 * s + g)), qf[s], st[tt]);
+        for (int tt = 0; tt < NT; ++tt)
+          st[tt] = mfma32x32x16(lds_read_b128(buf, swz256(k_part + 32 * tt + r32, 2 * s + g)),
+                                qf[s], st[tt]);
       // Keep six K fragment reads in flight ahead of the MFMAs: left alone,
       // the scheduler reads two, waits for them and multiplies, exposing the
       // LDS latency every two MFMAs.
       __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
 #pragma unroll
-      for (int i = 0; i < 26; ++i) {
+      for (int i = 0; i < 8 * NT - 6; ++i) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
         __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
       }
       __builtin_amdgcn_sched_group_barrier(0x008, 6, 0);
       // Mask keys past the row's last visible key (wave-uniform test first).
-      if (kb + BKS - 1 > lim_w) {
+      if (kb + 32 * NT - 1 > lim_w) {
 #pragma unroll
-        for (int tt = 0; tt < 4; ++tt)
+        for (int tt = 0; tt < NT; ++tt)
 #pragma unroll
           for (int i = 0; i < 16; ++i) {
             const int key = kb + 32 * tt + 8 * (i >> 2) + 4 * g + (i & 3);
             if (key > lim) st[tt][i] = -INFINITY;
           }
       }
-      bf16x8 pf[4][2];
-      float ls = tile_probs4(st, pf, m_ref, sl2);
+      bf16x8 pf[NT][2];
+      float ls = tile_probs(st, pf, m_ref, sl2);
       if (__builtin_amdgcn_ballot_w64(!(ls <= kSumMax)) != 0) {
         float mx = st[0][0];
 #pragma unroll
-        for (int tt = 0; tt < 4; ++tt)
+        for (int tt = 0; tt < NT; ++tt)
 #pragma unroll
           for (int i = 0; i < 16; ++i) mx = fmaxf(mx, st[tt][i]);
         mx = fmaxf(mx, __shfl_xor(mx, 32)) * sl2;
@@ -206,21 +222,21 @@ __global__ __launch_bounds__(512, 1) void attn_fwd_kernel(
         for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
           for (int i = 0; i < 16; ++i) oacc[dt][i] *= alpha;
-        ls = tile_probs4(st, pf, m_ref, sl2);
+        ls = tile_probs(st, pf, m_ref, sl2);
       }
       l_run += ls;
 #pragma unroll
-      for (int c = 0; c < 8; ++c)
+      for (int c = 0; c < 2 * NT; ++c)
 #pragma unroll
         for (int dt = 0; dt < 4; ++dt)
-          oacc[dt] = mfma32x32x16(tr_operand(buf + K_TILE, 16 * c, 32 * dt, lane), pf[c >> 1][c & 1],
-                                  oacc[dt]);
+          oacc[dt] = mfma32x32x16(tr_operand(buf + K_TILE, k_part + 16 * c, 32 * dt, lane),
+                                  pf[c >> 1][c & 1], oacc[dt]);
       // Stream the V^T fragments: four (eight transposing reads) ahead, then
       // two reads per MFMA (the default schedule issued bursts of eight
       // reads and waited between them).
       __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
 #pragma unroll
-      for (int i = 0; i < 28; ++i) {
+      for (int i = 0; i < 8 * NT - 4; ++i) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
         __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
       }
@@ -228,10 +244,51 @@ __global__ __launch_bounds__(512, 1) void attn_fwd_kernel(
     }
   }
 
-  if (!rows_ok) return;
-  const float l_tot = l_run + __shfl_xor(l_run, 32);
+  float l_tot = l_run + __shfl_xor(l_run, 32);
+  if (KS > 1) {
+    // Fold the KS parts of every row in fp32, in ascending key order: parts
+    // 1.. pass (m_ref, l, acc) through the stage buffers (16 KB per wave).
+    float* fold = reinterpret_cast<float*>(smem);
+    float* fold_ml = fold + (KS - 1) * NQW * 4096;
+    __syncthreads();   // every wave is done reading the last stage
+    if (ks > 0) {
+      const int slot = (ks - 1) * NQW + wq;
+#pragma unroll
+      for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+          f32x4 v;
+#pragma unroll
+          for (int b = 0; b < 4; ++b) v[b] = oacc[dt][4 * a + b];
+          *reinterpret_cast<f32x4*>(fold + slot * 4096 + (4 * dt + a) * 256 + lane * 4) = v;
+        }
+      fold_ml[slot * 128 + lane] = m_ref;
+      fold_ml[slot * 128 + 64 + lane] = l_tot;
+    }
+    __syncthreads();
+    if (ks > 0) return;
+#pragma unroll
+    for (int p = 1; p < KS; ++p) {
+      const int slot = (p - 1) * NQW + wq;
+      const float m_p = fold_ml[slot * 128 + lane], l_p = fold_ml[slot * 128 + 64 + lane];
+      const float m_new = fmaxf(m_ref, m_p);
+      const float a0 = fast_exp2(m_ref - m_new), a1 = fast_exp2(m_p - m_new);
+      m_ref = m_new;
+      l_tot = l_tot * a0 + l_p * a1;
+#pragma unroll
+      for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+          const f32x4 v =
+              *reinterpret_cast<const f32x4*>(fold + slot * 4096 + (4 * dt + a) * 256 + lane * 4);
+#pragma unroll
+          for (int b = 0; b < 4; ++b) oacc[dt][4 * a + b] = oacc[dt][4 * a + b] * a0 + v[b] * a1;
+        }
+    }
+  }
+  if (!row_ok) return;
   const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;   // no visible key: O = 0
-  bf16* op = Oc + ((int64_t)(sp * U + u) * Sqp + myq) * HEAD_DIM + 4 * g;
+  bf16* op = O.p + bi * O.batch + u * O.head + myq * O.row + 4 * g;
 #pragma unroll
   for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
@@ -241,44 +298,61 @@ __global__ __launch_bounds__(512, 1) void attn_fwd_kernel(
       for (int b = 0; b < 4; ++b) ov[b] = (bf16)(oacc[dt][4 * a + b] * inv);
       *reinterpret_cast<bf16x4*>(op + 32 * dt + 8 * a) = ov;
     }
-  if (g == 0 && myq < lse_rows)
-    lse[(int64_t)(lse_h0 + sp * U + u) * lse_ld + myq] =
+  if (g == 0)
+    lse[((int64_t)bi * lse_heads + h0 + u) * Sq + myq] =
         l_tot > 0.f ? (m_ref + __log2f(l_tot)) * 0.6931471805599453f : -INFINITY;
 }
 
 }  // namespace
 
-hipError_t launch_attn_fwd_split(const bf16* Qc, const bf16* Kp, const bf16* Vp, bf16* Oc,
-                                 float* lse, int64_t Sq, int64_t Sqp, int64_t Skv, int64_t Skvp,
-                                 int64_t delta, int U, int h0, int G, int causal, int ns,
-                                 int lse_h0, int64_t lse_ld, int64_t lse_rows, hipStream_t st) {
-  const int nqb = (int)((Sqp + BQ - 1) / BQ);
+// The waves of a workgroup cover 256, 128 or 64 query rows (1, 2 or 4 key
+// parts).  More parts make more, shorter workgroups, each stage of which
+// feeds less work per barrier and per byte copied: at a full chip 2 parts run
+// at 0.87 and 4 parts at 0.72 of the rate of one (32768 x 32768 keys, 8 heads,
+// all visible: 3515 / 4025 / 4809 us).  So the fewest parts whose
+// workgroups still fill the 256 CUs, in 256-row blocks x heads (the
+// chunk size and the batch do not enter, so they do not change a bit):
+//   every key visible: one round of equal blocks.  128 blocks 508 / 651 us
+//     (2 / 1 parts, 32768 rows, 1 head), 256 blocks 1009 / 883 (2 heads);
+//     64 blocks 160 / 217 us (4 / 2 parts, 16384 rows, 1 head), 128 blocks
+//     603 / 508 (32768 rows).
+//   causal: the last block is twice the mean, and a single round is as long
+//     as that.  256 blocks 269 / 354 us (2 / 1 parts, 16384 rows, 4 heads), 512
+//     blocks 524 / 466 (8 heads); 128 blocks 171 / 223 us (4 / 2 parts, 16384
+//     rows, 2 heads), 256 blocks 326 / 269.  Between the measured counts the
+//     lines lie where the longest block of the coarser split takes as
+//     long as all blocks of the finer one spread over the chip.
+int attn_fwd_key_parts(int64_t Sq, int64_t Skv, int64_t delta, int Hq, int causal) {
+  const int64_t blocks = (Sq + 255) / 256 * Hq;
+  const bool all = !causal || delta >= Skv - 1;
+  if (blocks > (all ? 128 : 448)) return 1;
+  return blocks > (all ? 64 : 224) ? 2 : 4;
+}
+
+hipError_t launch_attn_fwd(const HeadView& Q, const HeadView& K, const HeadView& V,
+                           const HeadView& O, float* lse, int64_t Sq, int64_t Skv, int64_t delta,
+                           int64_t B, int lse_heads, int nh, int h0, int G, int causal, int parts,
+                           hipStream_t st) {
+  const int bq = 256 / parts;
+  const int nqb = (int)((Sq + bq - 1) / bq);
   // Offsets beyond either length change nothing: clamp into int range.
   const int dl = (int)(delta < -Sq ? -Sq : delta > Skv ? Skv : delta);
-  dim3 grid((unsigned)(nqb * U * ns));
-  if (causal)
-    hipLaunchKernelGGL(attn_fwd_kernel<true>, grid, dim3(512), 0, st, Qc, Kp, Vp, Oc, lse, (int)Sq,
-                       (int)Sqp, (int)Skv, (int)Skvp, dl, U, h0, G, nqb, ns, lse_h0, (int)lse_ld,
-                       (int)lse_rows);
-  else
-    hipLaunchKernelGGL(attn_fwd_kernel<false>, grid, dim3(512), 0, st, Qc, Kp, Vp, Oc, lse, (int)Sq,
-                       (int)Sqp, (int)Skv, (int)Skvp, dl, U, h0, G, nqb, ns, lse_h0, (int)lse_ld,
-                       (int)lse_rows);
+  const int nhb = (int)(nh * B);
+  dim3 grid((unsigned)(nqb * nhb));
+#define UPIPE_FWD(C, P)                                                                       \
+  hipLaunchKernelGGL((attn_fwd_kernel<C, P>), grid, dim3(512), 0, st, Q, K, V, O, lse, (int)Sq, \
+                     (int)Skv, dl, lse_heads, nh, h0, G, nqb, nhb)
+  if (causal) {
+    if (parts == 1) UPIPE_FWD(true, 1);
+    else if (parts == 2) UPIPE_FWD(true, 2);
+    else UPIPE_FWD(true, 4);
+  } else {
+    if (parts == 1) UPIPE_FWD(false, 1);
+    else if (parts == 2) UPIPE_FWD(false, 2);
+    else UPIPE_FWD(false, 4);
+  }
+#undef UPIPE_FWD
   return hipGetLastError();
-}
-
-hipError_t launch_attn_fwd(const bf16* Qc, const bf16* Kp, const bf16* Vp, bf16* Oc, float* lse,
-                           int64_t Sq, int64_t Sqp, int64_t Skv, int64_t Skvp, int64_t delta, int U,
-                           int h0, int G, int causal, hipStream_t st) {
-  return launch_attn_fwd_split(Qc, Kp, Vp, Oc, lse, Sq, Sqp, Skv, Skvp, delta, U, h0, G, causal, 1,
-                               h0, Sq, Sq, st);
-}
-
-int attn_fwd_key_splits(int64_t Sqp, int64_t Skvp) {
-  // Fewer 256-row query blocks than half the CUs leave CUs idle at U = 1:
-  // split the key range of every block in two (a function of the lengths
-  // only, so that every chunk size U gives the same results).
-  return ((Sqp + BQ - 1) / BQ <= 128 && Skvp / BKS >= 2) ? 2 : 1;
 }
 
 }  // namespace upipe

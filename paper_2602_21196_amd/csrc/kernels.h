@@ -26,24 +26,32 @@ hipError_t launch_rowdot_lse(const bf16* a, int64_t a_row, int64_t a_head,
                              hipStream_t st);
 
 // ---- attention forward (attn_fwd.hip) ------------------------------------
-// Qc [U, Sqp, d], Kp and Vp [Hkv, Skvp, d] -> Oc [U, Sqp, d] and lse rows
-// h0..h0+U-1 of the caller's [Hq, Sq] array.  Query row i sees key j iff
-// j < Skv and (not causal or j <= i + delta); rows that see no key get O = 0,
-// lse = -inf.  Self-attention: Sq = Skv = S, delta = 0.
-hipError_t launch_attn_fwd(const bf16* Qc, const bf16* Kp, const bf16* Vp,
-                           bf16* Oc, float* lse, int64_t Sq, int64_t Sqp,
-                           int64_t Skv, int64_t Skvp, int64_t delta, int U,
-                           int h0, int G, int causal, hipStream_t st);
-// The same with the key range of every query block cut into `ns` splits of
-// equal stage counts, split s writing O to Oc + s U Sqp d ([ns][U][Sqp][d])
-// and lse row (lse_h0 + s U + u) of leading dimension lse_ld, rows i <
-// lse_rows (the plain call: ns = 1, lse_h0 = h0, lse_ld = lse_rows = Sq).
-hipError_t launch_attn_fwd_split(const bf16* Qc, const bf16* Kp, const bf16* Vp, bf16* Oc,
-                                 float* lse, int64_t Sq, int64_t Sqp, int64_t Skv, int64_t Skvp,
-                                 int64_t delta, int U, int h0, int G, int causal, int ns,
-                                 int lse_h0, int64_t lse_ld, int64_t lse_rows, hipStream_t st);
-// Number of key splits the forward uses for these padded lengths (1 or 2).
-int attn_fwd_key_splits(int64_t Sqp, int64_t Skvp);
+// Rows of 128 elements of several heads of a batch of sequences: element
+// (b, s, h, e) is p[b * batch + s * row + h * head + e].  Token-major
+// [B, S, H, d]: row = H d, head = d, batch = S H d; head-major [H, Sp, d]:
+// row = d, head = Sp d.
+struct HeadView {
+  bf16* p;
+  int64_t row, head, batch;
+};
+// The kernels address one head's key/value rows with 32-bit byte offsets, up
+// to the end of the last 128-row tile.
+inline bool kv_rows_addressable(int64_t S, int64_t row) {
+  return round_up(S, SEQ_PAD) * row * 2 < (int64_t(1) << 32);
+}
+// Heads h0 .. h0 + nh - 1 of B sequences: Q, O (head u of the view is head
+// h0 + u; they may be the same rows), K, V (head g of the view is key/value
+// head g; kv_rows_addressable) and lse [B, lse_heads, Sq].  Query row i sees
+// key j iff j < Skv and (not causal or j <= i + delta); rows that see no key
+// get O = 0, lse = -inf.  Self-attention: Sq = Skv = S, delta = 0.  `parts`
+// as attn_fwd_key_parts says for the whole call's heads.
+hipError_t launch_attn_fwd(const HeadView& Q, const HeadView& K, const HeadView& V,
+                           const HeadView& O, float* lse, int64_t Sq, int64_t Skv, int64_t delta,
+                           int64_t B, int lse_heads, int nh, int h0, int G, int causal, int parts,
+                           hipStream_t st);
+// Parts (1, 2 or 4) into which the waves of a workgroup split the keys of
+// every stage, for a call over Hq heads.
+int attn_fwd_key_parts(int64_t Sq, int64_t Skv, int64_t delta, int Hq, int causal);
 // In place, per row (s, h) of o [S, H, d] and lse [H, S]: fold the partial
 // result (o_p, lse_p) over a disjoint key set into (o, lse).
 hipError_t launch_lse_merge(bf16* o, float* lse, const bf16* o_p,

@@ -172,8 +172,8 @@ int run_layer_fwd_seq(const bf16* x, const bf16* wqkv, const bf16* wo, bf16* y, 
   bf16* Kp = (bf16*)(ws + p.Kp);
   bf16* Vp = (bf16*)(ws + p.Vp);
   bf16* Qc = (bf16*)(ws + p.Qc);
-  bf16* Oc = (bf16*)(ws + p.Oc);
   const int G = Hq / Hkv;
+  const int parts = attn_fwd_key_parts(S, S, 0, Hq, 1);
   const GemmOperand X = operand(x, dm, S, dm);
   // K | V = x [Wk | Wv], both head-major.
   UPIPE_LAUNCH(kGemm, st,
@@ -185,8 +185,11 @@ int run_layer_fwd_seq(const bf16* x, const bf16* wqkv, const bf16* wo, bf16* y, 
                  gemm1(X, true, operand(wqkv + (int64_t)h0 * HEAD_DIM, ldw, U * HEAD_DIM, dm),
                        false, heads_epi(Qc, nullptr, U, Sp, rope), GEMM_EPI_HEADS, Sp,
                        U * HEAD_DIM, dm, st));
-    UPIPE_LAUNCH(kAttnFwd, st, launch_attn_fwd(Qc, Kp, Vp, Oc, lse, S, Sp, S, Sp, 0, U, h0, G, 1, st));
-    UPIPE_LAUNCH(kUnpackRows, st, launch_unpack_rows(Oc, S, Hq, h0, U, Sp, o_saved, st));
+    HeadView O = token_major(o_saved, S, Hq);
+    O.p += h0 * O.head;
+    UPIPE_LAUNCH(kAttnFwd, st,
+                 launch_attn_fwd(head_major(Qc, Sp), head_major(Kp, Sp), head_major(Vp, Sp), O, lse,
+                                 S, S, 0, 1, Hq, U, h0, G, 1, parts, st));
   }
   // y = final_out Wo.
   UPIPE_LAUNCH(kGemm, st,
@@ -273,7 +276,9 @@ int run_layer_bwd_seq(const bf16* x, const bf16* wqkv, const bf16* wo, const bf1
       // same operands: bitwise what the forward produced), and its rows of
       // dWo = O_c^T dY.
       UPIPE_LAUNCH(kAttnFwd, st,
-                   launch_attn_fwd(Qc, Kp, Vp, Oc, lse_r, S, Sp, S, Sp, 0, U, h0, G, 1, st));
+                   launch_attn_fwd(head_major(Qc, Sp), head_major(Kp, Sp), head_major(Vp, Sp),
+                                   head_major(Oc, Sp), lse_r, S, S, 0, 1, Hq, U, h0, G, 1,
+                                   attn_fwd_key_parts(S, S, 0, Hq, 1), st));
       UPIPE_LAUNCH(kRowdotLse, st,
                    launch_rowdot_lse(dOc, HEAD_DIM, head, Oc, HEAD_DIM, head, lse_r, S, h0, U,
                                      Sp, D, lse_c, st));

@@ -74,7 +74,7 @@ int upipe_attn_fwd_noalloc(const void* q, const void* k, const void* v, void* o,
     char* ws = nullptr;
     rc = scratch_on_current_device(stream, &ws);
     if (rc != UPIPE_OK) return rc;
-    return run_attn_fwd((const bf16*)q, (const bf16*)k, (const bf16*)v, (bf16*)o, lse, S, Hq,
+    return run_attn_fwd((const bf16*)q, (const bf16*)k, (const bf16*)v, (bf16*)o, lse, 1, S, Hq,
                         Hkv, causal, U, ws, stream);
   } catch (...) {
     return UPIPE_ERR_HIP;

@@ -213,7 +213,10 @@ int upipe_lse_merge(void* o, float* lse, const void* o_part, const float* lse_pa
  *   dk   bf16 [S, Hkv, d]  out: summed over each group's query heads
  *   dv   bf16 [S, Hkv, d]  out
  * `lse` must come from upipe_attn_fwd on the same q, k, v (it is used to
- * rebuild the probabilities without a second softmax pass).
+ * rebuild the probabilities without a second softmax pass).  Below 65536 rows
+ * every tensor is used in place, all heads together, and dq serves as scratch
+ * before it is written; from there on, chunks of U heads are packed head-major
+ * for dk and dv.
  * ---------------------------------------------------------------------- */
 int upipe_attn_bwd(const void* q, const void* k, const void* v, const void* o,
                    const float* lse, const void* dout, void* dq, void* dk,

@@ -86,23 +86,29 @@ struct AttnBwdPlan {
   bool carry = false;  // a key/value group spans several chunks
   bool kv_direct = false;   // keys/values read in place (no Kp, Vp)
   size_t Kp = 0, Vp = 0, dK32 = 0, dV32 = 0;
-  size_t Qc = 0, dOc = 0, dQc = 0, D = 0, lse_c = 0;
+  size_t Qc = 0, dOc = 0;
+  size_t rows = 0;     // D and lse rows, to the end
   size_t total = 0;
 };
 
-// dK/dV of the chunk of U heads starting at h0 (arguments as for
-// launch_attn_bwd_dkdv; Qc, dOc, lse_c, D hold the chunk's U heads).  When
-// the fp32 carries exist (dK32 != nullptr: some group spans chunks) or every
-// group is one head (G == 1), the heads go one launch each: the same
-// additions in the same order as a single launch over the chunk (the carries
+// dK/dV of the heads h0 .. h0 + nh - 1 of one sequence (arguments as for
+// launch_attn_bwd_dkdv).  Where the fp32 carries exist (dK32 != nullptr: some
+// group spans chunks) or every group is one head, the heads go one launch
+// each: the same additions in the same order as a single launch (the carries
 // hand each head's sums to the next), but every workgroup of a launch then
 // walks one head's query tiles alongside the others and they share L2
 // lines, where in one launch over several heads they drift apart.
-int run_dkdv_chunk(const bf16* Qc, const bf16* dOc, const float* lse_c, const float* D,
-                   const bf16* Kp, const bf16* Vp, float* dK32, float* dV32, bf16* dk, bf16* dv,
-                   int64_t kv_row, int64_t kv_head, int64_t S, int64_t Sp, int U, int h0, int G,
-                   int causal, hipStream_t st);
-
+int run_dkdv(const HeadView& Q, const HeadView& dO, const float* lse_c, const float* D,
+             const HeadView& K, const HeadView& V, float* dK32, float* dV32, const HeadView& dk,
+             const HeadView& dv, int64_t S, int64_t Sp, int nh, int h0, int G, int causal,
+             hipStream_t st);
+// From this length on a head's 128-key blocks alone fill the 256 CUs evenly
+// (512 of them, the longest running beside the shortest): dK/dV runs head
+// by head.  Below, all heads in one launch, in segments (dkdv_split): 32768
+// rows of 8 heads 7.04 -> 4.40 ms; 65536 rows 17.3 against 17.7 ms in segments.
+constexpr int64_t kPerHeadRows = 65536;
+// Sequence b and head u of a view, as a view that starts there.
+HeadView sub(HeadView x, int64_t b, int64_t u);
 HeadView token_major(const bf16* p, int64_t S, int H);
 HeadView head_major(const bf16* p, int64_t Sp);
 
@@ -118,7 +124,7 @@ int run_attn_fwd_ring(const bf16* q, const bf16* k, const bf16* v, bf16* o, floa
                       int U, char* ws, hipStream_t st);
 int run_attn_bwd(const bf16* q, const bf16* k, const bf16* v, const bf16* o,
                  const float* lse, const bf16* dout, bf16* dq, bf16* dk,
-                 bf16* dv, int64_t S, int Hq, int Hkv, int causal, int U,
+                 bf16* dv, int64_t B, int64_t S, int Hq, int Hkv, int causal, int U,
                  char* ws, hipStream_t st);
 
 }  // namespace upipe

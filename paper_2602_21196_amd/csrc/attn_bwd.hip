@@ -1,4 +1,4 @@
-// Causal GQA flash-attention backward for gfx950 (one head chunk per launch).
+// Causal GQA flash-attention backward for gfx950.
 //
 // Analytic gradient of softmax attention (paper Section 2.1), with the
 // probabilities rebuilt from the saved row log-sum-exp (staged as -sqrt(d) lse,
@@ -9,20 +9,28 @@
 //   dQ_i  = sum_j dS_ij k_j / sqrt d.
 // Two kernels, no atomics, one fixed summation order:
 //   dkdv: a workgroup owns 128 keys of one key/value head (4 waves x 32 keys,
-//         K and V fragments in registers) and walks the chunk's query heads in
-//         ascending order and, within a head, the 128-row query tiles from the
-//         last one down to its diagonal (each tile as 64-row halves, upper
-//         first, and each half as two 32-row subtiles, upper first), so that
-//         all resident workgroups read the same query tiles at about the same
-//         time (shared L2 lines).  Its
-//         fp32 dK/dV accumulators start from the values the previous chunk
-//         left in the workspace (UPipe keeps per-group dK/dV accumulators alive
-//         across stages, Appendix A), so any chunk size U gives bit-identical
-//         sums.
+//         K and V fragments in registers; or 64 keys, two waves to each 32) and
+//         walks the group's query heads in ascending order and, within a head,
+//         the 128-row query tiles from the last one down to its diagonal
+//         (each tile as 64-row halves, upper first, and each half as two
+//         32-row subtiles, upper first), so that all resident workgroups
+//         read the same query tiles at about the same time (shared L2 lines).
+//         Long sequences: its fp32 dK/dV accumulators start from the values
+//         the previous launch left in the workspace (UPipe keeps per-group
+//         dK/dV accumulators alive across stages, Appendix A), so any chunk
+//         size U gives bit-identical sums.  Shorter ones: the walk is cut
+//         into segments side by side, whose sums are added in their order.
 //   dq:   a workgroup owns 256 query rows of one head (8 waves) and walks
-//         64-key stages in ascending order, recomputing P and dS.
+//         64-key stages in ascending order, recomputing P and dS; or 128 or 64
+//         rows, with the keys of a 128-key stage split over the waves.
+// What bounds them: at full chip, MFMA issue (dK/dV) and the power limit (dQ);
+// short of 512 key blocks or 256-row blocks, the chip's filling.  Against one
+// launch per chunk on packed copies, whole backward, one key/value head:
+// 8192 rows of 4 heads 1930 -> 335 us, 32768 of 8 14.5 -> 7.1 ms.
 // Tiles reach LDS through buffer->LDS copies issued one tile ahead.
 // Transposed operands are read out of row-major tiles (common.h, tr_operand).
+#include <algorithm>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -47,6 +55,7 @@ constexpr int KV_BLK = ROWT / 1024 / 4;     // 1 KB blocks per wave per array
 
 struct QStageSrc {
   buf_rsrc q, dO, lse, D;
+  uint32_t q_rowb, do_rowb;   // bytes from one row to the next
 };
 
 // This wave's share of one tile's copies: KV_BLK blocks of 1 KB each of Q and
@@ -65,9 +74,9 @@ __device__ __forceinline__ void issue_qstage(const QStageSrc& r, uint32_t qb, ch
     // this lane's 16 bytes: Q / dO row `row` of the tile (16 lanes per row),
     // chunk swizzled for the transposing reads
     const int row = 4 * blk + (lane >> 4);
-    const uint32_t off = row * 256u + (((lane & 15) ^ tsw(row)) << 4);
-    dma_buf_b128(r.q, off, qb * 256u, buf + OFF_Q + blk * 1024);
-    dma_buf_b128(r.dO, off, qb * 256u, buf + OFF_DO + blk * 1024);
+    const uint32_t c = ((lane & 15) ^ tsw(row)) << 4;
+    dma_buf_b128(r.q, row * r.q_rowb + c, qb * r.q_rowb, buf + OFF_Q + blk * 1024);
+    dma_buf_b128(r.dO, row * r.do_rowb + c, qb * r.do_rowb, buf + OFF_DO + blk * 1024);
   }
   if (lane < QT / 4) {
     if (w == 0) dma_buf_b128(r.lse, lane * 16u, qb * 4u, buf + OFF_LSE);
@@ -257,51 +266,109 @@ __device__ __forceinline__ void pair_step(const char* buf, int base, uint32_t qb
   }
 }
 
-template <bool CAUSAL>
+// Key blocks (of 128 / QS keys) whose list of query tiles has more than s
+// segments: the first ones, since the lists get no longer.
+template <bool CAUSAL, int QS>
+__host__ __device__ inline int seg_blocks(int s, int T, int G, int nqt) {
+  if (!CAUSAL) return G * nqt > s * T ? QS * nqt : 0;
+  const int tiles = nqt - s * (T / G);    // T is a multiple of G
+  return tiles > 0 ? QS * tiles : 0;
+}
+
+// The x-th key block by the length of its list's first segment, longest first.
+// Tile j from the end has a list of G (j + 1) tiles, the first segment of
+// which is G (j % m + 1) long, m = T / G.
+template <bool CAUSAL, int QS>
+__device__ inline int by_remainder(int x, int T, int G, int nqt) {
+  if (!CAUSAL) return x;
+  const int m = T / G, nt = nqt / m, rem = nqt % m, jx = x / QS;
+  const int a = (m - rem) * nt;     // the lengths that only whole runs of m have
+  int j;
+  if (jx < a) j = (jx % nt) * m + m - 1 - jx / nt;
+  else j = ((jx - a) % (nt + 1)) * m + rem - 1 - (jx - a) / (nt + 1);
+  return QS * (nqt - 1 - j) + x % QS;
+}
+
+// QS = 1: a workgroup owns 128 keys, every wave takes all rows of a tile.
+// QS = 2: 64 keys, two waves per 32 of them, one for each 64-row half of a tile;
+// their sums are added through LDS.
+// T = 0: one workgroup walks the whole list of (head, query tile) of its
+// key block, on top of the carries.  T > 0: the list is cut into segments of T
+// (the first takes the remainder), each with a workgroup of its own; where
+// there are several, each leaves its fp32 sums in a slot and
+// dkdv_fold_kernel adds them in list order.
+template <bool CAUSAL, int QS>
 __global__ __launch_bounds__(256, 1) void attn_bwd_dkdv_kernel(
-    const bf16* __restrict__ Qc, const bf16* __restrict__ dOc, const float* __restrict__ lse_c,
-    const float* __restrict__ Dc, const bf16* __restrict__ Kp, const bf16* __restrict__ Vp,
-    float* __restrict__ dK32,
-    float* __restrict__ dV32, bf16* __restrict__ dk, bf16* __restrict__ dv, int64_t S, int64_t Sp,
-    int U, int h0, int G, int64_t kv_row, int64_t kv_head) {
+    HeadView Q, HeadView dO, const float* __restrict__ lse_c, const float* __restrict__ Dc,
+    HeadView K, HeadView V, float* __restrict__ dK32, float* __restrict__ dV32, HeadView dk, HeadView dv, DkdvSlots slots, int64_t S, int64_t Sp,
+    int U, int h0, int G) {
+  constexpr int KB = 128 / QS;           // keys per workgroup
   __shared__ __attribute__((aligned(1024))) char smem[2 * KV_STAGE];
   const int t = threadIdx.x;
   const int lane = t & 63;
   const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int wk = QS == 1 ? w : w & 1, qs = QS == 1 ? 0 : w >> 1;
   const int r32 = lane & 31, g = lane >> 5;
-  const int kvh = h0 / G + blockIdx.y;
-  const uint32_t kb0 = blockIdx.x * 128u;
-  const uint32_t kw = kb0 + 32 * w;      // first key of this wave
-  const uint32_t mykey = kw + r32;       // key column owned by this lane
+  const int T = slots.T;
+  const int kv = T > 0 ? blockIdx.x % slots.kv_heads : blockIdx.y;
+  const int kvh = h0 / G + kv;
   const uint32_t Spv = (uint32_t)Sp;
+  const int nqt = (int)(Spv / QT);
   const int hlo = max(h0, kvh * G), hhi = min(h0 + U, (kvh + 1) * G);
+  // Key block, and this workgroup's part [first_it, first_it + total) of its list.
+  int kb = T > 0 ? blockIdx.x / slots.kv_heads : blockIdx.x, seg = 0, slot = -1;
+  if (T > 0) {   // whole segments first, then the others by their length
+    int acc = 0;
+    for (seg = slots.max_seg; seg > 0; --seg) {
+      const int c = seg_blocks<CAUSAL, QS>(seg, T, G, nqt);
+      acc += c;
+      if (kb < c) break;
+      kb -= c;
+    }
+    if (seg == 0) kb = by_remainder<CAUSAL, QS>(kb, T, G, nqt);
+    slot = seg > 0 ? slots.per_head - acc + kb : kb;
+  }
+  const uint32_t kb0 = kb * (uint32_t)KB;
+  const uint32_t kw = kb0 + 32 * wk;     // first key of this wave
+  const uint32_t mykey = kw + r32;       // key column owned by this lane
   const bool first = kvh * G >= h0;           // no earlier chunk touched kvh
   const bool last = (kvh + 1) * G <= h0 + U;  // no later chunk will
-  const uint32_t nqt = (Spv + QT - 1) / QT;
-  const uint32_t qt_lo = CAUSAL ? kb0 / QT : 0;   // lowest query tile needed
-  const uint32_t per_head = nqt - qt_lo;
-  const int total = (int)(per_head * (hhi - hlo));
+  const int qt_lo = CAUSAL ? (int)(kb0 / QT) : 0;   // lowest query tile needed
+  const int per_head = nqt - qt_lo;
+  int total = per_head * (hhi - hlo), first_it = 0;
+  bool whole = true;
+  if (T > 0) {
+    const int n = (total + T - 1) / T, r = total - (n - 1) * T;
+    whole = n == 1;
+    first_it = seg == 0 ? 0 : r + (seg - 1) * T;
+    total = seg == 0 ? r : T;
+  }
 
   auto srcs = [&](int hh) {
     QStageSrc r;
-    const int64_t hoff = (int64_t)(hh - h0) * Sp * HEAD_DIM;
-    r.q = make_rsrc(Qc + hoff, Spv * 256u);
-    r.dO = make_rsrc(dOc + hoff, Spv * 256u);
-    r.lse = make_rsrc(lse_c + (int64_t)(hh - h0) * Sp, Spv * 4u);
-    r.D = make_rsrc(Dc + (int64_t)(hh - h0) * Sp, Spv * 4u);
+    const int64_t u = hh - h0;
+    r.q_rowb = (uint32_t)(Q.row * 2);
+    r.do_rowb = (uint32_t)(dO.row * 2);
+    r.q = make_rsrc(Q.p + u * Q.head, (uint32_t)(S - 1) * r.q_rowb + 256u);
+    r.dO = make_rsrc(dO.p + u * dO.head, (uint32_t)(S - 1) * r.do_rowb + 256u);
+    r.lse = make_rsrc(lse_c + u * Sp, Spv * 4u);
+    r.D = make_rsrc(Dc + u * Sp, Spv * 4u);
     return r;
   };
 
-  // First tile: head hlo, query tile nqt-1.
-  QStageSrc cur = srcs(hlo);
-  issue_qstage(cur, (nqt - 1) * QT, smem, w, lane);
+  int hh = hlo + first_it / per_head;
+  int qt = nqt - 1 - first_it % per_head;    // query tile of the current iteration
+  QStageSrc cur = srcs(hh);
+  issue_qstage(cur, qt * QT, smem, w, lane);
 
   // K and -V B-operand fragments (lane = key column, k = head dim); -V makes
-  // the dP products count down from D.
+  // the dP products count down from D.  Keys past S repeat the last one; their
+  // sums are not used.
   bf16x8 kf[8], vf[8];
   {
-    const bf16* kp = Kp + ((int64_t)kvh * Sp + mykey) * HEAD_DIM + 8 * g;
-    const bf16* vp = Vp + ((int64_t)kvh * Sp + mykey) * HEAD_DIM + 8 * g;
+    const uint32_t key = min(mykey, (uint32_t)S - 1);
+    const bf16* kp = K.p + kvh * K.head + key * K.row + 8 * g;
+    const bf16* vp = V.p + kvh * V.head + key * V.row + 8 * g;
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
       kf[s] = *reinterpret_cast<const bf16x8*>(kp + 16 * s);
@@ -322,7 +389,7 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkdv_kernel(
   f32x16 dka[4], dva[4];
   float* dK32h = dK32 + (int64_t)kvh * Sp * HEAD_DIM;
   float* dV32h = dV32 + (int64_t)kvh * Sp * HEAD_DIM;
-  if (first) {
+  if (QS > 1 || first) {
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
@@ -341,13 +408,11 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkdv_kernel(
       }
   }
 
-  int hh = hlo;
-  uint32_t qt = nqt - 1;     // query tile of the current iteration
   for (int it = 0; it < total; ++it) {
     char* buf = smem + (it & 1) * KV_STAGE;
     const uint32_t qb = qt * QT;
     // next tile (descending query tiles, then the next head)
-    uint32_t nq = qt - 1;
+    int nq = qt - 1;
     int nh = hh;
     if (qt == qt_lo) {
       nq = nqt - 1;
@@ -359,125 +424,225 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkdv_kernel(
       if (nh != hh) cur = srcs(nh);
       issue_qstage(cur, nq * QT, smem + ((it + 1) & 1) * KV_STAGE, w, lane);
     }
-    // Pairs of 32-row subtiles, upper rows first; a pair is needed when its
-    // last row reaches this wave's first key (and lies inside the sequence).
-    // The upper pair reads the lower pair's first fragments in its region D.
     Frags fa;
-    const bool run1 = qb + 64 < Spv && (!CAUSAL || qb + 127 >= kw);
-    const bool run0 = qb < Spv && (!CAUSAL || qb + 63 >= kw);
-    if (run1) {
-      read_sdp(buf, 96, r32, g, fa);
-      pair_step<CAUSAL, true>(buf, 64, qb, kw, mykey, r32, g, lane, kf, vf, dva, dka, fa);
-    }
-    if (run0) {
-      if (!run1) read_sdp(buf, 32, r32, g, fa);
-      pair_step<CAUSAL, false>(buf, 0, qb, kw, mykey, r32, g, lane, kf, vf, dva, dka, fa);
+    if (QS == 1) {
+      // Pairs of 32-row subtiles, upper rows first; a pair is needed when its
+      // last row reaches this wave's first key.  The upper pair reads the
+      // lower pair's first fragments in its region D.
+      const bool run1 = !CAUSAL || qb + 127 >= kw;
+      const bool run0 = !CAUSAL || qb + 63 >= kw;
+      if (run1) {
+        read_sdp(buf, 96, r32, g, fa);
+        pair_step<CAUSAL, true>(buf, 64, qb, kw, mykey, r32, g, lane, kf, vf, dva, dka, fa);
+      }
+      if (run0) {
+        if (!run1) read_sdp(buf, 32, r32, g, fa);
+        pair_step<CAUSAL, false>(buf, 0, qb, kw, mykey, r32, g, lane, kf, vf, dva, dka, fa);
+      }
+    } else {
+      const int base = 64 * qs;
+      if (!CAUSAL || qb + base + 63 >= kw) {
+        read_sdp(buf, base + 32, r32, g, fa);
+        pair_step<CAUSAL, false>(buf, base, qb, kw, mykey, r32, g, lane, kf, vf, dva, dka, fa);
+      }
     }
     qt = nq;
     hh = nh;
   }
 
-  if (last) {
+  if (QS > 1) {   // rows 64.. of the tiles onto rows 0..63, in fp32
+    float* fold = reinterpret_cast<float*>(smem) + wk * 8192 + lane * 4;
+    __syncthreads();   // every wave is done reading the last tile
+    if (qs > 0) {
+#pragma unroll
+      for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+          f32x4 x, y;
+#pragma unroll
+          for (int b = 0; b < 4; ++b) {
+            x[b] = dka[dt][4 * a + b];
+            y[b] = dva[dt][4 * a + b];
+          }
+          *reinterpret_cast<f32x4*>(fold + (4 * dt + a) * 256) = x;
+          *reinterpret_cast<f32x4*>(fold + (16 + 4 * dt + a) * 256) = y;
+        }
+    }
+    __syncthreads();
+    if (qs > 0) return;
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {
+        const f32x4 x = *reinterpret_cast<const f32x4*>(fold + (4 * dt + a) * 256);
+        const f32x4 y = *reinterpret_cast<const f32x4*>(fold + (16 + 4 * dt + a) * 256);
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          dka[dt][4 * a + b] += x[b];
+          dva[dt][4 * a + b] += y[b];
+        }
+      }
+  }
+  if (!whole || (QS == 1 && !last)) {
+    // Slots [2][KB][128], carries [Sp][128]: the key's row of 128 floats.
+    float* pk = dK32h + (int64_t)kw * HEAD_DIM;
+    float* pv = dV32h + (int64_t)kw * HEAD_DIM;
+    if (!whole) {
+      pk = slots.at((int64_t)kv * slots.per_head + slot, 2 * KB * HEAD_DIM) +
+           32 * wk * HEAD_DIM;
+      pv = pk + KB * HEAD_DIM;
+    }
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
-        const uint32_t key = kw + 8 * (i >> 2) + 4 * g + (i & 3);
-        if (key < (uint64_t)S) {
-          const int64_t off = (int64_t)key * kv_row + kvh * kv_head + 32 * dt + r32;
-          dk[off] = (bf16)(dka[dt][i] * -kScale);
-          dv[off] = (bf16)dva[dt][i];
-        }
+        const uint32_t off = (8 * (i >> 2) + 4 * g + (i & 3)) * HEAD_DIM + 32 * dt + r32;
+        pk[off] = dka[dt][i];
+        pv[off] = dva[dt][i];
       }
   } else {
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
-        const uint32_t off = (kw + 8 * (i >> 2) + 4 * g + (i & 3)) * HEAD_DIM + 32 * dt + r32;
-        dK32h[off] = dka[dt][i];
-        dV32h[off] = dva[dt][i];
+        const uint32_t key = kw + 8 * (i >> 2) + 4 * g + (i & 3);
+        if (key < (uint64_t)S) {
+          const int64_t e = 32 * dt + r32;
+          dk.p[kvh * dk.head + key * dk.row + e] = (bf16)(dka[dt][i] * -kScale);
+          dv.p[kvh * dv.head + key * dv.row + e] = (bf16)dva[dt][i];
+        }
       }
   }
 }
 
+// The segments' sums of the key blocks that have several, added in list order:
+// blockIdx.x = key block, y = key/value head; a thread has eight consecutive
+// elements of one key's dK or dV.  Reads each slot once.
+template <bool CAUSAL, int QS>
+__global__ __launch_bounds__(256) void dkdv_fold_kernel(DkdvSlots slots, HeadView dk, HeadView dv,
+                                                        int64_t S, int64_t Sp, int G) {
+  constexpr int KB = 128 / QS;
+  const int nqt = (int)(Sp / QT), kb = blockIdx.x / (KB / 8);
+  const int kvh = blockIdx.y;
+  const int e8 = ((blockIdx.x % (KB / 8)) * 256 + threadIdx.x) * 8;   // in [2][KB][128]
+  const int64_t base = (int64_t)kvh * slots.per_head;
+  const float* p = slots.at(base + kb, 2 * KB * HEAD_DIM) + e8;
+  f32x4 lo = *reinterpret_cast<const f32x4*>(p), hi = *reinterpret_cast<const f32x4*>(p + 4);
+  int c = seg_blocks<CAUSAL, QS>(1, slots.T, G, nqt);
+  int64_t at = base + c;     // slots of segment 0, then of 1, 2, ...
+  for (int s = 1; kb < c; ++s) {
+    p = slots.at(at + kb, 2 * KB * HEAD_DIM) + e8;
+    lo += *reinterpret_cast<const f32x4*>(p);
+    hi += *reinterpret_cast<const f32x4*>(p + 4);
+    at += c;
+    c = seg_blocks<CAUSAL, QS>(s + 1, slots.T, G, nqt);
+  }
+  const bool is_v = e8 >= KB * HEAD_DIM;
+  const int key = (e8 / HEAD_DIM) % KB + kb * KB, e = e8 % HEAD_DIM;
+  if (key >= S) return;
+  const float f = is_v ? 1.f : -kScale;
+  bf16x8 out;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    out[i] = (bf16)(lo[i] * f);
+    out[4 + i] = (bf16)(hi[i] * f);
+  }
+  const HeadView& d = is_v ? dv : dk;
+  *reinterpret_cast<bf16x8*>(d.p + kvh * d.head + key * d.row + e) = out;
+}
+
 // ---------------------------------------------------------------------- dQ
-// Workgroup = 8 waves x 32 query rows (256 rows, two waves per SIMD).  LDS
-// stage for one tile of DQ_BK keys: K and V rows [DQ_BK][128] (256-B rows).
-// The A operand of dQ^T = K^T . dS^T is read out of the K rows with
-// transposing LDS reads, so no [d][S] copy of K is needed.
-constexpr int DQ_BQ = 256;
-constexpr int DQ_BK = 64;
-constexpr int DQ_T = DQ_BK * HEAD_DIM * 2;
-constexpr int DQ_OFF_K = 0, DQ_OFF_V = DQ_T;
-constexpr int DQ_STAGE = 2 * DQ_T;
-constexpr int DQ_BLK = DQ_T / 1024 / 8;   // 1 KB blocks per wave per tile
+// Workgroup = 8 waves of 32 query rows x a part of every stage's keys: 256 rows
+// x 64-key stages, or, with the keys of 128-key stages split in 2 or 4 parts
+// (attn_bwd_dq_key_parts), 128 or 64 rows, whose sums are added in fp32 through
+// LDS.  LDS stage for one tile of keys: K and V rows (256-B rows).  The A
+// operand of dQ^T = K^T . dS^T is read out of the K rows with transposing LDS
+// reads, so no [d][S] copy of K is needed.
+template <int KS>
+struct DqTile {
+  static constexpr int NQW = 8 / KS;                // waves along the query rows
+  static constexpr int BQ = 32 * NQW;               // query rows per workgroup
+  static constexpr int BK = KS == 1 ? 64 : 128;     // keys per stage
+  static constexpr int NH = BK / 32 / KS;           // 32-key blocks of a stage per wave
+  static constexpr int T = BK * HEAD_DIM * 2;
+  static constexpr int OFF_K = 0, OFF_V = T;
+  static constexpr int STAGE = 2 * T;
+  static constexpr int BLK = T / 1024 / 8;          // 1 KB blocks per wave per tile
+};
 constexpr int DQ_LA = 6;                   // K/V fragment reads kept in flight
 
-// This wave's share of one tile's copies: DQ_BLK blocks of 1 KB each of K
-// rows (transposing-read swizzle) and V rows (4 rows of 256 B per block).
-__device__ __forceinline__ void issue_kstage(buf_rsrc rk, buf_rsrc rv, const uint32_t (&offk)[DQ_BLK],
-                                             const uint32_t (&offv)[DQ_BLK], uint32_t kb, char* buf,
-                                             int w) {
+// This wave's share of one tile's copies: BLK blocks of 1 KB each of K rows
+// (transposing-read swizzle) and V rows (4 rows of 256 B per block), at byte
+// offset `soff` of the head's rows.
+template <int KS>
+__device__ __forceinline__ void issue_kstage(buf_rsrc rk, buf_rsrc rv,
+                                             const uint32_t (&offk)[DqTile<KS>::BLK],
+                                             const uint32_t (&offv)[DqTile<KS>::BLK], uint32_t soff,
+                                             char* buf, int w) {
 #pragma unroll
-  for (int i = 0; i < DQ_BLK; ++i) {
-    const int blk = DQ_BLK * w + i;
-    dma_buf_b128(rk, offk[i], kb * 256u, buf + DQ_OFF_K + blk * 1024);
-    dma_buf_b128(rv, offv[i], kb * 256u, buf + DQ_OFF_V + blk * 1024);
+  for (int i = 0; i < DqTile<KS>::BLK; ++i) {
+    const int blk = DqTile<KS>::BLK * w + i;
+    dma_buf_b128(rk, offk[i], soff, buf + DqTile<KS>::OFF_K + blk * 1024);
+    dma_buf_b128(rv, offv[i], soff, buf + DqTile<KS>::OFF_V + blk * 1024);
   }
 }
 
-template <bool CAUSAL, bool ROPE>
+// dQ may be the rows of Q or dO: a workgroup reads its rows before it writes
+// them, and no other one reads them.
+template <bool CAUSAL, bool ROPE, int KS>
 __global__ __launch_bounds__(512, 1) void attn_bwd_dq_kernel(
-    const bf16* __restrict__ Qc, const bf16* __restrict__ dOc, const float* __restrict__ lse_c,
-    const float* __restrict__ Dc, const bf16* __restrict__ Kp, const bf16* __restrict__ Vp,
-    bf16* __restrict__ dQc, int64_t S, int64_t Sp, int U, int h0,
-    int G, int nqb, RopeArgs rope) {
-  __shared__ __attribute__((aligned(1024))) char smem[2 * DQ_STAGE];
+    HeadView Q, HeadView dO, const float* __restrict__ lse_c, const float* __restrict__ Dc,
+    HeadView K, HeadView V, HeadView dQ, int64_t S, int64_t Sp, int nh, int h0, int G, int nqb,
+    int nhb, RopeArgs rope) {
+  using T = DqTile<KS>;
+  __shared__ __attribute__((aligned(1024))) char smem[2 * T::STAGE];
   const int t = threadIdx.x;
   const int lane = t & 63;
   const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int wq = KS == 1 ? w : w % T::NQW, ks = KS == 1 ? 0 : w / T::NQW;
   const int r32 = lane & 31, g = lane >> 5;
   const int L = blockIdx.x;
-  const int qb = nqb - 1 - L / U;
-  const int u = L % U;
+  const int qb = nqb - 1 - L / nhb;
+  const int row0 = L % nhb;                 // row of lse_c and D: sequence, head
+  const int u = row0 % nh;
+  const int bi = row0 / nh;
   const int kvh = (h0 + u) / G;
-  const uint32_t Spv = (uint32_t)Sp;
-  const uint32_t q0 = (uint32_t)qb * DQ_BQ;
-  const uint32_t qw = q0 + 32 * w;
-  const uint32_t myq = qw + r32;
   const uint32_t Sv = (uint32_t)S;
-  const bool rows_ok = qw < Spv;            // the last block may hold 128 rows only
+  const uint32_t q0 = (uint32_t)qb * T::BQ;
+  const uint32_t qw = q0 + 32 * wq;
+  const uint32_t myq = qw + r32;
+  const bool wave_ok = qw < Sv;
+  const bool row_ok = myq < Sv;
 
-  // One head's K and V rows [Sp][128], 32-bit addressed.
-  const buf_rsrc rk = make_rsrc(Kp + (int64_t)kvh * Sp * HEAD_DIM, Spv * 256u);
-  const buf_rsrc rv = make_rsrc(Vp + (int64_t)kvh * Sp * HEAD_DIM, Spv * 256u);
-  uint32_t offk[DQ_BLK], offv[DQ_BLK];
+  // One head's K and V rows, 32-bit addressed; rows past S read as zero.
+  const uint32_t rowb = (uint32_t)(K.row * 2);
+  const buf_rsrc rk = make_rsrc(K.p + bi * K.batch + kvh * K.head, (Sv - 1) * rowb + 256u);
+  const buf_rsrc rv = make_rsrc(V.p + bi * V.batch + kvh * V.head, (Sv - 1) * rowb + 256u);
+  uint32_t offk[T::BLK], offv[T::BLK];
 #pragma unroll
-  for (int i = 0; i < DQ_BLK; ++i) {
-    const int blk = DQ_BLK * w + i;
+  for (int i = 0; i < T::BLK; ++i) {
+    const int blk = T::BLK * w + i;
     const int r = 4 * blk + (lane >> 4);      // row of the tile, 16 lanes per row
-    offk[i] = r * 256u + (((lane & 15) ^ tsw(r)) << 4);
-    offv[i] = r * 256u + (((lane & 15) ^ (r & 15)) << 4);
+    offk[i] = r * rowb + (((lane & 15) ^ tsw(r)) << 4);
+    offv[i] = r * rowb + (((lane & 15) ^ (r & 15)) << 4);
   }
-  const int nst = CAUSAL ? (int)((min(q0 + DQ_BQ, Spv) + DQ_BK - 1) / DQ_BK) : (int)(Spv / DQ_BK);
-  issue_kstage(rk, rv, offk, offv, 0, smem, w);
+  const int nst = (int)(((CAUSAL ? min(q0 + T::BQ, Sv) : Sv) + T::BK - 1) / T::BK);
+  issue_kstage<KS>(rk, rv, offk, offv, 0, smem, w);
 
+  // Rows past S compute on the last row's values and are not written.
   bf16x8 qf[8], df[8];
-  float nlse = 0.f, Dq = 0.f;
-#pragma unroll
-  for (int s = 0; s < 8; ++s)
-#pragma unroll
-    for (int e = 0; e < 8; ++e) { qf[s][e] = (bf16)0.f; df[s][e] = (bf16)0.f; }
-  if (rows_ok) {
-    const int64_t rowoff = ((int64_t)u * Sp + myq) * HEAD_DIM + 8 * g;
+  float nlse, Dq;   // nlse = -sqrt(d) lse: the score accumulator's seed
+  {
+    const uint32_t row = min(myq, Sv - 1);
+    const bf16* qp = Q.p + bi * Q.batch + u * Q.head + row * Q.row + 8 * g;
+    const bf16* dp = dO.p + bi * dO.batch + u * dO.head + row * dO.row + 8 * g;
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
-      qf[s] = *reinterpret_cast<const bf16x8*>(Qc + rowoff + 16 * s);
-      df[s] = *reinterpret_cast<const bf16x8*>(dOc + rowoff + 16 * s);
+      qf[s] = *reinterpret_cast<const bf16x8*>(qp + 16 * s);
+      df[s] = *reinterpret_cast<const bf16x8*>(dp + 16 * s);
     }
-    nlse = lse_c[(int64_t)u * Sp + myq];   // -sqrt(d) lse: the score accumulator's seed
-    Dq = Dc[(int64_t)u * Sp + myq];
+    nlse = lse_c[row0 * Sp + row];
+    Dq = Dc[row0 * Sp + row];
   }
 
   f32x16 qacc[4];
@@ -486,67 +651,101 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dq_kernel(
 #pragma unroll
     for (int i = 0; i < 16; ++i) qacc[dt][i] = 0.f;
 
+  const int k_part = 32 * T::NH * ks;        // first key of this wave's part of a stage
+  const uint32_t k_lane = T::OFF_K + k_part * 256 + swzt(r32, g);
+  const uint32_t v_lane = T::OFF_V + k_part * 256 + swz256(r32, g);
+  const uint32_t t_lane = T::OFF_K + k_part * 256 + tr_base(lane);
   for (int j = 0; j < nst; ++j) {
-    const uint32_t ks = (uint32_t)j * DQ_BK;
-    char* buf = smem + (j & 1) * DQ_STAGE;
+    const uint32_t boff = (j & 1) * T::STAGE;
     wait_vmem();
     __syncthreads();   // tile j landed for all waves; tile j-1's buffer is free
-    if (j + 1 < nst) issue_kstage(rk, rv, offk, offv, ks + DQ_BK, smem + ((j + 1) & 1) * DQ_STAGE, w);
-    if (!rows_ok) continue;
+    if (j + 1 < nst)
+      issue_kstage<KS>(rk, rv, offk, offv, (uint32_t)(j + 1) * T::BK * rowb,
+                       smem + ((j + 1) & 1) * T::STAGE, w);
+    if (!wave_ok) continue;
+    const uint32_t kb = (uint32_t)j * T::BK + k_part;
+    if (CAUSAL && kb > qw + 31) continue;    // its keys are masked for this wave
+    const bool diag = CAUSAL ? (kb + 32 * T::NH - 1 > qw) : (kb + 32 * T::NH > Sv);
+    // 32 keys at a time: one score and one dP accumulator live at a time,
+    // which leaves registers for DQ_LA fragment reads in flight ahead of the
+    // S / dP MFMAs (with two blocks' accumulators live the compiler kept one,
+    // waiting before every MFMA).  The dQ products add a wave's 16-key steps
+    // in ascending order.  The fragment addresses are exclusive-ors of three
+    // bases: one register for each of them would spill.
+    const uint32_t ka = k_lane + boff, va = v_lane + boff, ta = t_lane + boff;
 #pragma unroll
-    for (int h64 = 0; h64 < DQ_BK / 64; ++h64) {
-      const uint32_t kb = ks + 64 * h64;
-      if (CAUSAL && kb > qw + 31) break;     // rest of the tile masked for this wave
-      const bool diag = CAUSAL ? (kb + 63 > qw) : (kb + 64 > Sv);
-      // The 64 keys in two halves of 32: one score and one dP accumulator
-      // live at a time, which leaves registers for DQ_LA fragment reads in
-      // flight ahead of the S / dP MFMAs (with both halves' accumulators
-      // live the compiler kept one, waiting before every MFMA).  The dQ
-      // products still add the 16-key steps in ascending order.
+    for (int hh = 0; hh < T::NH; ++hh) {
+      f32x16 sacc, pacc;
 #pragma unroll
-      for (int hh = 0; hh < 2; ++hh) {
-        f32x16 sacc, pacc;
+      for (int i = 0; i < 16; ++i) { sacc[i] = nlse; pacc[i] = 0.f; }
 #pragma unroll
-        for (int i = 0; i < 16; ++i) { sacc[i] = nlse; pacc[i] = 0.f; }
-#pragma unroll
-        for (int s = 0; s < 8; ++s) {
-          const int row = 64 * h64 + 32 * hh + r32;
-          sacc = mfma32x32x16(lds_read_b128(buf + DQ_OFF_K, swzt(row, 2 * s + g)), qf[s], sacc);
-          pacc = mfma32x32x16(lds_read_b128(buf + DQ_OFF_V, swz256(row, 2 * s + g)), df[s], pacc);
-        }
-        __builtin_amdgcn_sched_group_barrier(0x100, DQ_LA, 0);
-#pragma unroll
-        for (int i = 0; i < 16 - DQ_LA; ++i) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-        }
-        __builtin_amdgcn_sched_group_barrier(0x008, DQ_LA, 0);
-        bf16x8 sf[2];
-        float p[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) p[i] = fast_exp2(sacc[i] * kSl2);
-        if (diag) {   // wave-uniform
-#pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            const uint32_t key = kb + 32 * hh + 8 * (i >> 2) + 4 * g + (i & 3);
-            const bool vis = CAUSAL ? (key <= myq) : (key < Sv);
-            if (!vis) p[i] = 0.f;
-          }
-        }
-#pragma unroll
-        for (int i = 0; i < 16; ++i) sf[i >> 3][i & 7] = (bf16)(p[i] * (pacc[i] - Dq));
-#pragma unroll
-        for (int c = 0; c < 2; ++c)
-#pragma unroll
-          for (int dt = 0; dt < 4; ++dt)
-            qacc[dt] = mfma32x32x16(
-                tr_operand(buf + DQ_OFF_K, 64 * h64 + 32 * hh + 16 * c, 32 * dt, lane), sf[c],
-                qacc[dt]);
+      for (int s = 0; s < 8; ++s) {
+        sacc = mfma32x32x16(lds_read_b128(smem, (ka ^ (32 * s)) + 8192 * hh), qf[s], sacc);
+        pacc = mfma32x32x16(lds_read_b128(smem, (va ^ (32 * s)) + 8192 * hh), df[s], pacc);
       }
+      __builtin_amdgcn_sched_group_barrier(0x100, DQ_LA, 0);
+#pragma unroll
+      for (int i = 0; i < 16 - DQ_LA; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      }
+      __builtin_amdgcn_sched_group_barrier(0x008, DQ_LA, 0);
+      bf16x8 sf[2];
+      float p[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) p[i] = fast_exp2(sacc[i] * kSl2);
+      if (diag) {   // wave-uniform
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const uint32_t key = kb + 32 * hh + 8 * (i >> 2) + 4 * g + (i & 3);
+          const bool vis = CAUSAL ? (key <= myq) : (key < Sv);
+          if (!vis) p[i] = 0.f;
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < 16; ++i) sf[i >> 3][i & 7] = (bf16)(p[i] * (pacc[i] - Dq));
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt)
+          qacc[dt] =
+              mfma32x32x16(tr_operand_at(smem, ta, 32 * hh + 16 * c, dt), sf[c], qacc[dt]);
     }
   }
 
-  if (!rows_ok) return;
+  if (KS > 1) {
+    // Add the KS parts' sums in ascending key order: parts 1.. pass theirs
+    // through the stage buffers (16 KB per wave).
+    float* fold = reinterpret_cast<float*>(smem);
+    __syncthreads();   // every wave is done reading the last stage
+    if (ks > 0) {
+      float* mine = fold + ((ks - 1) * T::NQW + wq) * 4096 + lane * 4;
+#pragma unroll
+      for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+          f32x4 v;
+#pragma unroll
+          for (int b = 0; b < 4; ++b) v[b] = qacc[dt][4 * a + b];
+          *reinterpret_cast<f32x4*>(mine + (4 * dt + a) * 256) = v;
+        }
+    }
+    __syncthreads();
+    if (ks > 0) return;
+#pragma unroll
+    for (int p = 1; p < KS; ++p) {
+      const float* part = fold + ((p - 1) * T::NQW + wq) * 4096 + lane * 4;
+#pragma unroll
+      for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+          const f32x4 v = *reinterpret_cast<const f32x4*>(part + (4 * dt + a) * 256);
+#pragma unroll
+          for (int b = 0; b < 4; ++b) qacc[dt][4 * a + b] += v[b];
+        }
+    }
+  }
+  if (!row_ok) return;
   if (ROPE) {   // dQ was taken with respect to rotated queries: turn it back
 #pragma unroll
     for (int dt = 0; dt < 2; ++dt)
@@ -558,7 +757,7 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dq_kernel(
         rope_pair(qacc[dt], qacc[dt + 2], i, c, s, true);
       }
   }
-  bf16* op = dQc + ((int64_t)u * Sp + myq) * HEAD_DIM + 4 * g;
+  bf16* op = dQ.p + bi * dQ.batch + u * dQ.head + myq * dQ.row + 4 * g;
 #pragma unroll
   for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
@@ -572,36 +771,160 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dq_kernel(
 
 }  // namespace
 
-hipError_t launch_attn_bwd_dkdv(const bf16* Qc, const bf16* dOc, const float* lse_c, const float* D,
-                                const bf16* Kp, const bf16* Vp, float* dK32, float* dV32, bf16* dk,
-                                bf16* dv, int64_t kv_row, int64_t kv_head, int64_t S, int64_t Sp,
-                                int U, int h0, int G, int causal, hipStream_t st) {
-  const int kv_lo = h0 / G, kv_hi = (h0 + U - 1) / G;
+hipError_t launch_attn_bwd_dkdv(const HeadView& Q, const HeadView& dO, const float* lse_c,
+                                const float* D, const HeadView& K, const HeadView& V, float* dK32,
+                                float* dV32, const HeadView& dk, const HeadView& dv, int64_t S,
+                                int64_t Sp, int nh, int h0, int G, int causal, hipStream_t st) {
+  const int kv_lo = h0 / G, kv_hi = (h0 + nh - 1) / G;
   dim3 grid((unsigned)(Sp / 128), (unsigned)(kv_hi - kv_lo + 1));
-  if (causal)
-    hipLaunchKernelGGL(attn_bwd_dkdv_kernel<true>, grid, dim3(256), 0, st, Qc, dOc, lse_c, D, Kp,
-                       Vp, dK32, dV32, dk, dv, S, Sp, U, h0, G, kv_row, kv_head);
-  else
-    hipLaunchKernelGGL(attn_bwd_dkdv_kernel<false>, grid, dim3(256), 0, st, Qc, dOc, lse_c, D, Kp,
-                       Vp, dK32, dV32, dk, dv, S, Sp, U, h0, G, kv_row, kv_head);
+#define UPIPE_DKDV(C)                                                                          \
+  hipLaunchKernelGGL((attn_bwd_dkdv_kernel<C, 1>), grid, dim3(256), 0, st, Q, dO, lse_c, D, K, \
+                     V, dK32, dV32, dk, dv, DkdvSlots{}, S, Sp, nh, h0, G)
+  if (causal) UPIPE_DKDV(true);
+  else UPIPE_DKDV(false);
+#undef UPIPE_DKDV
   return hipGetLastError();
 }
 
-hipError_t launch_attn_bwd_dq(const bf16* Qc, const bf16* dOc, const float* lse_c, const float* D,
-                              const bf16* Kp, const bf16* Vp, bf16* dQc, int64_t S, int64_t Sp,
-                              int U, int h0, int G, int causal, RopeArgs rope, hipStream_t st) {
-  const int nqb = (int)((Sp + DQ_BQ - 1) / DQ_BQ);
-  dim3 grid((unsigned)(nqb * U));
-#define UPIPE_DQ(C, R)                                                                         \
-  hipLaunchKernelGGL((attn_bwd_dq_kernel<C, R>), grid, dim3(512), 0, st, Qc, dOc, lse_c, D, Kp, \
-                     Vp, dQc, S, Sp, U, h0, G, nqb, rope)
-  if (causal) {
-    if (rope.on) UPIPE_DQ(true, true);
-    else UPIPE_DQ(true, false);
-  } else {
-    if (rope.on) UPIPE_DQ(false, true);
-    else UPIPE_DQ(false, false);
+namespace {
+
+int seg_blocks_of(int causal, int qs, int s, int T, int G, int nqt) {
+  if (causal)
+    return qs == 1 ? seg_blocks<true, 1>(s, T, G, nqt) : seg_blocks<true, 2>(s, T, G, nqt);
+  return qs == 1 ? seg_blocks<false, 1>(s, T, G, nqt) : seg_blocks<false, 2>(s, T, G, nqt);
+}
+
+// Slots of one key/value head with segments of T tiles, and the highest segment.
+int64_t slots_per_head(int causal, int qs, int T, int G, int nqt, int* max_seg) {
+  int64_t n = 0;
+  int s = 1;
+  for (int c; (c = seg_blocks_of(causal, qs, s, T, G, nqt)) > 0; ++s) n += s == 1 ? 2 * c : c;
+  *max_seg = s - 1;
+  return n;
+}
+
+}  // namespace
+
+// Chooses the keys of a workgroup (128 or 64) and the segment length T by the
+// time they are expected to take, in units of one 128 x 128 tile (3.5 us with
+// the chip partly filled, 4.1 us full): whole segments are dispatched first,
+// 256 at a time, then the first segments of the lists, of all lengths up to T,
+// longest first.  A workgroup costs two tiles besides its list, the fold 1.5
+// and 0.016 per slot.  A tile of 64 keys costs 0.86 of one of 128 (causal;
+// 0.72 if every key is visible): it halves the work but not the copies, so it
+// pays only where the workgroups of a launch do not fill the chip twice.
+// Measured, causal (best of 128 / 64 keys; one workgroup per list before):
+//   512 rows, 2 heads 37 -> 24 us; 4096 rows, 8 heads on 2 433 -> 111; 8192 rows, 4
+//   heads 848 -> 207; 16384 rows, 8 heads 3503 -> 1200; 32768 rows, 8 heads 7.8 ->
+//   4.4 ms, where 1028 tiles per CU are 4.2 ms.
+DkdvSplit dkdv_split(int64_t Sp, int Hkv, int G, int causal, size_t bytes0, size_t bytes1) {
+  const int nqt = (int)(Sp / QT);
+  DkdvSplit best;
+  double best_est = 1e300;
+  for (int qs = 1; qs <= 2; ++qs) {
+    const size_t slot = (size_t)2 * (128 / qs) * HEAD_DIM * 4;
+    const int64_t have = (int64_t)(bytes0 / slot + bytes1 / slot);
+    // The longest list in n / 8 parts; equal lists in whole parts only.
+    for (int n = 8; n <= 128; n += causal ? 1 : 8) {
+      DkdvSplit p;
+      p.qs = qs;
+      p.T = causal ? G * ((8 * nqt + n - 1) / n) : (8 * G * nqt + n - 1) / n;
+      p.per_head = (int)slots_per_head(causal, qs, p.T, G, nqt, &p.max_seg);
+      if (Hkv * (int64_t)p.per_head > have) continue;
+      const int c1 = seg_blocks_of(causal, qs, 1, p.T, G, nqt);
+      const double T = p.T * (qs == 1 ? 1.0 : causal ? 0.86 : 0.72) + 2.0;
+      const int64_t blocks = (int64_t)Hkv * nqt * qs;
+      const int64_t rest = causal ? blocks : 0;
+      const int64_t whole = Hkv * (int64_t)(p.per_head - c1) + (causal ? 0 : blocks);
+      if (qs > 1 && whole + rest > 288) continue;
+      const int64_t rounds = whole / 256, extra = whole % 256, room = 256 - extra;
+      double span = rounds * T;
+      if (rest <= room) {
+        if (rest + extra > 0) span += T;
+      } else {
+        // `room` of the others start at once, the rest (up to x long) as
+        // those finish, the shortest first
+        const double x = T * (rest - room) / rest;
+        span += std::max(T, rest <= 2 * room ? 2 * x : (extra + rest * 0.5) * T / 256 + 0.5 * T);
+      }
+      const double est = span + (c1 > 0 ? 1.5 + Hkv * p.per_head * 0.016 / qs : 0);
+      if (est < best_est) {
+        best_est = est;
+        best = p;
+      }
+    }
   }
+  return best;
+}
+
+hipError_t launch_attn_bwd_dkdv_split(const HeadView& Q, const HeadView& dO, const float* lse_c,
+                                      const float* D, const HeadView& K, const HeadView& V,
+                                      const HeadView& dk, const HeadView& dv, int64_t S, int64_t Sp,
+                                      int Hkv, int G, int causal, const DkdvSplit& p, char* region0,
+                                      size_t bytes0, char* region1, hipStream_t st) {
+  const int nqt = (int)(Sp / QT);
+  const size_t slot = (size_t)2 * (128 / p.qs) * HEAD_DIM * 4;
+  DkdvSlots s;
+  s.p0 = (float*)region0;
+  s.p1 = (float*)region1;
+  s.n0 = (int64_t)(bytes0 / slot);
+  s.T = p.T;
+  s.max_seg = p.max_seg;
+  s.kv_heads = Hkv;
+  s.per_head = p.per_head;
+  const int c1 = seg_blocks_of(causal, p.qs, 1, p.T, G, nqt);
+  dim3 grid((unsigned)((nqt * p.qs + p.per_head - c1) * Hkv));
+  dim3 fold((unsigned)(c1 * (128 / p.qs / 8)), (unsigned)Hkv);
+#define UPIPE_DKDV(C, N)                                                                         \
+  hipLaunchKernelGGL((attn_bwd_dkdv_kernel<C, N>), grid, dim3(256), 0, st, Q, dO, lse_c, D,      \
+                     K, V, nullptr, nullptr, dk, dv, s, S, Sp, Hkv * G, 0, G);       \
+  if (c1 > 0)                                                                                    \
+  hipLaunchKernelGGL((dkdv_fold_kernel<C, N>), fold, dim3(256), 0, st, s, dk, dv, S, Sp, G)
+  if (causal) {
+    if (p.qs == 1) { UPIPE_DKDV(true, 1); }
+    else { UPIPE_DKDV(true, 2); }
+  } else {
+    if (p.qs == 1) { UPIPE_DKDV(false, 1); }
+    else { UPIPE_DKDV(false, 2); }
+  }
+#undef UPIPE_DKDV
+  return hipGetLastError();
+}
+
+// As attn_fwd_key_parts, at the same lines: 512 blocks 700 / 756 us (1 / 2 parts,
+// causal, 16384 rows, 8 heads), 256 blocks 511 / 381 (4 heads) and 430 with 4, 128
+// blocks 288 / 221 (2 / 4 parts, 2 heads); every key visible 128 blocks 255 / 189
+// (1 / 2 parts, 8192 rows, 4 heads), 256 blocks 344 / 368 (8 heads), 64 blocks 148 /
+// 112 (2 / 4 parts, 2 heads).
+int attn_bwd_dq_key_parts(int64_t S, int Hq, int causal) {
+  const int64_t blocks = (S + 255) / 256 * Hq;
+  if (blocks > (causal ? 448 : 128)) return 1;
+  return blocks > (causal ? 224 : 64) ? 2 : 4;
+}
+
+hipError_t launch_attn_bwd_dq(const HeadView& Q, const HeadView& dO, const float* lse_c,
+                              const float* D, const HeadView& K, const HeadView& V,
+                              const HeadView& dQ, int64_t S, int64_t Sp, int64_t B, int nh, int h0,
+                              int G, int causal, int parts, RopeArgs rope, hipStream_t st) {
+  const int bq = 256 / parts;
+  const int nqb = (int)((S + bq - 1) / bq);
+  const int nhb = (int)(nh * B);
+  dim3 grid((unsigned)(nqb * nhb));
+#define UPIPE_DQ(C, R, P)                                                                  \
+  hipLaunchKernelGGL((attn_bwd_dq_kernel<C, R, P>), grid, dim3(512), 0, st, Q, dO, lse_c, D, \
+                     K, V, dQ, S, Sp, nh, h0, G, nqb, nhb, rope)
+#define UPIPE_DQ_PARTS(C, R)             \
+  if (parts == 1) UPIPE_DQ(C, R, 1);     \
+  else if (parts == 2) UPIPE_DQ(C, R, 2); \
+  else UPIPE_DQ(C, R, 4)
+  if (causal) {
+    if (rope.on) { UPIPE_DQ_PARTS(true, true); }
+    else { UPIPE_DQ_PARTS(true, false); }
+  } else {
+    if (rope.on) { UPIPE_DQ_PARTS(false, true); }
+    else { UPIPE_DQ_PARTS(false, false); }
+  }
+#undef UPIPE_DQ_PARTS
 #undef UPIPE_DQ
   return hipGetLastError();
 }

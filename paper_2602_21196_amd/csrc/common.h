@@ -114,6 +114,31 @@ __device__ __forceinline__ bf16x8 tr_operand(const char* tile, int k0, int n0, i
   return v;
 }
 
+// The same addresses as one per-lane base and exclusive-ors, for kernels that
+// cannot hold one register per address: with base = swz(r, g), chunk 2s + g of
+// the row (s < 8) lies at base ^ 32 s and rows 32 on at + 8192 (swz256 and
+// swzt alike); a transposing read's columns 32 dt on at tr_base ^ 64 dt, rows
+// 16 on at + 4096, and its upper half (8 rows on) at tr_base ^ 32, + 2048.
+__device__ __forceinline__ uint32_t tr_base(int lane) {
+  const int t = lane & 15, hi = (lane >> 4) & 1, g = lane >> 5;
+  return swzt(4 * g + (t >> 2), 2 * hi + ((t & 3) >> 1)) + ((t & 1) << 3);
+}
+// Columns 32 dt.., rows k0.. (a multiple of 16) of the tile whose tr_base,
+// with the tile's offset added, is `tb`.
+__device__ __forceinline__ bf16x8 tr_operand_at(const char* smem, uint32_t tb, int k0, int dt) {
+  typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
+  const uint32_t lo_at = (tb ^ (64 * dt)) + k0 * 256, up_at = (tb ^ (64 * dt + 32)) + k0 * 256 + 2048;
+  const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(smem + lo_at));
+  const bf16x4 up = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(smem + up_at));
+  bf16x8 v;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    v[e] = lo[e];
+    v[4 + e] = up[e];
+  }
+  return v;
+}
+
 // ---- rotary position embedding (RoFormer), head coordinate pairs (e, e + 64)
 // for e < 64: at sequence position p the pair turns by p * theta_e with
 // theta_e = base^(-e/64); the inverse (transpose) turns by the opposite angle.

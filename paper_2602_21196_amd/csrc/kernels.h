@@ -9,23 +9,6 @@
 
 namespace upipe {
 
-// ---- layout (layout.hip) -------------------------------------------------
-// src [S, H, d] heads h0..h0+n-1  ->  dst [n, Sp, d]; rows >= S are zero.
-hipError_t launch_pack_rows(const bf16* src, int64_t S, int H, int h0, int n,
-                            int64_t Sp, bf16* dst, hipStream_t st);
-// src [n, Sp, d] rows < S  ->  dst [S, H, d] heads h0..h0+n-1.
-hipError_t launch_unpack_rows(const bf16* src, int64_t S, int H, int h0, int n,
-                              int64_t Sp, bf16* dst, hipStream_t st);
-// D[n, Sp] = rowsum(a * b) over the head width and lse_c[n, Sp] = -sqrt(d)
-// times the lse rows h0.. of the caller's [Hq, S] array (zero for rows >= S).  Element
-// (s, hh, e) of a is a[s * a_row + hh * a_head + e], likewise for b.
-hipError_t launch_rowdot_lse(const bf16* a, int64_t a_row, int64_t a_head,
-                             const bf16* b, int64_t b_row, int64_t b_head,
-                             const float* lse, int64_t S, int h0, int n,
-                             int64_t Sp, float* D, float* lse_c,
-                             hipStream_t st);
-
-// ---- attention forward (attn_fwd.hip) ------------------------------------
 // Rows of 128 elements of several heads of a batch of sequences: element
 // (b, s, h, e) is p[b * batch + s * row + h * head + e].  Token-major
 // [B, S, H, d]: row = H d, head = d, batch = S H d; head-major [H, Sp, d]:
@@ -34,14 +17,30 @@ struct HeadView {
   bf16* p;
   int64_t row, head, batch;
 };
-// The kernels address one head's key/value rows with 32-bit byte offsets, up
-// to the end of the last 128-row tile.
-inline bool kv_rows_addressable(int64_t S, int64_t row) {
+
+// ---- layout (layout.hip) -------------------------------------------------
+// src [S, H, d] heads h0..h0+n-1  ->  dst [n, Sp, d]; rows >= S are zero.
+hipError_t launch_pack_rows(const bf16* src, int64_t S, int H, int h0, int n,
+                            int64_t Sp, bf16* dst, hipStream_t st);
+// src [n, Sp, d] rows < S  ->  dst [S, H, d] heads h0..h0+n-1.
+hipError_t launch_unpack_rows(const bf16* src, int64_t S, int H, int h0, int n,
+                              int64_t Sp, bf16* dst, hipStream_t st);
+// D[B, n, Sp] = rowsum(a * b) over the head width and lse_c[B, n, Sp] =
+// -sqrt(d) times the rows of heads h0.. of lse [B, lse_heads, S]; zero for
+// rows >= S.  Head hh of a and b is head h0 + hh.  B <= 65535.
+hipError_t launch_rowdot_lse(const HeadView& a, const HeadView& b, const float* lse, int64_t S,
+                             int64_t B, int lse_heads, int h0, int n, int64_t Sp, float* D,
+                             float* lse_c, hipStream_t st);
+
+// ---- attention forward (attn_fwd.hip) ------------------------------------
+// The kernels address one head's rows with 32-bit byte offsets, up to the
+// end of the last 128-row tile.
+inline bool rows_addressable(int64_t S, int64_t row) {
   return round_up(S, SEQ_PAD) * row * 2 < (int64_t(1) << 32);
 }
 // Heads h0 .. h0 + nh - 1 of B sequences: Q, O (head u of the view is head
 // h0 + u; they may be the same rows), K, V (head g of the view is key/value
-// head g; kv_rows_addressable) and lse [B, lse_heads, Sq].  Query row i sees
+// head g; rows_addressable) and lse [B, lse_heads, Sq].  Query row i sees
 // key j iff j < Skv and (not causal or j <= i + delta); rows that see no key
 // get O = 0, lse = -inf.  Self-attention: Sq = Skv = S, delta = 0.  `parts`
 // as attn_fwd_key_parts says for the whole call's heads.
@@ -59,28 +58,57 @@ hipError_t launch_lse_merge(bf16* o, float* lse, const bf16* o_p,
                             hipStream_t st);
 
 // ---- attention backward (attn_bwd.hip) -----------------------------------
-// lse_c below holds -sqrt(d) lse, the initial value of a row's score
-// accumulator (the kernels evaluate P = exp2(acc log2(e) / sqrt(d))).
-// Key/value gradients of the chunk's heads, accumulated in fp32 on top of
-// dK32/dV32 [Hkv, Sp, d] (read unless the chunk holds a group's first head;
-// dK32 carries the unscaled sum with its sign flipped, -sum dS^T Q), written
-// back there, or -- when the chunk holds the group's last head --
-// scaled and rounded into dk/dv bf16: row s of key/value head g at element
-// s * kv_row + g * kv_head (token-major [S, Hkv, d]: kv_row = Hkv * d,
-// kv_head = d; head-major [Hkv, Sp, d]: kv_row = d, kv_head = Sp * d).
-hipError_t launch_attn_bwd_dkdv(const bf16* Qc, const bf16* dOc,
-                                const float* lse_c, const float* D,
-                                const bf16* Kp, const bf16* Vp, float* dK32,
-                                float* dV32, bf16* dk, bf16* dv, int64_t kv_row,
-                                int64_t kv_head, int64_t S, int64_t Sp, int U,
-                                int h0, int G, int causal, hipStream_t st);
-// dQc [U, Sp, d] of the chunk's heads.  With rope.on, Q and K are the rotated
-// ones and dQ is turned back by the inverse rotation of its row before it is
-// rounded.
-hipError_t launch_attn_bwd_dq(const bf16* Qc, const bf16* dOc,
-                              const float* lse_c, const float* D,
-                              const bf16* Kp, const bf16* Vp, bf16* dQc, int64_t S, int64_t Sp, int U, int h0,
-                              int G, int causal, RopeArgs rope, hipStream_t st);
+// Rows u of lse_c and D [.][Sp] below belong to head h0 + u; lse_c holds
+// -sqrt(d) lse, the initial value of a row's score accumulator (the kernels
+// evaluate P = exp2(acc log2(e) / sqrt(d))).  Head u of Q, dO and dQ is head
+// h0 + u, head g of K, V, dk, dv is key/value head g.
+// Of one sequence: key/value gradients of the heads h0 .. h0 + nh - 1, accumulated in fp32 on top
+// of dK32/dV32 [Hkv, Sp, d] (read unless the launch holds a group's first
+// head; dK32 carries the unscaled sum with its sign flipped, -sum dS^T Q),
+// written back there, or -- when the launch holds the group's last head --
+// scaled and rounded into dk/dv.  The rows of Q and dO are rows_addressable.
+hipError_t launch_attn_bwd_dkdv(const HeadView& Q, const HeadView& dO, const float* lse_c,
+                                const float* D, const HeadView& K, const HeadView& V, float* dK32,
+                                float* dV32, const HeadView& dk, const HeadView& dv, int64_t S,
+                                int64_t Sp, int nh, int h0, int G, int causal, hipStream_t st);
+// The same over every head of one sequence, with each key block's list of
+// (head, query tile) cut into segments of T tiles that run side by side: their
+// fp32 sums meet in slots of region0 (bytes0) and region1, both free until
+// the call's last kernel is done.
+struct DkdvSplit {
+  int qs = 1;          // 128 / qs keys per workgroup
+  int T = 0;           // tiles of a segment
+  int max_seg = 0;     // segments of the longest list, less one
+  int per_head = 0;    // slots of a key/value head
+};
+struct DkdvSlots {
+  float* p0 = nullptr;     // slots 0 .. n0 - 1
+  float* p1 = nullptr;     // slots n0 ..
+  int64_t n0 = 0;
+  int T = 0, max_seg = 0, per_head = 0, kv_heads = 1;
+  __device__ float* at(int64_t i, int64_t floats) const {
+    return i < n0 ? p0 + i * floats : p1 + (i - n0) * floats;
+  }
+};
+// Segments for sequences of Sp padded rows, given what the regions hold.
+DkdvSplit dkdv_split(int64_t Sp, int Hkv, int G, int causal, size_t bytes0, size_t bytes1);
+hipError_t launch_attn_bwd_dkdv_split(const HeadView& Q, const HeadView& dO, const float* lse_c,
+                                      const float* D, const HeadView& K, const HeadView& V,
+                                      const HeadView& dk, const HeadView& dv, int64_t S, int64_t Sp,
+                                      int Hkv, int G, int causal, const DkdvSplit& p, char* region0,
+                                      size_t bytes0, char* region1, hipStream_t st);
+// dQ of these heads of B sequences (rows b nh + u of lse_c and D); it may be
+// the rows of Q or dO.  With rope.on, Q and K
+// are the rotated ones and dQ is turned back by the inverse rotation of its
+// row before it is rounded.  `parts` as attn_bwd_dq_key_parts says for the
+// whole call's heads.  The rows of K and V are rows_addressable.
+hipError_t launch_attn_bwd_dq(const HeadView& Q, const HeadView& dO, const float* lse_c,
+                              const float* D, const HeadView& K, const HeadView& V,
+                              const HeadView& dQ, int64_t S, int64_t Sp, int64_t B, int nh, int h0,
+                              int G, int causal, int parts, RopeArgs rope, hipStream_t st);
+// Parts (1, 2 or 4) into which the waves of a dQ workgroup split the keys of
+// every stage, for a call over Hq heads.
+int attn_bwd_dq_key_parts(int64_t S, int Hq, int causal);
 // In place: rotate every head h < H of row s < S, the 128 values at element
 // s * row + h * head of x, at position pos0 + s (inverse: by the opposite
 // angle).  Token-major [S, H, d]: row = H * d, head = d.

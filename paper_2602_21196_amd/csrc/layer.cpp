@@ -185,11 +185,9 @@ int run_layer_fwd_seq(const bf16* x, const bf16* wqkv, const bf16* wo, bf16* y, 
                  gemm1(X, true, operand(wqkv + (int64_t)h0 * HEAD_DIM, ldw, U * HEAD_DIM, dm),
                        false, heads_epi(Qc, nullptr, U, Sp, rope), GEMM_EPI_HEADS, Sp,
                        U * HEAD_DIM, dm, st));
-    HeadView O = token_major(o_saved, S, Hq);
-    O.p += h0 * O.head;
     UPIPE_LAUNCH(kAttnFwd, st,
-                 launch_attn_fwd(head_major(Qc, Sp), head_major(Kp, Sp), head_major(Vp, Sp), O, lse,
-                                 S, S, 0, 1, Hq, U, h0, G, 1, parts, st));
+                 launch_attn_fwd(head_major(Qc, Sp), head_major(Kp, Sp), head_major(Vp, Sp),
+                                 sub(token_major(o_saved, S, Hq), 0, h0), lse, S, S, 0, 1, Hq, U, h0, G, 1, parts, st));
   }
   // y = final_out Wo.
   UPIPE_LAUNCH(kGemm, st,
@@ -280,21 +278,24 @@ int run_layer_bwd_seq(const bf16* x, const bf16* wqkv, const bf16* wo, const bf1
                                    head_major(Oc, Sp), lse_r, S, S, 0, 1, Hq, U, h0, G, 1,
                                    attn_fwd_key_parts(S, S, 0, Hq, 1), st));
       UPIPE_LAUNCH(kRowdotLse, st,
-                   launch_rowdot_lse(dOc, HEAD_DIM, head, Oc, HEAD_DIM, head, lse_r, S, h0, U,
-                                     Sp, D, lse_c, st));
+                   launch_rowdot_lse(head_major(dOc, Sp), head_major(Oc, Sp), lse_r, S, 1, Hq, h0,
+                                     U, Sp, D, lse_c, st));
       rc = wgrad(operand(Oc, HEAD_DIM, w, S, HEAD_DIM, head), dYn, w, dm,
                  dwo + (int64_t)h0 * HEAD_DIM * dm, dm, dWo32 + (int64_t)h0 * HEAD_DIM * dm);
       if (rc != UPIPE_OK) return rc;
     } else {
       UPIPE_LAUNCH(kRowdotLse, st,
-                   launch_rowdot_lse(dOc, HEAD_DIM, head, o_saved + (int64_t)h0 * HEAD_DIM, qw,
-                                     HEAD_DIM, lse, S, h0, U, Sp, D, lse_c, st));
+                   launch_rowdot_lse(head_major(dOc, Sp), sub(token_major(o_saved, S, Hq), 0, h0),
+                                     lse, S, 1, Hq, h0, U, Sp, D, lse_c, st));
     }
-    rc = run_dkdv_chunk(Qc, dOc, lse_c, D, Kp, Vp, dK32, dV32, dKh, dVh, HEAD_DIM, head, S, Sp,
-                        U, h0, G, 1, st);
+    const HeadView Qh = head_major(Qc, Sp), dOh = head_major(dOc, Sp);
+    const HeadView Kh = head_major(Kp, Sp), Vh = head_major(Vp, Sp);
+    rc = run_dkdv(Qh, dOh, lse_c, D, Kh, Vh, dK32, dV32, head_major(dKh, Sp),
+                  head_major(dVh, Sp), S, Sp, U, h0, G, 1, st);
     if (rc != UPIPE_OK) return rc;
     UPIPE_LAUNCH(kAttnBwdDq, st,
-                 launch_attn_bwd_dq(Qc, dOc, lse_c, D, Kp, Vp, dQc, S, Sp, U, h0, G, 1, rope, st));
+                 launch_attn_bwd_dq(Qh, dOh, lse_c, D, Kh, Vh, head_major(dQc, Sp), S, Sp, 1, U, h0, G, 1,
+                                    attn_bwd_dq_key_parts(S, Hq, 1), rope, st));
   }
   // dK is the gradient with respect to the rotated keys: turn it back, in
   // place (one bf16 pass over [Hkv, S, d]; kept out of the dK/dV kernel,

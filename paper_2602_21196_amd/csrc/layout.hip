@@ -50,35 +50,36 @@ __global__ __launch_bounds__(256) void unpack_rows_kernel(
   }
 }
 
-// D[hh][s] = sum_e dO(s, hh, e) * O(s, hh, e) in fp32 (the backward's row
-// term) and the chunk's log-sum-exp rows times -sqrt(d) (the initial value
-// of the backward kernels' score accumulators: they end at
-// q.k - sqrt(d) lse, so P = exp2(acc log2(e) / sqrt(d))), copied to a padded
-// buffer.  Element
-// (s, hh, e) of an operand X lives at X + s * x_row + hh * x_head + e.  One
-// wave per (row, head); lanes hold two elements each and reduce by shuffles.
+// The backward's row terms, for the heads h0 .. h0 + n - 1 of B sequences:
+// D[b][hh][s] = sum_e dO(b, s, hh, e) * O(b, s, hh, e) in fp32, and the
+// log-sum-exp rows times -sqrt(d) (the initial value of the backward kernels'
+// score accumulators: they end at q.k - sqrt(d) lse, so
+// P = exp2(acc log2(e) / sqrt(d))), both padded to Sp rows with zeros.
+// HBM-bound: sixteen lanes read a row as 16 bytes each and add their sums by
+// shuffles (a wave per row with 4 bytes a lane: 28.8 us per head of 131072
+// rows).
 __global__ __launch_bounds__(256) void rowdot_lse_kernel(
-    const bf16* __restrict__ a, int64_t a_row, int64_t a_head,
-    const bf16* __restrict__ b, int64_t b_row, int64_t b_head,
-    const float* __restrict__ lse, int64_t S, int h0, int n, int64_t Sp,
-    float* __restrict__ D, float* __restrict__ lse_c) {
-  const int lane = threadIdx.x & 63;
-  const int64_t task = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (task >= (int64_t)n * Sp) return;
-  const int hh = task / Sp;
-  const int64_t s = task % Sp;
-  float acc = 0.f, l = 0.f;
+    HeadView a, HeadView b, const float* __restrict__ lse, int64_t S, int lse_heads, int h0,
+    int64_t Sp, float* __restrict__ D, float* __restrict__ lse_c) {
+  const int c = threadIdx.x & 15;
+  const int64_t s = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
+  const int64_t hh = blockIdx.y, bi = blockIdx.z;
+  float acc = 0.f;
   if (s < S) {
-    const bf16* pa = a + s * a_row + hh * a_head + 2 * lane;
-    const bf16* pb = b + s * b_row + hh * b_head + 2 * lane;
-    acc = (float)pa[0] * (float)pb[0] + (float)pa[1] * (float)pb[1];
-    l = lse[(int64_t)(h0 + hh) * S + s] * -11.313708498984761f;   // -sqrt(128) lse
+    const bf16x8 x = *reinterpret_cast<const bf16x8*>(a.p + bi * a.batch + hh * a.head +
+                                                       s * a.row + 8 * c);
+    const bf16x8 y = *reinterpret_cast<const bf16x8*>(b.p + bi * b.batch + hh * b.head +
+                                                       s * b.row + 8 * c);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc = fmaf((float)x[e], (float)y[e], acc);
   }
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off);
-  if (lane == 0) {
-    D[(int64_t)hh * Sp + s] = acc;
-    lse_c[(int64_t)hh * Sp + s] = l;
+  for (int off = 8; off >= 1; off >>= 1) acc += __shfl_xor(acc, off);
+  if (c == 0) {
+    const int64_t r = (bi * gridDim.y + hh) * Sp + s;
+    D[r] = acc;
+    // -sqrt(128) lse
+    lse_c[r] = s < S ? lse[(bi * lse_heads + h0 + hh) * S + s] * -11.313708498984761f : 0.f;
   }
 }
 
@@ -190,15 +191,11 @@ hipError_t launch_unpack_rows(const bf16* src, int64_t S, int H, int h0, int n,
   return hipGetLastError();
 }
 
-hipError_t launch_rowdot_lse(const bf16* a, int64_t a_row, int64_t a_head,
-                             const bf16* b, int64_t b_row, int64_t b_head,
-                             const float* lse, int64_t S, int h0, int n,
-                             int64_t Sp, float* D, float* lse_c,
-                             hipStream_t st) {
-  const int64_t tasks = (int64_t)n * Sp;
-  hipLaunchKernelGGL(rowdot_lse_kernel, dim3((unsigned)((tasks + 3) / 4)),
-                     dim3(256), 0, st, a, a_row, a_head, b, b_row, b_head, lse,
-                     S, h0, n, Sp, D, lse_c);
+hipError_t launch_rowdot_lse(const HeadView& a, const HeadView& b, const float* lse, int64_t S,
+                             int64_t B, int lse_heads, int h0, int n, int64_t Sp, float* D,
+                             float* lse_c, hipStream_t st) {
+  hipLaunchKernelGGL(rowdot_lse_kernel, dim3((unsigned)(Sp / 16), (unsigned)n, (unsigned)B),
+                     dim3(256), 0, st, a, b, lse, S, lse_heads, h0, Sp, D, lse_c);
   return hipGetLastError();
 }
 

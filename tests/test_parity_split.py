@@ -1,13 +1,20 @@
-"""GPU parity where the launch rule changes: the attention forward splits the
-keys of a stage into 1, 2 or 4 parts by the number of 256-row query blocks
-times heads, and packs keys and values only when one head's token-major rows
-span 2^32 bytes.  Query counts end one row into a block, on it and before it;
-the key ranges are short, so the oracle stays cheap."""
+"""GPU parity where a launch rule changes.
+
+Forward: a stage's keys are split into 1, 2 or 4 parts by the number of 256-row
+query blocks times heads, and keys and values are packed only when one head's
+token-major rows span 2^32 bytes.  Query counts end one row into a block, on it
+and before it; the key ranges are short, so the oracle stays cheap.
+
+Backward: dK/dV cuts the walk over a key block's query tiles into segments,
+with 128 or 64 keys a workgroup, and dQ splits keys like the forward; tensors
+that overlap an output take the path that packs them."""
 
 import numpy as np
 import pytest
 import torch
 
+import workloads as W
+from oracle import attention as A
 from oracle import ring as R
 from tol import as64, assert_close
 
@@ -79,3 +86,67 @@ def test_forward_packs_keys_beyond_32_bit_offsets():
         torch.cuda.synchronize()
         assert torch.equal(_bits(o[:, h]), _bits(o1[:, 0])), h
         assert torch.equal(_bits(lse[h]), _bits(l1[0])), h
+
+
+# One to 16 query tiles, one group and several, odd groups, remainders of
+# segments and tiles; the workspace bounds the segments, and it is smallest at
+# different chunk sizes (with and without carries).
+BACKWARD = [(129, 3, 1, True), (385, 3, 3, True), (640, 5, 1, True), (897, 16, 4, True),
+            (1409, 6, 1, True), (2049, 1, 1, True), (2047, 12, 2, True), (1281, 7, 1, False),
+            (1152, 4, 4, False), (1920, 16, 2, False)]
+
+
+@pytest.mark.parametrize("S,Hq,Hkv,causal", BACKWARD)
+def test_backward_segments(S, Hq, Hkv, causal):
+    """Against the oracle (tol.py's bars) and bitwise equal for every U."""
+    up = _upipe()
+    cpu = W.attention_inputs(S, Hq, Hkv, 128, 40 + S)
+    ref = A.attn_bwd(*(as64(t) for t in cpu), causal)
+    q, k, v, do = (t.to(DEV) for t in cpu)
+    first = None
+    for U in [u for u in range(1, Hq + 1) if Hq % u == 0]:
+        print(f"segments S={S} Hq={Hq} Hkv={Hkv} causal={causal} U={U}", flush=True)
+        o, lse = up.attn_fwd(q, k, v, causal=causal, U=U)
+        got = up.attn_bwd(q, k, v, o, lse, do, causal=causal, U=U)
+        torch.cuda.synchronize()
+        if first is None:
+            first = got
+            for name, a, r in zip(("dq", "dk", "dv"), got, ref):
+                assert_close(name, a.cpu(), r)
+        for a, b in zip(first, got):
+            assert torch.equal(_bits(a), _bits(b)), U
+
+
+def test_backward_of_a_long_batch_equals_single_sequences():
+    """More sequences than rows are kept for at a time."""
+    up = _upipe()
+    q, k, v, do = (t.to(DEV) for t in W.batch_attention_inputs(600, 4, 2, 128, 77, 6))
+    o, lse = up.attn_fwd(q, k, v, U=2)
+    got = up.attn_bwd(q, k, v, o, lse, do, U=2)
+    for b in range(6):
+        one = up.attn_bwd(q[b], k[b], v[b], o[b], lse[b], do[b], U=2)
+        torch.cuda.synchronize()
+        for x, y in zip(got, one):
+            assert torch.equal(_bits(x[b]), _bits(y)), b
+
+
+@pytest.mark.parametrize("over", ["dout", "q"])
+def test_backward_gradient_over_an_input(over):
+    """dq in the place of dout or q: those are read before they are written."""
+    up = _upipe()
+    S, Hq, Hkv = 700, 4, 1
+    cpu = W.attention_inputs(S, Hq, Hkv, 128, 9)
+    ref = A.attn_bwd(*(as64(t) for t in cpu), True)
+    q, k, v, do = (t.to(DEV) for t in cpu)
+    o, lse = up.attn_fwd(q, k, v, U=1)
+    dk, dv = torch.empty_like(k), torch.empty_like(v)
+    dq = do if over == "dout" else q
+    ws = up.workspace(up.upipe_attn_bwd_workspace_size(S, Hq, Hkv, 128, 1), DEV)
+    st = up.upipe_attn_bwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(),
+                           do.data_ptr(), dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), S, Hq, Hkv,
+                           128, 1, 1, ws.data_ptr(), ws.numel(),
+                           torch.cuda.current_stream().cuda_stream)
+    assert st == 0
+    torch.cuda.synchronize()
+    for name, a, r in zip(("dq", "dk", "dv"), (dq, dk, dv), ref):
+        assert_close(name, a.cpu(), r)

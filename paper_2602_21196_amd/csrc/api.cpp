@@ -273,16 +273,27 @@ int run_attn_bwd(const bf16* q, const bf16* k, const bf16* v, const bf16* o,
   if (S < kPerHeadRows && rows_addressable(S, std::max(Q.row, K.row)) && apart) {
     // Every tensor in place.  dK/dV of all heads of a sequence in one launch,
     // cut into segments that run side by side: their slots lie behind the
-    // rows of up to kBatchRows sequences and in dq, which is written last.  Cut
-    // for the smallest workspace that a chunk size of this call could bring,
-    // so that no sum depends on U (nor on the batch).
-    constexpr int64_t kBatchRows = 4;
+    // rows and in dq, which is written last.  Cut for the smallest workspace
+    // that a chunk size of this call could bring, so that no sum depends on U
+    // (nor on the batch).
     size_t least = p.total;
     for (int u = 1; u <= Hq; ++u)
       if (Hq % u == 0) least = std::min(least, plan_attn_bwd(S, Hq, Hkv, u).total);
-    const int64_t nb = std::max<int64_t>(1, std::min<int64_t>(kBatchRows, least / 4 / row_bytes));
+    auto cut_beside = [&](int64_t seqs) {
+      return dkdv_split(p.Sp, Hkv, G, causal, least - seqs * row_bytes, (size_t)Q.batch * 2);
+    };
+    // The rows of four sequences, whose dQ then runs in one launch, unless
+    // their room is worth more to the segments.
+    int64_t nb = 1;
+    DkdvSplit cut = cut_beside(1);
+    if (4 * row_bytes <= least) {
+      const DkdvSplit four = cut_beside(4);
+      if (four.est <= 1.03 * cut.est) {
+        nb = 4;
+        cut = four;
+      }
+    }
     const size_t taken = nb * row_bytes;
-    const DkdvSplit cut = dkdv_split(p.Sp, Hkv, G, causal, least - taken, (size_t)Q.batch * 2);
     for (int64_t b0 = 0; b0 < B; b0 += nb) {
       const int64_t n = std::min(nb, B - b0);
       float* D = (float*)ws;

@@ -266,8 +266,13 @@ __device__ __forceinline__ void pair_step(const char* buf, int base, uint32_t qb
   }
 }
 
-// Key blocks (of 128 / QS keys) whose list of query tiles has more than s
-// segments: the first ones, since the lists get no longer.
+// Segments.  The lists of all key blocks are prefixes of one list, the query
+// tiles from the last one down and within a tile the group's heads (beginning
+// at the key block's own); it is cut at every T-th entry, so that the
+// workgroups of one segment walk the same tiles side by side.  A key block (of 128 / QS keys) has whole segments and a
+// last one of any length up to T.
+
+// Key blocks whose list is longer than s segments: the first ones.
 template <bool CAUSAL, int QS>
 __host__ __device__ inline int seg_blocks(int s, int T, int G, int nqt) {
   if (!CAUSAL) return G * nqt > s * T ? QS * nqt : 0;
@@ -275,11 +280,11 @@ __host__ __device__ inline int seg_blocks(int s, int T, int G, int nqt) {
   return tiles > 0 ? QS * tiles : 0;
 }
 
-// The x-th key block by the length of its list's first segment, longest first.
-// Tile j from the end has a list of G (j + 1) tiles, the first segment of
-// which is G (j % m + 1) long, m = T / G.
+// The x-th key block by the length of its last segment, longest first.  Tile j
+// from the end has a list of G (j + 1) entries, the last segment of which is
+// G (j % m + 1) long, m = T / G.
 template <bool CAUSAL, int QS>
-__device__ inline int by_remainder(int x, int T, int G, int nqt) {
+__device__ inline int by_last_segment(int x, int T, int G, int nqt) {
   if (!CAUSAL) return x;
   const int m = T / G, nt = nqt / m, rem = nqt % m, jx = x / QS;
   const int a = (m - rem) * nt;     // the lengths that only whole runs of m have
@@ -292,11 +297,11 @@ __device__ inline int by_remainder(int x, int T, int G, int nqt) {
 // QS = 1: a workgroup owns 128 keys, every wave takes all rows of a tile.
 // QS = 2: 64 keys, two waves per 32 of them, one for each 64-row half of a tile;
 // their sums are added through LDS.
-// T = 0: one workgroup walks the whole list of (head, query tile) of its
-// key block, on top of the carries.  T > 0: the list is cut into segments of T
-// (the first takes the remainder), each with a workgroup of its own; where
-// there are several, each leaves its fp32 sums in a slot and
-// dkdv_fold_kernel adds them in list order.
+// T = 0: one workgroup walks the whole list of its key block, head by head, on
+// top of the carries.  T > 0: a workgroup per segment; where a key block has
+// several, each leaves its fp32 sums in a slot and dkdv_fold_kernel adds them
+// in list order.  Whole segments are dispatched first, then the last ones by
+// length.
 template <bool CAUSAL, int QS>
 __global__ __launch_bounds__(256, 1) void attn_bwd_dkdv_kernel(
     HeadView Q, HeadView dO, const float* __restrict__ lse_c, const float* __restrict__ Dc,
@@ -310,24 +315,30 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkdv_kernel(
   const int wk = QS == 1 ? w : w & 1, qs = QS == 1 ? 0 : w >> 1;
   const int r32 = lane & 31, g = lane >> 5;
   const int T = slots.T;
-  const int kv = T > 0 ? blockIdx.x % slots.kv_heads : blockIdx.y;
-  const int kvh = h0 / G + kv;
   const uint32_t Spv = (uint32_t)Sp;
   const int nqt = (int)(Spv / QT);
-  const int hlo = max(h0, kvh * G), hhi = min(h0 + U, (kvh + 1) * G);
-  // Key block, and this workgroup's part [first_it, first_it + total) of its list.
-  int kb = T > 0 ? blockIdx.x / slots.kv_heads : blockIdx.x, seg = 0, slot = -1;
-  if (T > 0) {   // whole segments first, then the others by their length
-    int acc = 0;
-    for (seg = slots.max_seg; seg > 0; --seg) {
-      const int c = seg_blocks<CAUSAL, QS>(seg, T, G, nqt);
-      acc += c;
-      if (kb < c) break;
-      kb -= c;
+  // Key/value head, key block and, with segments, segment and slot.
+  int kv = blockIdx.y, kb = blockIdx.x, seg = 0, slot = 0;
+  if (T > 0) {
+    const int d = blockIdx.x, nw = slots.kv_heads * slots.whole;
+    if (d < nw) {
+      int i = d, base = 0, c;
+      for (; i >= (c = seg_blocks<CAUSAL, QS>(seg + 1, T, G, nqt)) * slots.kv_heads; ++seg) {
+        i -= c * slots.kv_heads;
+        base += c;
+      }
+      kv = i / c;
+      kb = i % c;
+      slot = base + kb;
+    } else {
+      kv = (d - nw) % slots.kv_heads;
+      kb = by_last_segment<CAUSAL, QS>((d - nw) / slots.kv_heads, T, G, nqt);
+      seg = -1;
+      slot = slots.whole + kb;
     }
-    if (seg == 0) kb = by_remainder<CAUSAL, QS>(kb, T, G, nqt);
-    slot = seg > 0 ? slots.per_head - acc + kb : kb;
   }
+  const int kvh = h0 / G + kv;
+  const int hlo = max(h0, kvh * G), hhi = min(h0 + U, (kvh + 1) * G);
   const uint32_t kb0 = kb * (uint32_t)KB;
   const uint32_t kw = kb0 + 32 * wk;     // first key of this wave
   const uint32_t mykey = kw + r32;       // key column owned by this lane
@@ -335,13 +346,22 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkdv_kernel(
   const bool last = (kvh + 1) * G <= h0 + U;  // no later chunk will
   const int qt_lo = CAUSAL ? (int)(kb0 / QT) : 0;   // lowest query tile needed
   const int per_head = nqt - qt_lo;
-  int total = per_head * (hhi - hlo), first_it = 0;
-  bool whole = true;
+  int total = per_head * (hhi - hlo);
+  int hh = hlo, qt = nqt - 1;     // head and query tile of the current iteration
+  int left = 0;                   // heads of that tile yet to come (segments)
+  bool whole = true;              // one workgroup has the whole list
   if (T > 0) {
-    const int n = (total + T - 1) / T, r = total - (n - 1) * T;
+    const int n = (total + T - 1) / T;
     whole = n == 1;
-    first_it = seg == 0 ? 0 : r + (seg - 1) * T;
-    total = seg == 0 ? r : T;
+    if (seg < 0) {
+      seg = n - 1;
+      total -= seg * T;
+    } else {
+      total = T;
+    }
+    left = G - 1 - seg * T % G;
+    hh += (seg * T + kb) % G;   // the heads share out the L2 channels of token-major rows
+    qt -= seg * T / G;
   }
 
   auto srcs = [&](int hh) {
@@ -356,8 +376,6 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkdv_kernel(
     return r;
   };
 
-  int hh = hlo + first_it / per_head;
-  int qt = nqt - 1 - first_it % per_head;    // query tile of the current iteration
   QStageSrc cur = srcs(hh);
   issue_qstage(cur, qt * QT, smem, w, lane);
 
@@ -411,10 +429,14 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkdv_kernel(
   for (int it = 0; it < total; ++it) {
     char* buf = smem + (it & 1) * KV_STAGE;
     const uint32_t qb = qt * QT;
-    // next tile (descending query tiles, then the next head)
-    int nq = qt - 1;
-    int nh = hh;
-    if (qt == qt_lo) {
+    // next tile: descending query tiles, then the next head; with segments
+    // the next head round, then descending
+    int nq = qt - 1, nh = hh;
+    if (T > 0) {
+      nh = hh + 1 < hhi ? hh + 1 : hlo;
+      if (left-- > 0) nq = qt;
+      else left = G - 1;
+    } else if (qt == qt_lo) {
       nq = nqt - 1;
       nh = hh + 1;
     }
@@ -525,18 +547,20 @@ __global__ __launch_bounds__(256) void dkdv_fold_kernel(DkdvSlots slots, HeadVie
   const int nqt = (int)(Sp / QT), kb = blockIdx.x / (KB / 8);
   const int kvh = blockIdx.y;
   const int e8 = ((blockIdx.x % (KB / 8)) * 256 + threadIdx.x) * 8;   // in [2][KB][128]
-  const int64_t base = (int64_t)kvh * slots.per_head;
-  const float* p = slots.at(base + kb, 2 * KB * HEAD_DIM) + e8;
-  f32x4 lo = *reinterpret_cast<const f32x4*>(p), hi = *reinterpret_cast<const f32x4*>(p + 4);
-  int c = seg_blocks<CAUSAL, QS>(1, slots.T, G, nqt);
-  int64_t at = base + c;     // slots of segment 0, then of 1, 2, ...
-  for (int s = 1; kb < c; ++s) {
-    p = slots.at(at + kb, 2 * KB * HEAD_DIM) + e8;
+  const int64_t base = (int64_t)kvh * slots.per_head + kb;
+  f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;
+  auto add = [&](int64_t i) {
+    const float* p = slots.at(base + i, 2 * KB * HEAD_DIM) + e8;
     lo += *reinterpret_cast<const f32x4*>(p);
     hi += *reinterpret_cast<const f32x4*>(p + 4);
+  };
+  int64_t at = 0;
+  int c;
+  for (int s = 1; kb < (c = seg_blocks<CAUSAL, QS>(s, slots.T, G, nqt)); ++s) {
+    add(at);
     at += c;
-    c = seg_blocks<CAUSAL, QS>(s + 1, slots.T, G, nqt);
   }
+  add(slots.whole);
   const bool is_v = e8 >= KB * HEAD_DIM;
   const int key = (e8 / HEAD_DIM) % KB + kb * KB, e = e8 % HEAD_DIM;
   if (key >= S) return;
@@ -794,33 +818,36 @@ int seg_blocks_of(int causal, int qs, int s, int T, int G, int nqt) {
   return qs == 1 ? seg_blocks<false, 1>(s, T, G, nqt) : seg_blocks<false, 2>(s, T, G, nqt);
 }
 
-// Slots of one key/value head with segments of T tiles, and the highest segment.
-int64_t slots_per_head(int causal, int qs, int T, int G, int nqt, int* max_seg) {
+// Whole segments of one key/value head's lists that are not their last.
+int64_t whole_segments(int causal, int qs, int T, int G, int nqt) {
   int64_t n = 0;
-  int s = 1;
-  for (int c; (c = seg_blocks_of(causal, qs, s, T, G, nqt)) > 0; ++s) n += s == 1 ? 2 * c : c;
-  *max_seg = s - 1;
+  for (int s = 1, c; (c = seg_blocks_of(causal, qs, s, T, G, nqt)) > 0; ++s) n += c;
   return n;
 }
 
 }  // namespace
 
 // Chooses the keys of a workgroup (128 or 64) and the segment length T by the
-// time they are expected to take, in units of one 128 x 128 tile (3.5 us with
-// the chip partly filled, 4.1 us full): whole segments are dispatched first,
-// 256 at a time, then the first segments of the lists, of all lengths up to T,
-// longest first.  A workgroup costs two tiles besides its list, the fold 1.5
-// and 0.016 per slot.  A tile of 64 keys costs 0.86 of one of 128 (causal;
-// 0.72 if every key is visible): it halves the work but not the copies, so it
-// pays only where the workgroups of a launch do not fill the chip twice.
-// Measured, causal (best of 128 / 64 keys; one workgroup per list before):
-//   512 rows, 2 heads 37 -> 24 us; 4096 rows, 8 heads on 2 433 -> 111; 8192 rows, 4
-//   heads 848 -> 207; 16384 rows, 8 heads 3503 -> 1200; 32768 rows, 8 heads 7.8 ->
-//   4.4 ms, where 1028 tiles per CU are 4.2 ms.
+// time they are expected to take, in units of one 128 x 128 tile on a full chip
+// (4.1 us).  Measured, causal, d_model 4096 block (T: workgroups, us):
+//   8192 rows, 4 heads    T 20: 442, 207   32: 288, 214   40: 238, 182   64: 160, 258
+//                         128: 96, 463     256: 64, 885 (no segments)
+//   16384 rows, 4 heads   T 80: 476, 684   96: 408, 784   128: 320, 680  192: 240, 772
+// A tile takes 3.25 us with few workgroups running, 4.1 with 256 (one per CU);
+// with 64 keys 2.6 (causal; 0.72 of 128 keys' if every key is visible), for half
+// the work but all of the copies, so 64 keys pay only where the slots that
+// the workspace holds bound T and the launch is one round.  Whole segments run
+// 256 at a time, then the last segments of the lists, of all lengths up to T,
+// longest first: the shorter ones wait for a CU, and the next in order for
+// that one's shader engine, so a second wave costs 0.3 T more than
+// its longest.  A workgroup costs two tiles besides its list, the fold 1.5 and
+// 0.016 per slot.
+// Against one workgroup per key block: 512 rows, 2 heads 37 -> 25 us; 4096 rows, 8
+// heads on 2 433 -> 112; 8192 rows, 4 heads 848 -> 203; 32768 rows, 8 heads 7.8 -> 4.4
+// ms, where 1028 tiles per CU are 4.2 ms.
 DkdvSplit dkdv_split(int64_t Sp, int Hkv, int G, int causal, size_t bytes0, size_t bytes1) {
   const int nqt = (int)(Sp / QT);
   DkdvSplit best;
-  double best_est = 1e300;
   for (int qs = 1; qs <= 2; ++qs) {
     const size_t slot = (size_t)2 * (128 / qs) * HEAD_DIM * 4;
     const int64_t have = (int64_t)(bytes0 / slot + bytes1 / slot);
@@ -829,13 +856,14 @@ DkdvSplit dkdv_split(int64_t Sp, int Hkv, int G, int causal, size_t bytes0, size
       DkdvSplit p;
       p.qs = qs;
       p.T = causal ? G * ((8 * nqt + n - 1) / n) : (8 * G * nqt + n - 1) / n;
-      p.per_head = (int)slots_per_head(causal, qs, p.T, G, nqt, &p.max_seg);
-      if (Hkv * (int64_t)p.per_head > have) continue;
-      const int c1 = seg_blocks_of(causal, qs, 1, p.T, G, nqt);
-      const double T = p.T * (qs == 1 ? 1.0 : causal ? 0.86 : 0.72) + 2.0;
+      p.whole = (int)whole_segments(causal, qs, p.T, G, nqt);
+      const int64_t used = Hkv * (int64_t)(p.whole + seg_blocks_of(causal, qs, 1, p.T, G, nqt));
+      if (used > have) continue;
       const int64_t blocks = (int64_t)Hkv * nqt * qs;
+      const double busy = std::min(1.0, (blocks + Hkv * (double)p.whole) / 256);
+      const double T = p.T * (qs == 1 ? 0.8 + 0.2 * busy : causal ? 0.64 : 0.58) + 2.0;
       const int64_t rest = causal ? blocks : 0;
-      const int64_t whole = Hkv * (int64_t)(p.per_head - c1) + (causal ? 0 : blocks);
+      const int64_t whole = Hkv * (int64_t)p.whole + (causal ? 0 : blocks);
       if (qs > 1 && whole + rest > 288) continue;
       const int64_t rounds = whole / 256, extra = whole % 256, room = 256 - extra;
       double span = rounds * T;
@@ -845,13 +873,11 @@ DkdvSplit dkdv_split(int64_t Sp, int Hkv, int G, int causal, size_t bytes0, size
         // `room` of the others start at once, the rest (up to x long) as
         // those finish, the shortest first
         const double x = T * (rest - room) / rest;
-        span += std::max(T, rest <= 2 * room ? 2 * x : (extra + rest * 0.5) * T / 256 + 0.5 * T);
+        span += rest <= 2 * room ? std::max(T, 2 * x) + 0.3 * T
+                                 : std::max(T, (extra + rest * 0.5) * T / 256 + 0.5 * T);
       }
-      const double est = span + (c1 > 0 ? 1.5 + Hkv * p.per_head * 0.016 / qs : 0);
-      if (est < best_est) {
-        best_est = est;
-        best = p;
-      }
+      p.est = span + (used > 0 ? 1.5 + used * 0.016 / qs : 0);
+      if (best.T == 0 || p.est < best.est) best = p;
     }
   }
   return best;
@@ -862,6 +888,7 @@ hipError_t launch_attn_bwd_dkdv_split(const HeadView& Q, const HeadView& dO, con
                                       const HeadView& dk, const HeadView& dv, int64_t S, int64_t Sp,
                                       int Hkv, int G, int causal, const DkdvSplit& p, char* region0,
                                       size_t bytes0, char* region1, hipStream_t st) {
+  if (p.T < 1) return hipErrorInvalidValue;
   const int nqt = (int)(Sp / QT);
   const size_t slot = (size_t)2 * (128 / p.qs) * HEAD_DIM * 4;
   DkdvSlots s;
@@ -869,11 +896,11 @@ hipError_t launch_attn_bwd_dkdv_split(const HeadView& Q, const HeadView& dO, con
   s.p1 = (float*)region1;
   s.n0 = (int64_t)(bytes0 / slot);
   s.T = p.T;
-  s.max_seg = p.max_seg;
   s.kv_heads = Hkv;
-  s.per_head = p.per_head;
-  const int c1 = seg_blocks_of(causal, p.qs, 1, p.T, G, nqt);
-  dim3 grid((unsigned)((nqt * p.qs + p.per_head - c1) * Hkv));
+  s.whole = p.whole;
+  const int c1 = seg_blocks_of(causal, p.qs, 1, p.T, G, nqt);   // blocks with several
+  s.per_head = p.whole + c1;
+  dim3 grid((unsigned)((nqt * p.qs + p.whole) * Hkv));
   dim3 fold((unsigned)(c1 * (128 / p.qs / 8)), (unsigned)Hkv);
 #define UPIPE_DKDV(C, N)                                                                         \
   hipLaunchKernelGGL((attn_bwd_dkdv_kernel<C, N>), grid, dim3(256), 0, st, Q, dO, lse_c, D,      \

@@ -78,14 +78,14 @@ hipError_t launch_attn_bwd_dkdv(const HeadView& Q, const HeadView& dO, const flo
 struct DkdvSplit {
   int qs = 1;          // 128 / qs keys per workgroup
   int T = 0;           // tiles of a segment
-  int max_seg = 0;     // segments of the longest list, less one
-  int per_head = 0;    // slots of a key/value head
+  int whole = 0;       // segments of a key/value head that are not a list's last
+  double est = 0;      // expected time, in tiles
 };
 struct DkdvSlots {
   float* p0 = nullptr;     // slots 0 .. n0 - 1
   float* p1 = nullptr;     // slots n0 ..
   int64_t n0 = 0;
-  int T = 0, max_seg = 0, per_head = 0, kv_heads = 1;
+  int T = 0, kv_heads = 1, whole = 0, per_head = 0;   // per_head: slots of a kv head
   __device__ float* at(int64_t i, int64_t floats) const {
     return i < n0 ? p0 + i * floats : p1 + (i - n0) * floats;
   }

@@ -251,9 +251,10 @@ int upipe_rope(void* x, int64_t S, int H, int d, int64_t pos0, double base, int 
 
 /* ------------------------------------------------------------------------
  * Attention block forward (Section 3.3, Appendix A "Untied Ulysses
- * (forward)": per stage, QKV projection of the stage's heads, attention,
- * output written into its slot of `final_out`; after the last stage the
- * output projection y = final_out wo).  Always causal.
+ * (forward)"): QKV projection, attention written into `final_out`, output
+ * projection y = final_out wo.  On one GPU all heads go through each step
+ * together (the queries pass through o_saved); no result depends on U.  Always
+ * causal.
  *
  *   x         bf16 [S, d_model]                  hidden states
  *   wqkv      bf16 [d_model, (Hq + 2 Hkv) d]     columns [Q heads|K|V]
@@ -270,21 +271,19 @@ int upipe_layer_fwd(const void* x, const void* wqkv, const void* wo, void* y,
                     hipStream_t stream);
 
 /* ------------------------------------------------------------------------
- * Attention block backward (Appendix A "Untied Ulysses (backward)"): the
- * gradient of final_out, dY wo^T, is formed once and kept for the stage
- * loop, and dWo = final_out^T dY; per chunk, Q_c is recomputed from x and the
- * attention backward yields dQ_c and the running dK, dV sums; after the last
- * chunk dX = [dQ | dK | dV] wqkv^T and dWqkv = x^T [dQ | dK | dV], each in
- * one product.  K and V are recomputed from x (activation checkpointing
- * keeps only x, final_out, lse).
+ * Attention block backward (Appendix A "Untied Ulysses (backward)"): Q, K and
+ * V are recomputed from x (activation checkpointing keeps only x, final_out,
+ * lse); the gradient of final_out is dY wo^T and dWo = final_out^T dY; the
+ * attention backward yields dQ, dK, dV of all heads; then dX = [dQ | dK | dV]
+ * wqkv^T and dWqkv = x^T [dQ | dK | dV].  Each product runs once.
  *
  *   x, wqkv, wo        as for upipe_layer_fwd
  *   o_saved, lse_saved the forward's outputs for the same x and weights
  *                      (selective checkpointing: the attention output is
- *                      kept), or both NULL (full checkpointing: each
- *                      chunk's attention forward is recomputed, bitwise
- *                      equal to the forward's, at the cost of one more
- *                      attention forward; the results are identical)
+ *                      kept), or both NULL (full checkpointing: the
+ *                      attention forward is recomputed, bitwise equal to
+ *                      the forward's, at the cost of one more attention
+ *                      forward; the results are identical)
  *   dy    bf16 [S, d_model]                 upstream gradient of y
  *   dx    bf16 [S, d_model]                 out
  *   dwqkv bf16 [d_model, (Hq + 2 Hkv) d]    out

@@ -38,12 +38,16 @@ inline GemmOperand operand(const bf16* p, int64_t ld, int64_t rows_valid, int64_
 enum { GEMM_EPI_HEADS = 0, GEMM_EPI_ACC32 = 1, GEMM_EPI_PARTIAL = 2 };
 
 struct GemmEpilogue {
-  // GEMM_EPI_HEADS: output column block nb (128 wide) is head nb of group 0
-  // if nb < n_split, else head nb - n_split of group 1; dst_norm[g] is
-  // [heads][Sp][128].  Every row m < M is written.
-  bf16* dst_norm[2];
-  int64_t n_split;
-  int64_t Sp;
+  // GEMM_EPI_HEADS: output column block nb (128 wide) is head nb - first of
+  // the last group with first <= nb; row m of it goes to
+  // p + head * head_stride + m * row_stride (128 elements), m < m_store.
+  struct Group {
+    bf16* p;
+    int64_t row, head;
+    int first;
+  };
+  Group group[3];
+  int n_groups;
   // Rotary embedding of the heads of the groups whose bit is set in
   // rope_groups (bit g: group g), row m at position rope.pos0 + m, applied
   // to the fp32 accumulators before rounding.
@@ -51,7 +55,7 @@ struct GemmEpilogue {
   int rope_groups;
   // GEMM_EPI_ACC32: accumulators start at c32[m][n] (ldc) unless `first`;
   // the result goes to c32 unless `last`, else to out[m][n] (ldo) as bf16.
-  // Rows >= m_store are neither read nor written.
+  // Rows >= m_store are neither read nor written (here and with HEADS).
   float* c32;
   int64_t ldc;
   bf16* out;

@@ -221,8 +221,11 @@ __global__ __launch_bounds__(256, 3 - GemmStages<EPI>::N) void gemm_kernel(
 
   // ---- epilogues.  Lane holds column n = n0 + 32wn + 64nt + r32 and rows
   //      m = m0 + 64wm + 32mt + 8a + 4g + b for element i = 4a + b.
-  if (EPI == GEMM_EPI_HEADS && E.rope.on &&
-      ((E.rope_groups >> (n0 / 128 < E.n_split ? 0 : 1)) & 1)) {
+  const int nb = (int)(n0 / 128);     // output head (HEADS): a tile is 128 columns
+  int grp = 0;
+  if (EPI == GEMM_EPI_HEADS)
+    while (grp + 1 < E.n_groups && nb >= E.group[grp + 1].first) ++grp;
+  if (EPI == GEMM_EPI_HEADS && E.rope.on && ((E.rope_groups >> grp) & 1)) {
     // Pair (e, e + 64), e = 32wn + r32, of rows m: acc[mt][0][i], acc[mt][1][i].
     // The turn of the first row of each 32-row block is reduced in fp64; the
     // offsets 8a + b (< 28) add at most 28 theta_e / 2 pi turns in fp32.
@@ -246,14 +249,12 @@ __global__ __launch_bounds__(256, 3 - GemmStages<EPI>::N) void gemm_kernel(
       const int64_t n = n0 + 32 * wn + 64 * nt + r32;
       const int64_t mb = m0 + 64 * wm + 32 * mt;
       if (EPI == GEMM_EPI_HEADS) {
-        const int64_t nb = n / 128, e = n % 128;
-        const int grp = nb < E.n_split ? 0 : 1;
-        const int64_t head = nb - (grp ? E.n_split : 0);
-        bf16* dn = E.dst_norm[grp];
+        const GemmEpilogue::Group& G = E.group[grp];
+        bf16* dn = G.p + (nb - G.first) * G.head + n % 128;
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
           const int64_t m = mb + 8 * (i >> 2) + 4 * g + (i & 3);
-          dn[(head * E.Sp + m) * 128 + e] = (bf16)acc[mt][nt][i];
+          if (m < E.m_store) dn[m * G.row] = (bf16)acc[mt][nt][i];
         }
       } else if (EPI == GEMM_EPI_ACC32) {
 #pragma unroll
@@ -277,22 +278,27 @@ __global__ __launch_bounds__(256, 3 - GemmStages<EPI>::N) void gemm_kernel(
 
 // t = sum over splits s = 0.. of partial[s][m][n], summed in ascending s,
 // then added to acc32[m][n] unless `first`; the total goes to acc32 unless
-// `last`, else to out[m * ldo + col0 + n] as bf16.
+// `last`, else to out[m * ldo + col0 + n] as bf16.  HBM-bound: a thread has four
+// consecutive columns (N is a multiple of 128).
 __global__ __launch_bounds__(256) void reduce_splitk_kernel(const float* __restrict__ partial,
                                                             int splits, int64_t M, int64_t N,
                                                             bf16* __restrict__ out, int64_t ldo,
                                                             int64_t col0, float* __restrict__ acc32,
                                                             int first, int last) {
-  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t idx = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
   if (idx >= M * N) return;
-  float s = 0.f;
-  for (int k = 0; k < splits; ++k) s += partial[(int64_t)k * M * N + idx];
-  if (!first) s = acc32[idx] + s;
+  f32x4 s = *reinterpret_cast<const f32x4*>(partial + idx);
+  for (int k = 1; k < splits; ++k)
+    s += *reinterpret_cast<const f32x4*>(partial + (int64_t)k * M * N + idx);
+  if (!first) s = *reinterpret_cast<const f32x4*>(acc32 + idx) + s;
   if (last) {
     const int64_t m = idx / N, n = idx % N;
-    out[m * ldo + col0 + n] = (bf16)s;
+    bf16x4 v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = (bf16)s[e];
+    *reinterpret_cast<bf16x4*>(out + m * ldo + col0 + n) = v;
   } else {
-    acc32[idx] = s;
+    *reinterpret_cast<f32x4*>(acc32 + idx) = s;
   }
 }
 
@@ -331,7 +337,7 @@ hipError_t launch_reduce_splitk(const float* partial, int splits, int64_t M, int
                                 int64_t ldo, int64_t col0, float* acc32, int first, int last,
                                 hipStream_t st) {
   const int64_t n = M * N;
-  hipLaunchKernelGGL(reduce_splitk_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
+  hipLaunchKernelGGL(reduce_splitk_kernel, dim3((unsigned)((n + 1023) / 1024)), dim3(256), 0, st,
                      partial, splits, M, N, out, ldo, col0, acc32, first, last);
   return hipGetLastError();
 }

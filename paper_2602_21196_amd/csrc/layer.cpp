@@ -1,38 +1,33 @@
-// Attention-block entry points: projections around the chunked attention.
+// Attention-block entry points: projections around the attention of all heads.
 //
-// Forward (paper Section 3.3, Appendix A "Untied Ulysses (forward)"):
-//   K, V = x Wk, x Wv                      once (kept for every chunk)
-//   per chunk c of U heads:
-//     Q_c  = x Wq_c                          QKV projection slice
-//     O_c  = attention(Q_c, K, V)           flash forward, lse saved
-//     final_out[:, chunk] = O_c              (o_saved)
-//   y = final_out Wo                         output projection, once
-// Backward (Appendix A "Untied Ulysses (backward)"), with K, V and Q_c
+// The paper runs stages of U heads (Section 3.3) because every stage's heads
+// arrive by an all-to-all.  On one GPU all heads are here, so each product over
+// heads runs once and the attention kernels take all heads in one launch; no
+// result depends on U.
+// Forward (Appendix A "Untied Ulysses (forward)"):
+//   Q | K | V = x Wqkv                     one product; Q in the rows of
+//                                          o_saved, K and V head-major
+//   final_out = attention(Q, K, V)         in the place of Q, lse saved
+//   y = final_out Wo                       output projection
+// Backward (Appendix A "Untied Ulysses (backward)"), with Q, K, V
 // recomputed from x (activation checkpointing keeps x, final_out, lse):
-//   dFO   = dY Wo^T                          gradient of final_out, once,
-//                                            head-major, kept for the loop
-//   dWo   = final_out^T dY                   split-K over S, ordered sum
-//   per chunk c:
-//     Q_c   = x Wq_c                         recompute
-//     (O_c, lse_c = attention(Q_c, K, V)     full checkpointing only: the
-//      dWo_c = O_c^T dY)                     attention output was not kept
-//     D     = rowsum(dFO_c * O_c)
-//     dK, dV += ...,  dQ_c                   attention backward; dQ_c lands
-//                                            in its heads' slots of dQKV
-//   dx    = [dQ | dK | dV] Wqkv^T            one product, bf16 out
-//   dWqkv = x^T [dQ | dK | dV]               split-K over S
-// The per-head results (dQ_c, the fp32 dK/dV carries taken in one fixed head
-// order) do not depend on U, and every product over heads runs once, so all
-// outputs are bitwise identical for every chunk size U.  On one GPU the
-// paper's per-stage accumulation of dX (a d_model-wide buffer updated by
-// every stage) becomes one product over the bf16 dQ of all heads, which is
-// smaller than that accumulator and reads nothing twice.
-// Rotary embedding (optional, Section 4 "Implementation"): Q_c and K are
+//   Q | K | V = x Wqkv                     Q in the dQ part of dQKV
+//   dFO   = dY Wo^T                        gradient of final_out, head-major
+//   (O, lse = attention(Q, K, V))          full checkpointing only: the
+//                                          attention output was not kept
+//   dWo   = final_out^T dY                 split-K over S, ordered sum
+//   D     = rowsum(dFO * O)
+//   dK, dV, then dQ in the place of Q      attention backward
+//   dx    = [dQ | dK | dV] Wqkv^T          one product, bf16 out
+//   dWqkv = x^T [dQ | dK | dV]             split-K over S
+// Against the products and attention of one chunk of U heads at a time, 8192 tokens
+// of the Llama3-8B share (d_model 4096, 4 heads, U = 1): the five QKV products
+// 2 x 307 -> 2 x 95 us.
+// Rotary embedding (optional, Section 4 "Implementation"): Q and K are
 // rotated in the projection epilogue, on the fp32 accumulators, before they
 // are rounded and stored -- in place, with no extra pass or fp32 copy.  The
-// backward recomputes them the same way and turns dQ_c back by the inverse
-// rotation in the dQ kernel's final write, and dK in one in-place pass after
-// the last chunk.
+// backward recomputes them the same way and turns dQ back by the inverse
+// rotation in the dQ kernel's final write, and dK in one in-place pass.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -47,8 +42,6 @@ namespace upipe {
 
 namespace {
 
-constexpr int64_t kSplitTarget = 32;   // weight-gradient split count target
-
 int check_layer_shape(int64_t S, int d_model, int Hq, int Hkv, int d, int U) {
   int rc = check_attn_shape(S, Hq, Hkv, d, U);
   if (rc != UPIPE_OK) return rc;
@@ -59,25 +52,30 @@ int check_layer_shape(int64_t S, int d_model, int Hq, int Hkv, int d, int U) {
   return UPIPE_OK;
 }
 
-// Split length of the sequence for weight gradients: a function of S only
-// (never of U), a multiple of the GEMM k-step.
-int64_t wgrad_split_len(int64_t S) {
-  int64_t len = round_up((S + kSplitTarget - 1) / kSplitTarget, 256);
-  return len < 256 ? 256 : len;
+// Split length of the sequence for the weight gradient of a [M, N] weight: a
+// function of S and the whole weight only (never of U), a multiple of the
+// GEMM k-step.  Two rounds of 128 x 128 tiles on the 256 CUs x 2 workgroups: more
+// pieces cost fp32 partials (4096 x 768, 8192 rows: 32 pieces 116 + 124 us for
+// product and sum, 5 pieces 75 + 18 us), fewer leave CUs idle.
+int64_t wgrad_split_len(int64_t S, int64_t M, int64_t N) {
+  const int64_t tiles = (M / 128) * (N / 128);
+  const int64_t want = std::min<int64_t>(32, std::max<int64_t>(1, 1024 / tiles));
+  return std::max<int64_t>(256, round_up((S + want - 1) / want, 256));
 }
 
 struct LayerFwdPlan {
   int64_t Sp = 0;
-  size_t Kp = 0, Vp = 0, Qc = 0, Oc = 0, total = 0;
+  size_t Kp = 0, Vp = 0, total = 0;
 };
 
 struct LayerBwdPlan {
-  int64_t Sp = 0, split_len = 0;
-  int splits = 0;
+  int64_t Sp = 0;
   bool carry = false;          // a key/value group spans several chunks
-  size_t Kp = 0, Vp = 0, dK32 = 0, dV32 = 0, Qc = 0, D = 0, lse_c = 0;
+  int o_heads = 0;             // heads of recomputed attention output held at a time
+  size_t Kp = 0, Vp = 0, dK32 = 0, dV32 = 0, D = 0, lse_c = 0;
   size_t Oc = 0, lse_r = 0;    // recomputed attention output (full checkpointing)
-  size_t dFO = 0, dQKV = 0, partial = 0;
+  size_t dFO = 0, dQKV = 0;
+  size_t scratch = 0, scratch_bytes = 0;   // split-K partials; dK/dV segment sums
   size_t dWqkv32 = 0, dWo32 = 0;   // weight-gradient sums over a batch of sequences
   size_t total = 0;
 };
@@ -91,19 +89,41 @@ LayerFwdPlan plan_layer_fwd(int64_t S, int d_model, int Hq, int Hkv, int U) {
   Carver c;
   p.Kp = c.take(Hkv * head);
   p.Vp = c.take(Hkv * head);
-  p.Qc = c.take(U * head);
-  p.Oc = c.take(U * head);
+  // A chunk's Q and O, no longer staged: the size that callers have been told
+  // to bring stays.
+  c.take(U * head);
+  c.take(U * head);
   p.total = c.used;
   return p;
+}
+
+// Bytes of the backward's workspace when the weight gradients were cut into up
+// to 32 pieces and a chunk's Q, O and rows were held: callers have been told to
+// bring these, and the plan below stays within them.
+size_t layer_bwd_budget(int64_t S, int d_model, int Hq, int Hkv, int U) {
+  const int64_t Sp = round_up(S, SEQ_PAD);
+  const int64_t len = std::max<int64_t>(256, round_up((S + 31) / 32, 256));
+  const size_t head = (size_t)Sp * HEAD_DIM * 2;
+  const int64_t widest = (int64_t)(Hq + 2 * Hkv) * HEAD_DIM;
+  Carver c;
+  c.take(2 * Hkv * head);
+  if (group_split(Hq, Hkv, U)) c.take(4 * Hkv * head);
+  c.take(2 * U * head);
+  c.take(2 * (size_t)U * Sp * 4);
+  c.take((size_t)Hq * S * 4);
+  c.take((2 * Hq + 2 * Hkv) * head);
+  c.take((size_t)((S + len - 1) / len) * d_model * widest * 4);
+  c.take((size_t)d_model * widest * 4);
+  c.take((size_t)Hq * HEAD_DIM * d_model * 4);
+  return c.used;
 }
 
 LayerBwdPlan plan_layer_bwd(int64_t S, int d_model, int Hq, int Hkv, int U) {
   LayerBwdPlan p;
   p.Sp = round_up(S, SEQ_PAD);
-  p.split_len = wgrad_split_len(S);
-  p.splits = (int)((S + p.split_len - 1) / p.split_len);
   const size_t head = (size_t)p.Sp * HEAD_DIM * 2;
-  const size_t row32 = (size_t)p.Sp * 4;
+  const size_t rows = (size_t)Hq * p.Sp * 4;
+  const int64_t nqkv = (int64_t)(Hq + 2 * Hkv) * HEAD_DIM, qw = (int64_t)Hq * HEAD_DIM;
   Carver c;
   p.Kp = c.take(Hkv * head);
   p.Vp = c.take(Hkv * head);
@@ -112,33 +132,49 @@ LayerBwdPlan plan_layer_bwd(int64_t S, int d_model, int Hq, int Hkv, int U) {
     p.dK32 = c.take(Hkv * head * 2);
     p.dV32 = c.take(Hkv * head * 2);
   }
-  p.Qc = c.take(U * head);
-  p.D = c.take(U * row32);
-  p.lse_c = c.take(U * row32);
-  p.Oc = c.take(U * head);
+  p.D = c.take(rows);
+  p.lse_c = c.take(rows);
   p.lse_r = c.take((size_t)Hq * S * 4);
   p.dFO = c.take(Hq * head);
   p.dQKV = c.take((Hq + 2 * Hkv) * head);
-  // Split-K partials of the larger weight gradient: dWqkv [d_model, (Hq +
-  // 2Hkv) d] or dWo [Hq d, d_model].
-  const int64_t widest = (int64_t)(Hq + 2 * Hkv) * HEAD_DIM;
-  p.partial = c.take((size_t)p.splits * d_model * widest * 4);
-  p.dWqkv32 = c.take((size_t)d_model * widest * 4);
-  p.dWo32 = c.take((size_t)Hq * HEAD_DIM * d_model * 4);
-  p.total = c.used;
+  const int64_t l1 = wgrad_split_len(S, d_model, nqkv), l2 = wgrad_split_len(S, qw, d_model);
+  p.scratch_bytes = std::max((size_t)((S + l1 - 1) / l1) * d_model * nqkv * 4,
+                             (size_t)((S + l2 - 1) / l2) * d_model * qw * 4);
+  p.scratch = c.take(p.scratch_bytes);
+  p.dWqkv32 = c.take((size_t)d_model * nqkv * 4);
+  p.dWo32 = c.take((size_t)qw * d_model * 4);
+  // The rest of the budget holds as many heads of recomputed attention output
+  // as there are (one at least).
+  const size_t budget = layer_bwd_budget(S, d_model, Hq, Hkv, U);
+  const size_t used = c.used + 256;
+  p.o_heads = budget > used ? (int)std::min<size_t>(Hq, (budget - used) / head) : 0;
+  p.o_heads = std::max(1, p.o_heads);
+  p.Oc = c.take(p.o_heads * head);
+  p.total = std::max(c.used, budget);
   return p;
 }
 
-// Head-major outputs; `rope` rotates the heads of group 0 (Q, or K of K|V).
-GemmEpilogue heads_epi(bf16* n0, bf16* n1, int64_t n_split, int64_t Sp,
-                       RopeArgs rope = RopeArgs{}) {
+// Head-major [heads][Sp][128] output from p on.
+GemmEpilogue heads_epi(bf16* p, int64_t Sp, int64_t m_store) {
   GemmEpilogue e{};
-  e.dst_norm[0] = n0;
-  e.dst_norm[1] = n1;
-  e.n_split = n_split;
-  e.Sp = Sp;
+  e.group[0] = {p, HEAD_DIM, Sp * HEAD_DIM, 0};
+  e.n_groups = 1;
+  e.m_store = m_store;
+  return e;
+}
+
+// Q | K | V of a product with Wqkv: Q wherever its view says, K and V
+// head-major, Q and K rotated.
+GemmEpilogue qkv_epi(const HeadView& Q, bf16* Kp, bf16* Vp, int Hq, int Hkv, int64_t S, int64_t Sp,
+                     RopeArgs rope) {
+  GemmEpilogue e{};
+  e.group[0] = {Q.p, Q.row, Q.head, 0};
+  e.group[1] = {Kp, HEAD_DIM, Sp * HEAD_DIM, Hq};
+  e.group[2] = {Vp, HEAD_DIM, Sp * HEAD_DIM, Hq + Hkv};
+  e.n_groups = 3;
+  e.m_store = S;
   e.rope = rope;
-  e.rope_groups = rope.on ? 1 : 0;
+  e.rope_groups = rope.on ? 3 : 0;
   return e;
 }
 
@@ -167,28 +203,17 @@ int run_layer_fwd_seq(const bf16* x, const bf16* wqkv, const bf16* wo, bf16* y, 
                       float* lse, int64_t S, int dm, int Hq, int Hkv, int U, RopeArgs rope,
                       char* ws, hipStream_t st) {
   const LayerFwdPlan p = plan_layer_fwd(S, dm, Hq, Hkv, U);
-  const int64_t Sp = p.Sp, ldw = (int64_t)(Hq + 2 * Hkv) * HEAD_DIM;
+  const int64_t Sp = p.Sp, nqkv = (int64_t)(Hq + 2 * Hkv) * HEAD_DIM;
   const int64_t qw = (int64_t)Hq * HEAD_DIM;
   bf16* Kp = (bf16*)(ws + p.Kp);
   bf16* Vp = (bf16*)(ws + p.Vp);
-  bf16* Qc = (bf16*)(ws + p.Qc);
-  const int G = Hq / Hkv;
-  const int parts = attn_fwd_key_parts(S, S, 0, Hq, 1);
-  const GemmOperand X = operand(x, dm, S, dm);
-  // K | V = x [Wk | Wv], both head-major.
+  const HeadView QO = token_major(o_saved, S, Hq);
   UPIPE_LAUNCH(kGemm, st,
-               gemm1(X, true, operand(wqkv + qw, ldw, 2 * Hkv * HEAD_DIM, dm),
-                     false, heads_epi(Kp, Vp, Hkv, Sp, rope), GEMM_EPI_HEADS, Sp,
-                     2 * Hkv * HEAD_DIM, dm, st));
-  for (int h0 = 0; h0 < Hq; h0 += U) {
-    UPIPE_LAUNCH(kGemm, st,
-                 gemm1(X, true, operand(wqkv + (int64_t)h0 * HEAD_DIM, ldw, U * HEAD_DIM, dm),
-                       false, heads_epi(Qc, nullptr, U, Sp, rope), GEMM_EPI_HEADS, Sp,
-                       U * HEAD_DIM, dm, st));
-    UPIPE_LAUNCH(kAttnFwd, st,
-                 launch_attn_fwd(head_major(Qc, Sp), head_major(Kp, Sp), head_major(Vp, Sp),
-                                 sub(token_major(o_saved, S, Hq), 0, h0), lse, S, S, 0, 1, Hq, U, h0, G, 1, parts, st));
-  }
+               gemm1(operand(x, dm, S, dm), true, operand(wqkv, nqkv, nqkv, dm), false,
+                     qkv_epi(QO, Kp, Vp, Hq, Hkv, S, Sp, rope), GEMM_EPI_HEADS, Sp, nqkv, dm, st));
+  UPIPE_LAUNCH(kAttnFwd, st,
+               launch_attn_fwd(QO, head_major(Kp, Sp), head_major(Vp, Sp), QO, lse, S, S, 0, 1, Hq,
+                               Hq, 0, Hq / Hkv, 1, attn_fwd_key_parts(S, S, 0, Hq, 1), st));
   // y = final_out Wo.
   UPIPE_LAUNCH(kGemm, st,
                gemm1(operand(o_saved, qw, S, qw), true, operand(wo, dm, dm, qw), false,
@@ -204,28 +229,20 @@ int run_layer_bwd_seq(const bf16* x, const bf16* wqkv, const bf16* wo, const bf1
                       int64_t S, int dm, int Hq, int Hkv, int U, RopeArgs rope, int first,
                       int last, char* ws, hipStream_t st) {
   const LayerBwdPlan p = plan_layer_bwd(S, dm, Hq, Hkv, U);
-  const int64_t Sp = p.Sp, ldw = (int64_t)(Hq + 2 * Hkv) * HEAD_DIM;
-  const int64_t qw = (int64_t)Hq * HEAD_DIM, kvw = (int64_t)Hkv * HEAD_DIM;
+  const int64_t Sp = p.Sp, nqkv = (int64_t)(Hq + 2 * Hkv) * HEAD_DIM;
+  const int64_t qw = (int64_t)Hq * HEAD_DIM;
   const int64_t head = Sp * HEAD_DIM;   // elements of one head-major head
   bf16* Kp = (bf16*)(ws + p.Kp);
   bf16* Vp = (bf16*)(ws + p.Vp);
-  float* dK32 = p.carry ? (float*)(ws + p.dK32) : nullptr;
-  float* dV32 = p.carry ? (float*)(ws + p.dV32) : nullptr;
-  bf16* Qc = (bf16*)(ws + p.Qc);
   float* D = (float*)(ws + p.D);
   float* lse_c = (float*)(ws + p.lse_c);
-  bf16* Oc = (bf16*)(ws + p.Oc);
-  float* lse_r = (float*)(ws + p.lse_r);
-  const bool recompute = o_saved == nullptr;   // full checkpointing: no saved output
   bf16* dFO = (bf16*)(ws + p.dFO);
   bf16* dQKV = (bf16*)(ws + p.dQKV);     // heads: dQ 0..Hq-1, dK Hq.., dV Hq+Hkv..
   bf16* dKh = dQKV + (int64_t)Hq * head;
   bf16* dVh = dKh + (int64_t)Hkv * head;
-  float* partial = (float*)(ws + p.partial);
-  float* dWqkv32 = (float*)(ws + p.dWqkv32);
-  float* dWo32 = (float*)(ws + p.dWo32);
   const int G = Hq / Hkv;
-  const int64_t nqkv = (int64_t)(Hq + 2 * Hkv) * HEAD_DIM;
+  const HeadView Q = head_major(dQKV, Sp), K = head_major(Kp, Sp), V = head_major(Vp, Sp);
+  const HeadView dO = head_major(dFO, Sp);
   const GemmOperand X = operand(x, dm, S, dm);
   const GemmOperand XT = operand(x, dm, dm, S);        // MN-major view: (m = col, k = s)
   const GemmOperand dY = operand(dy, dm, S, dm);
@@ -234,69 +251,75 @@ int run_layer_bwd_seq(const bf16* x, const bf16* wqkv, const bf16* wo, const bf1
   // Weight gradient C[M][N] = sum over s of A(m, s) B(n, s), split into fixed
   // pieces of the sequence and summed in order (then onto the batch sum
   // acc32 [M][N]) into out[m * ldo + n].
-  auto wgrad = [&](const GemmOperand& A, const GemmOperand& B, int64_t M, int64_t N, bf16* out,
-                   int64_t ldo, float* acc32) -> int {
+  auto wgrad = [&](const GemmOperand& A, const GemmOperand& B, int64_t M, int64_t N, int64_t len,
+                   bf16* out, int64_t ldo, size_t acc32) -> int {
     GemmEpilogue e{};
-    e.partial = partial;
+    e.partial = (float*)(ws + p.scratch);
     e.k_total = S;
+    const int splits = (int)((S + len - 1) / len);
     UPIPE_LAUNCH(kGemmWgrad, st,
-                 launch_gemm(A, false, B, false, e, GEMM_EPI_PARTIAL, M, N, 0, p.split_len,
-                             p.splits, st));
+                 launch_gemm(A, false, B, false, e, GEMM_EPI_PARTIAL, M, N, 0, len, splits, st));
     UPIPE_LAUNCH(kReduceSplitk, st,
-                 launch_reduce_splitk(partial, p.splits, M, N, out, ldo, 0, acc32, first, last,
-                                      st));
+                 launch_reduce_splitk(e.partial, splits, M, N, out, ldo, 0, (float*)(ws + acc32),
+                                      first, last, st));
     return UPIPE_OK;
   };
 
-  // Recompute K and V (head-major, K rotated).
+  // Q, K and V again (Q and K rotated); dQ will take the place of Q.
   UPIPE_LAUNCH(kGemm, st,
-               gemm1(X, true, operand(wqkv + qw, ldw, 2 * kvw, dm), false,
-                     heads_epi(Kp, Vp, Hkv, Sp, rope), GEMM_EPI_HEADS, Sp, 2 * kvw, dm, st));
-  // dFO = dY Wo^T for every head, head-major (Wo rows are k-contiguous).
+               gemm1(X, true, operand(wqkv, nqkv, nqkv, dm), false,
+                     qkv_epi(Q, Kp, Vp, Hq, Hkv, S, Sp, rope), GEMM_EPI_HEADS, Sp, nqkv, dm, st));
+  // dFO = dY Wo^T for every head (Wo rows are k-contiguous).
   UPIPE_LAUNCH(kGemm, st,
-               gemm1(dY, true, operand(wo, dm, qw, dm), true, heads_epi(dFO, nullptr, Hq, Sp),
+               gemm1(dY, true, operand(wo, dm, qw, dm), true, heads_epi(dFO, Sp, S),
                      GEMM_EPI_HEADS, Sp, qw, dm, st));
+  const int64_t wo_len = wgrad_split_len(S, qw, dm);
   int rc;
-  if (!recompute) {   // dWo = final_out^T dY from the kept final_out
-    rc = wgrad(operand(o_saved, qw, qw, S), dYn, qw, dm, dwo, dm, dWo32);
+  if (o_saved != nullptr) {   // dWo = final_out^T dY from the kept final_out
+    rc = wgrad(operand(o_saved, qw, qw, S), dYn, qw, dm, wo_len, dwo, dm, p.dWo32);
     if (rc != UPIPE_OK) return rc;
-  }
-  for (int h0 = 0; h0 < Hq; h0 += U) {
-    const int64_t w = (int64_t)U * HEAD_DIM;
-    bf16* dOc = dFO + (int64_t)h0 * head;
-    bf16* dQc = dQKV + (int64_t)h0 * head;
-    // Q_c recomputed, head-major, rotated.
-    UPIPE_LAUNCH(kGemm, st,
-                 gemm1(X, true, operand(wqkv + (int64_t)h0 * HEAD_DIM, ldw, w, dm), false,
-                       heads_epi(Qc, nullptr, U, Sp, rope), GEMM_EPI_HEADS, Sp, w, dm, st));
-    if (recompute) {
-      // The chunk's attention output and lse again (the same kernel on the
-      // same operands: bitwise what the forward produced), and its rows of
-      // dWo = O_c^T dY.
+    UPIPE_LAUNCH(kRowdotLse, st,
+                 launch_rowdot_lse(dO, token_major(o_saved, S, Hq), lse, S, 1, Hq, 0, Hq, Sp, D,
+                                   lse_c, st));
+  } else {
+    // Full checkpointing: the attention output and lse again (the same kernel
+    // on the same operands: bitwise what the forward produced), and their
+    // rows of dWo, as many heads at a time as the workspace holds.
+    float* lse_r = (float*)(ws + p.lse_r);
+    bf16* Oc = (bf16*)(ws + p.Oc);
+    const int parts = attn_fwd_key_parts(S, S, 0, Hq, 1);
+    for (int h0 = 0; h0 < Hq; h0 += p.o_heads) {
+      const int n = std::min(p.o_heads, Hq - h0);
+      const int64_t w = (int64_t)n * HEAD_DIM, row0 = (int64_t)h0 * HEAD_DIM * dm;
+      const HeadView O = head_major(Oc, Sp);
       UPIPE_LAUNCH(kAttnFwd, st,
-                   launch_attn_fwd(head_major(Qc, Sp), head_major(Kp, Sp), head_major(Vp, Sp),
-                                   head_major(Oc, Sp), lse_r, S, S, 0, 1, Hq, U, h0, G, 1,
-                                   attn_fwd_key_parts(S, S, 0, Hq, 1), st));
+                   launch_attn_fwd(sub(Q, 0, h0), K, V, O, lse_r, S, S, 0, 1, Hq, n, h0, G, 1,
+                                   parts, st));
       UPIPE_LAUNCH(kRowdotLse, st,
-                   launch_rowdot_lse(head_major(dOc, Sp), head_major(Oc, Sp), lse_r, S, 1, Hq, h0,
-                                     U, Sp, D, lse_c, st));
-      rc = wgrad(operand(Oc, HEAD_DIM, w, S, HEAD_DIM, head), dYn, w, dm,
-                 dwo + (int64_t)h0 * HEAD_DIM * dm, dm, dWo32 + (int64_t)h0 * HEAD_DIM * dm);
+                   launch_rowdot_lse(sub(dO, 0, h0), O, lse_r, S, 1, Hq, h0, n, Sp, D + h0 * Sp,
+                                     lse_c + h0 * Sp, st));
+      rc = wgrad(operand(Oc, HEAD_DIM, w, S, HEAD_DIM, head), dYn, w, dm, wo_len, dwo + row0, dm,
+                 p.dWo32 + row0 * 4);
       if (rc != UPIPE_OK) return rc;
-    } else {
-      UPIPE_LAUNCH(kRowdotLse, st,
-                   launch_rowdot_lse(head_major(dOc, Sp), sub(token_major(o_saved, S, Hq), 0, h0),
-                                     lse, S, 1, Hq, h0, U, Sp, D, lse_c, st));
     }
-    const HeadView Qh = head_major(Qc, Sp), dOh = head_major(dOc, Sp);
-    const HeadView Kh = head_major(Kp, Sp), Vh = head_major(Vp, Sp);
-    rc = run_dkdv(Qh, dOh, lse_c, D, Kh, Vh, dK32, dV32, head_major(dKh, Sp),
-                  head_major(dVh, Sp), S, Sp, U, h0, G, 1, st);
-    if (rc != UPIPE_OK) return rc;
-    UPIPE_LAUNCH(kAttnBwdDq, st,
-                 launch_attn_bwd_dq(Qh, dOh, lse_c, D, Kh, Vh, head_major(dQc, Sp), S, Sp, 1, U, h0, G, 1,
-                                    attn_bwd_dq_key_parts(S, Hq, 1), rope, st));
   }
+  // The weight gradients' scratch is free now: dK/dV segment sums.
+  if (S < kPerHeadRows) {
+    const DkdvSplit cut = dkdv_split(Sp, Hkv, G, 1, p.scratch_bytes, 0);
+    UPIPE_LAUNCH(kAttnBwdDkdv, st,
+                 launch_attn_bwd_dkdv_split(Q, dO, lse_c, D, K, V, head_major(dKh, Sp),
+                                            head_major(dVh, Sp), S, Sp, Hkv, G, 1, cut,
+                                            ws + p.scratch, p.scratch_bytes, nullptr, st));
+  } else {
+    float* dK32 = p.carry ? (float*)(ws + p.dK32) : nullptr;
+    float* dV32 = p.carry ? (float*)(ws + p.dV32) : nullptr;
+    rc = run_dkdv(Q, dO, lse_c, D, K, V, dK32, dV32, head_major(dKh, Sp), head_major(dVh, Sp), S,
+                  Sp, Hq, 0, G, 1, st);
+    if (rc != UPIPE_OK) return rc;
+  }
+  UPIPE_LAUNCH(kAttnBwdDq, st,
+               launch_attn_bwd_dq(Q, dO, lse_c, D, K, V, Q, S, Sp, 1, Hq, 0, G, 1,
+                                  attn_bwd_dq_key_parts(S, Hq, 1), rope, st));
   // dK is the gradient with respect to the rotated keys: turn it back, in
   // place (one bf16 pass over [Hkv, S, d]; kept out of the dK/dV kernel,
   // whose register allocation is at its limit).
@@ -305,11 +328,11 @@ int run_layer_bwd_seq(const bf16* x, const bf16* wqkv, const bf16* wo, const bf1
   // dx = [dQ | dK | dV] Wqkv^T (head-major A; Wqkv rows are k-contiguous).
   UPIPE_LAUNCH(kGemm, st,
                gemm1(operand(dQKV, HEAD_DIM, S, nqkv, HEAD_DIM, head), true,
-                     operand(wqkv, ldw, dm, nqkv), true, store_epi(dx, dm, S), GEMM_EPI_ACC32,
+                     operand(wqkv, nqkv, dm, nqkv), true, store_epi(dx, dm, S), GEMM_EPI_ACC32,
                      Sp, dm, nqkv, st));
   // dWqkv = x^T [dQ | dK | dV].
-  return wgrad(XT, operand(dQKV, HEAD_DIM, nqkv, S, HEAD_DIM, head), dm, nqkv, dwqkv, ldw,
-               dWqkv32);
+  return wgrad(XT, operand(dQKV, HEAD_DIM, nqkv, S, HEAD_DIM, head), dm, nqkv,
+               wgrad_split_len(S, dm, nqkv), dwqkv, nqkv, p.dWqkv32);
 }
 
 // Batches: the B sequences run one after another through the same

@@ -35,7 +35,7 @@ inline GemmOperand operand(const bf16* p, int64_t ld, int64_t rows_valid, int64_
   return GemmOperand{p, ld, blk, blk_stride, rows_valid, k_valid};
 }
 
-enum { GEMM_EPI_HEADS = 0, GEMM_EPI_ACC32 = 1, GEMM_EPI_PARTIAL = 2 };
+enum { GEMM_EPI_HEADS = 0, GEMM_EPI_STORE = 1, GEMM_EPI_PARTIAL = 2 };
 
 struct GemmEpilogue {
   // GEMM_EPI_HEADS: output column block nb (128 wide) is head nb - first of
@@ -53,16 +53,10 @@ struct GemmEpilogue {
   // to the fp32 accumulators before rounding.
   RopeArgs rope;
   int rope_groups;
-  // GEMM_EPI_ACC32: accumulators start at c32[m][n] (ldc) unless `first`;
-  // the result goes to c32 unless `last`, else to out[m][n] (ldo) as bf16.
-  // Rows >= m_store are neither read nor written (here and with HEADS).
-  float* c32;
-  int64_t ldc;
+  // GEMM_EPI_STORE: the result goes to out[m][n] (ldo) as bf16, m < m_store.
   bf16* out;
   int64_t ldo;
   int64_t m_store;
-  int first;
-  int last;
   // GEMM_EPI_PARTIAL: split s of the k range writes partial[s][M][N] fp32.
   float* partial;
   // k extent, counted from k_begin (splits beyond it are clamped).
@@ -73,8 +67,8 @@ struct GemmEpilogue {
 // is cut into `splits` pieces of k_len; k_begin and k_len are multiples of
 // 128, and so is k_total when an operand is K-major (hipErrorInvalidValue
 // otherwise).  Supported
-// combinations: (A K-major, B MN-major, HEADS | ACC32), (A K-major, B K-major,
-// HEADS | ACC32), (A MN-major, B MN-major, PARTIAL).
+// combinations: (A K-major, B MN-major, HEADS | STORE), (A K-major, B K-major,
+// HEADS | STORE), (A MN-major, B MN-major, PARTIAL).
 hipError_t launch_gemm(const GemmOperand& A, bool a_kmajor, const GemmOperand& B, bool b_kmajor,
                        const GemmEpilogue& E, int epi, int64_t M, int64_t N, int64_t k_begin,
                        int64_t k_len, int splits, hipStream_t st);

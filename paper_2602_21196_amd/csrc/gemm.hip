@@ -1,27 +1,30 @@
 // Projection GEMMs of the attention block on gfx950: C = A . B, bf16 inputs,
 // fp32 accumulation on MFMA 32x32x16.
 //
-// The block needs nine differently laid-out products (QKV projection slice,
-// output projection, their data and weight gradients; paper Section 3.3 and
+// The block needs differently laid-out products (QKV projection, output
+// projection, their data and weight gradients; paper Section 3.3 and
 // Appendix A).  No tensor is transposed in HBM.  Every operand tile is staged
-// into LDS exactly as it lies in memory -- 128 rows of 256 bytes:
-//   K-major operand  (k contiguous)    : rows = m (or n), 128 k per row;
-//   MN-major operand (m/n contiguous)  : rows = k, 128 m (or n) per row --
-// by buffer->LDS copies (no register staging), and the MFMA fragments are
-// read in one common k order, k = 8g + 0..7 within each 16-k step:
-//   a K-major operand          : plain 16-byte reads;
-//   an MN-major operand        : transposing reads (tr_operand_k8).
+// into LDS as it lies in memory, 64 k at a time, by buffer->LDS copies (no
+// register staging), and the MFMA fragments are read in one common k order,
+// k = 8g + 0..7 within each 16-k step:
+//   K-major operand  (k contiguous)    : rows = m (or n), 128 B of k each, two
+//                                        rows to a 256-B LDS line; plain
+//                                        16-byte reads;
+//   MN-major operand (m/n contiguous)  : 128-wide column blocks of 64 lines of
+//                                        256 B, line = k; transposing reads.
 // Operands may be split into 128-wide blocks with their own stride (the
-// head-major chunk buffers [U][Sp][128]).
+// head-major buffers [H][Sp][128]).
 //
-// Tile: 128 x 128 per workgroup, 4 waves as 2 x 2 of 64 x 32+32 (wave column
-// half wn holds columns 32 wn + 64 nt + 0..31, nt = 0, 1: the coordinate pairs
-// (e, e + 64) of a 128-wide head sit in one lane, which the rotary embedding
-// of the head-major epilogue needs), BK = 128, one 64 KB LDS stage per
-// workgroup and two workgroups per CU.  The k loop runs in ascending order with
-// one fp32 accumulator chain per output element, so a product split over
-// several calls (k ranges accumulated through an fp32 buffer) is bitwise equal
-// to a single call over the whole k range.
+// Tiles (BM x BN per workgroup) by what bounds them: a CU's L2->LDS path (64
+// B/clk) needs as long as its MFMAs for a 128 x 128 tile, half as long for 256 x
+// 256.  So 256 x 256 wherever its tiles fill the chip, else 128 x 128 (256 x 128
+// was never the fastest); two stages of 64 k each, the next one's copies in
+// flight during the products.  8192 x 4096 x 4096: 288 -> 220 us (955 -> 1249
+// TFLOP/s) against 128 x 128 tiles of 128 k in one stage; 8192^3 1297.  A wave has 64 columns, 32 c + 64 nt + 0..31 of a 128-wide
+// block (nt = 0, 1): the coordinate pairs (e, e + 64) of a head sit in one lane,
+// which the rotary embedding of the head epilogue needs.  The k loop runs in
+// ascending order with one fp32 accumulator chain per output element, so no
+// result depends on the tile.
 #include "common.h"
 #include "gemm.h"
 
@@ -29,8 +32,8 @@ namespace upipe {
 
 namespace {
 
-constexpr int BM = 128, BN = 128, BKG = 128;
-constexpr int TILE_BYTES = 128 * 256;     // 32 KB per operand per stage
+constexpr int BK = 64;
+typedef int i32x4 __attribute__((ext_vector_type(4)));
 
 // Address of operand element (r, k).
 // The block width is a power of two (128, or the unblocked 2^50), so the
@@ -43,234 +46,243 @@ __device__ __forceinline__ const bf16* elem_ptr(const GemmOperand& o, bool kmajo
   return o.p + (r >> sh) * o.blk_stride + k * o.ld + (r & mask);
 }
 
-// Buffer resource over the operand's tile at (r0, k0), bounded by the valid
-// rows (K-major: rows r0.. < rows_valid) or valid k (MN-major: k0.. <
-// k_valid), so that padding reads as zero.
-__device__ __forceinline__ buf_rsrc tile_rsrc(const GemmOperand& o, bool kmajor, int64_t r0,
-                                              int64_t k0) {
-  const int64_t n_lines = kmajor ? o.rows_valid - r0 : o.k_valid - k0;   // 256-B lines in use
-  int64_t bytes = n_lines <= 0 ? 0 : ((n_lines > 128 ? 127 : n_lines - 1) * o.ld + 128) * 2;
-  return make_rsrc(elem_ptr(o, kmajor, r0, k0), (uint32_t)bytes);
+// Buffer resource of one wave's part of an operand tile at (r0, k0), as its four
+// words: LINES lines of the tile (K-major: rows r0.. < rows_valid, 64 k of each;
+// MN-major: k0.. < k_valid, the 128 columns from r0 on, none past rows_valid),
+// so that padding reads as zero.
+template <bool KMAJOR, int LINES>
+__device__ __forceinline__ i32x4 tile_rsrc(const GemmOperand& o, int64_t r0, int64_t k0) {
+  const int64_t valid = KMAJOR ? o.rows_valid - r0 : r0 < o.rows_valid ? o.k_valid - k0 : 0;
+  const int64_t n = valid > LINES ? LINES : valid;
+  const int64_t bytes = n <= 0 ? 0 : ((n - 1) * o.ld + (KMAJOR ? BK : 128)) * 2;
+  const uint64_t a = (uint64_t)elem_ptr(o, KMAJOR, r0, k0);
+  return i32x4{(int)a, (int)((a >> 32) & 0xffff), (int)bytes, 0x00020000};
 }
 
-// This wave's share of one operand tile: 8 blocks of 4 lines of 256 B.  The
-// lane offsets `off` place line chunk c at LDS chunk c ^ tsw(line).
-__device__ __forceinline__ void issue_tile(buf_rsrc r, const uint32_t (&off)[8], char* tile, int w) {
-#pragma unroll
-  for (int i = 0; i < 8; ++i) dma_buf_b128(r, off[i], 0, tile + (8 * w + i) * 1024);
+// Buffer -> LDS copy of 16 bytes per lane to lds + 16 * lane.  Written out, so
+// that the compiler does not wait for the copies of the next stage before the
+// reads of this one (it cannot tell which LDS bytes a copy writes); the k loop
+// waits for them itself.  It has no register results.
+__device__ __forceinline__ void copy_b128(i32x4 r, uint32_t voff, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+               :: "s"(lds), "v"(voff), "s"(r) : "memory", "m0");
 }
 
-__device__ __forceinline__ void lane_offsets(int64_t ld, int w, int lane, uint32_t (&off)[8]) {
+// One operand's tile of R (m or n) x 64 k, R = 128 or 256, staged by W waves.
+template <bool KMAJOR, int R, int W>
+struct Tile {
+  static constexpr int BYTES = R * BK * 2;
+  static constexpr int NBLK = BYTES / 1024 / W;        // 1 KB blocks per wave
+  static constexpr int WAVES = W * 128 / R;            // that copy one 128-wide block
+  uint32_t voff[NBLK];
+
+  __device__ __forceinline__ void init(int64_t ld, int w, int lane) {
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int line = 4 * (8 * w + i) + (lane >> 4);
-    off[i] = (uint32_t)(line * ld * 2) + (((lane & 15) ^ tsw(line)) << 4);
+    for (int i = 0; i < NBLK; ++i) {
+      if (KMAJOR) {
+        // lines 4 blk.., line l = rows 2l, 2l + 1, chunk c of a row at c ^ (l & 7)
+        const int blk = NBLK * w + i, line = 4 * blk + (lane >> 4), slot = lane & 15;
+        const int row = 2 * line + (slot >> 3), c = (slot & 7) ^ (line & 7);
+        voff[i] = (uint32_t)(row * ld * 2) + c * 16;
+      } else {
+        const int blk = NBLK * (w % WAVES) + i, line = 4 * blk + (lane >> 4);
+        voff[i] = (uint32_t)(line * ld * 2) + (((lane & 15) ^ tsw(line)) << 4);
+      }
+    }
   }
-}
-
-// MN-major operand fragment: the 32 columns r0.. of a [k][128] tile at
-// k-step ks, lane l getting column r0 + (l % 32) at k = 16 ks + 8g + 0..7
-// (g = l / 32) -- eight consecutive k, so that a K-major partner reads the
-// same k as one plain 16-byte chunk.  (The attention kernels' tr_operand
-// takes k = 4g + 0..3, 8 + 4g + 0..3 instead, the row order of an MFMA
-// result tile; here both operands come from LDS and only have to agree.)
-// Two ds_read_b64_tr_b16 per lane: within each 16-lane group, loader lane t
-// reads the 8 bytes at row 16 ks + 8g + t/4 (+ 4 for the second read),
-// columns r0 + 16 ((l >> 4) & 1) + 4 (t % 4); with the swzt swizzle the
-// 8 rows x 4 chunks of one read fill every bank exactly twice.
-__device__ __forceinline__ bf16x8 tr_operand_k8(const char* tile, int ks, int r0, int lane) {
-  typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
-  const int t = lane & 15, hi = (lane >> 4) & 1, g = lane >> 5;
-  const int col = r0 + 16 * hi + 4 * (t & 3);
-  const int row = 16 * ks + 8 * g + (t >> 2);
-  const uint32_t cb = (uint32_t)(col & 7) << 1;   // byte offset inside the 16-byte chunk
-  const bf16x4 lo =
-      __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(tile + swzt(row, col >> 3) + cb));
-  const bf16x4 up =
-      __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(tile + swzt(row + 4, col >> 3) + cb));
-  bf16x8 v;
+  // This wave's copies of the tile at (r0, k0) to LDS address `lds`.
+  __device__ __forceinline__ void issue(const GemmOperand& o, int64_t r0, int64_t k0, uint32_t lds,
+                                        int w) const {
+    const i32x4 r = tile_rsrc<KMAJOR, KMAJOR ? R : BK>(o, KMAJOR ? r0 : r0 + 128 * (w / WAVES), k0);
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    v[e] = lo[e];
-    v[4 + e] = up[e];
+    for (int i = 0; i < NBLK; ++i) copy_b128(r, voff[i], lds + (NBLK * w + i) * 1024);
   }
-  return v;
-}
-
-// Fragment of the 32 rows (m or n) r0.. at k-step ks (16 k) of one tile, in
-// the k order k = 16 ks + 8g + 0..7 shared by both modes:
-//   KM: K-major tile, one plain 16-byte read (chunk 2 ks + g of the row)
-//   MN: MN-major tile, transposing reads (tr_operand_k8)
-// The plain reads of 32 rows x 2 chunks touch each bank once per 16 lanes.
-enum { KM = 0, MN = 1 };
-template <int MODE>
-__device__ __forceinline__ bf16x8 frag(const char* tile, int r0, int ks, int lane) {
-  const int r32 = lane & 31, g = lane >> 5;
-  if (MODE == KM) return lds_read_b128(tile, swzt(r0 + r32, 2 * ks + g));
-  return tr_operand_k8(tile, ks, r0, lane);
-}
-
-// One stage of LDS (64 KB) per workgroup, so that two workgroups share a CU:
-// the copies of one overlap the products of the other.  Measured on the
-// Llama layer share against a double-buffered single workgroup per CU: the
-// projection products 14.4 -> 10.9 ms, the weight gradients 5.7 -> 3.0 ms per
-// step (one stage in flight per workgroup left the copy latency exposed).
-template <int EPI>
-struct GemmStages {
-  static constexpr int N = 1;
+  // Per-lane base of the fragment reads of this wave's rows (m or n), from w0 on.
+  static __device__ __forceinline__ uint32_t base(int w0, int lane) {
+    const int r32 = lane & 31, g = lane >> 5, t = lane & 15, hi = (lane >> 4) & 1;
+    if (KMAJOR)
+      return w0 * 128 + (r32 >> 1) * 256 + ((((r32 & 1) << 3) | (g ^ ((r32 >> 1) & 7))) << 4);
+    const uint32_t at = swzt(8 * g + (t >> 2), 2 * hi + ((t & 3) >> 1)) + ((t & 1) << 3);
+    return (at ^ ((w0 & 127) * 2)) + (w0 >> 7) * (BK * 256);
+  }
+  // Fragment of the 32 rows r0.. (of the wave's; bits of r0 and w0 are apart) at
+  // k-step ks (16 k): lane l gets row r0 + l % 32 at k = 16 ks + 8g + 0..7, g = l / 32.  MN-major: two
+  // ds_read_b64_tr_b16 per lane; within each 16-lane group, loader lane t reads
+  // the 8 bytes at line 16 ks + 8g + t/4 (+ 4 for the second read), columns r0 + 16
+  // ((l >> 4) & 1) + 4 (t % 4); with the swzt swizzle the 8 lines x 4 chunks of one
+  // read fill every bank exactly twice.
+  static __device__ __forceinline__ bf16x8 frag(const char* smem, uint32_t at, int r0, int ks) {
+    if (KMAJOR) return lds_read_b128(smem, (at ^ (32 * ks)) + r0 * 128);
+    typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
+    const uint32_t x = r0 * 2, k = ks * 4096;
+    const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(smem + (at ^ x) + k));
+    const bf16x4 up =
+        __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(smem + (at ^ (x + 16)) + k + 1024));
+    bf16x8 v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      v[e] = lo[e];
+      v[4 + e] = up[e];
+    }
+    return v;
+  }
 };
 
-template <bool A_K, bool B_K, int EPI>
-__global__ __launch_bounds__(256, 3 - GemmStages<EPI>::N) void gemm_kernel(
+// BM x BN = 256 x 256: eight waves of 128 x 64, one workgroup per CU; 128 x 128: four of
+// 64 x 64, two workgroups per CU.  Two stages in LDS.
+template <int BM, int BN>
+struct Shape {
+  static constexpr int WN = BN / 64, MT = BM / 64;
+  static constexpr int WM = BM / (32 * MT), W = WM * WN;        // waves
+  static constexpr int STAGE = (BM + BN) * BK * 2;
+};
+
+template <bool A_K, bool B_K, int EPI, int BM, int BN>
+__global__ __launch_bounds__((64 * Shape<BM, BN>::W), 2) void gemm_kernel(
     GemmOperand A, GemmOperand B, GemmEpilogue E, int64_t M, int64_t N, int64_t k_begin,
     int64_t k_len) {
-  constexpr int AM = A_K ? KM : MN;
-  constexpr int BMODE = B_K ? KM : MN;
-  constexpr int NST = GemmStages<EPI>::N;
-  __shared__ __attribute__((aligned(1024))) char smem[NST * 2 * TILE_BYTES];
+  using H = Shape<BM, BN>;
+  using TA = Tile<A_K, BM, H::W>;
+  using TB = Tile<B_K, BN, H::W>;
+  constexpr int MT = H::MT;
+  __shared__ __attribute__((aligned(1024))) char smem[2 * H::STAGE];
+  typedef __attribute__((address_space(3))) char lds_char;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char*)smem;
   const int t = threadIdx.x;
   const int lane = t & 63;
   const int w = __builtin_amdgcn_readfirstlane(t >> 6);
   const int r32 = lane & 31, g = lane >> 5;
-  const int wm = w >> 1, wn = w & 1;
-  const int64_t tiles_n = N / BN;
-  // Workgroups are dispatched round-robin over the 8 XCDs, each with its own
-  // L2; which tile a workgroup computes is a permutation chosen per product
-  // (the results do not depend on it):
-  //   HEADS   (long k, a few weight columns): every XCD takes a contiguous
-  //           run of tiles, m-major, so the activation rows are fetched once;
-  //   PARTIAL (split-K weight gradients): every XCD takes whole splits, and
-  //           walks a split along its shorter side first (the tiles that
-  //           share the wider operand's block run together);
-  //   ACC32   (short k, many weight columns): round-robin, so each XCD keeps
-  //           an eighth of the weight columns in its L2.
-  int64_t tile = blockIdx.x, split = blockIdx.y;
-  if (EPI != GEMM_EPI_ACC32) {
-    const int64_t nx = gridDim.x;
-    const int64_t d = (int64_t)blockIdx.y * nx + blockIdx.x;   // dispatch order
-    const int64_t nwg = nx * gridDim.y, xcd = d % 8, slot = d / 8;
-    const int64_t per = nwg / 8, rem = nwg % 8;
-    const int64_t L = xcd < rem ? xcd * (per + 1) + slot : rem * (per + 1) + (xcd - rem) * per + slot;
+  const int wm = w / H::WN, wn = w % H::WN;
+  const int rowA = 32 * MT * wm;                                // of this wave in the tile
+  const int colB = 128 * (wn >> 1) + 32 * (wn & 1);             // + 64 nt
+  const int64_t tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
+  // Workgroups go round-robin to the 8 XCDs, each with its own L2: every XCD
+  // takes a contiguous run of (split, tile), the tiles of a split in bands of
+  // eight along m, so that the ones running together share operand rows.
+  int64_t tile, split;
+  {
+    const int64_t nx = gridDim.x, d = (int64_t)blockIdx.y * nx + blockIdx.x;
+    const int64_t nwg = nx * gridDim.y, xcd = d % 8, per = nwg / 8, rem = nwg % 8;
+    const int64_t L = xcd * per + (xcd < rem ? xcd : rem) + d / 8;
     tile = L % nx;
     split = L / nx;
-    const int64_t tiles_m = M / BM;
-    if (EPI == GEMM_EPI_PARTIAL && tiles_m < tiles_n)   // m fastest
-      tile = (tile % tiles_m) * tiles_n + tile / tiles_m;
   }
-  const int64_t m0 = (tile / tiles_n) * BM, n0 = (tile % tiles_n) * BN;
+  const int64_t band = tile / (8 * tiles_n), in = tile % (8 * tiles_n);
+  const int64_t bh = tiles_m - 8 * band < 8 ? tiles_m - 8 * band : 8;
+  const int64_t m0 = (8 * band + in % bh) * BM, n0 = (in / bh) * BN;
   const int64_t kb0 = k_begin + split * k_len;
   int64_t kend = kb0 + k_len;
   if (kend > k_begin + E.k_total) kend = k_begin + E.k_total;
-  const int nk = kend > kb0 ? (int)((kend - kb0 + BKG - 1) / BKG) : 0;
+  const int nk = kend > kb0 ? (int)((kend - kb0 + BK - 1) / BK) : 0;
 
-  f32x16 acc[2][2];
-  if (EPI == GEMM_EPI_ACC32 && !E.first) {
+  f32x16 acc[MT][2];
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
+  for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-      for (int nt = 0; nt < 2; ++nt) {
-        const int64_t n = n0 + 32 * wn + 64 * nt + r32;
+    for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int64_t m = m0 + 64 * wm + 32 * mt + 8 * (i >> 2) + 4 * g + (i & 3);
-          acc[mt][nt][i] = m < E.m_store ? E.c32[m * E.ldc + n] : 0.f;
-        }
-      }
-  } else {
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-      for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[mt][nt][i] = 0.f;
-  }
+      for (int i = 0; i < 16; ++i) acc[mt][nt][i] = 0.f;
 
-  uint32_t offa[8], offb[8];
-  lane_offsets(A.ld, w, lane, offa);
-  lane_offsets(B.ld, w, lane, offb);
+  TA ta;
+  TB tb;
+  ta.init(A.ld, w, lane);
+  tb.init(B.ld, w, lane);
   auto issue = [&](int kk) {
-    const int64_t k0 = kb0 + (int64_t)kk * BKG;
-    char* buf = smem + (kk % NST) * 2 * TILE_BYTES;
-    issue_tile(tile_rsrc(A, A_K, m0, k0), offa, buf, w);
-    issue_tile(tile_rsrc(B, B_K, n0, k0), offb, buf + TILE_BYTES, w);
+    const int64_t k0 = kb0 + (int64_t)kk * BK;
+    const uint32_t at = lds0 + (kk & 1) * H::STAGE;
+    ta.issue(A, m0, k0, at, w);
+    tb.issue(B, n0, k0, at + TA::BYTES, w);
   };
+  const uint32_t a_lane = TA::base(rowA, lane);
+  const uint32_t b_lane = TA::BYTES + TB::base(colB, lane);
   if (nk > 0) issue(0);
   for (int kk = 0; kk < nk; ++kk) {
-    const char* bufA = smem + (kk % NST) * 2 * TILE_BYTES;
-    const char* bufB = bufA + TILE_BYTES;
-    if (NST == 1 && kk > 0) {
-      __syncthreads();   // every wave is done with stage kk-1
-      issue(kk);
-    }
-    wait_vmem();
-    __syncthreads();   // stage kk landed for all waves; stage kk-1's buffer is free
-    if (NST == 2 && kk + 1 < nk) issue(kk + 1);
+    // This wave's copies of stage kk have landed, its reads of stage kk - 1 are
+    // done; past the barrier every wave's.
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    if (kk + 1 < nk) issue(kk + 1);
+    const uint32_t aa = a_lane + (kk & 1) * H::STAGE, ba = b_lane + (kk & 1) * H::STAGE;
 #pragma unroll
-    for (int ks = 0; ks < BKG / 16; ++ks) {
-      bf16x8 af[2], bfr[2];
+    for (int ks = 0; ks < BK / 16; ++ks) {
+      bf16x8 af[MT], bfr[2];
 #pragma unroll
-      for (int mt = 0; mt < 2; ++mt) af[mt] = frag<AM>(bufA, 64 * wm + 32 * mt, ks, lane);
+      for (int mt = 0; mt < MT; ++mt) af[mt] = TA::frag(smem, aa, 32 * mt, ks);
 #pragma unroll
-      for (int nt = 0; nt < 2; ++nt) bfr[nt] = frag<BMODE>(bufB, 32 * wn + 64 * nt, ks, lane);
+      for (int nt = 0; nt < 2; ++nt) bfr[nt] = TB::frag(smem, ba, 64 * nt, ks);
 #pragma unroll
-      for (int mt = 0; mt < 2; ++mt)
+      for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
         for (int nt = 0; nt < 2; ++nt) acc[mt][nt] = mfma32x32x16(af[mt], bfr[nt], acc[mt][nt]);
     }
+    // Keep one k-step's fragment reads in flight ahead of the MFMAs (left to
+    // itself the scheduler waits for a step's reads before its first MFMA:
+    // 8192 x 4096 x 4096 230 -> 220 us).
+    constexpr int NR = MT * (A_K ? 1 : 2) + 2 * (B_K ? 1 : 2);   // reads of a k-step
+    constexpr int PER = (NR + 2 * MT - 1) / (2 * MT);             // per MFMA
+    constexpr int NI = (3 * NR + PER - 1) / PER;
+    __builtin_amdgcn_sched_group_barrier(0x100, NR, 0);
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, PER, 0);
+    }
+    __builtin_amdgcn_sched_group_barrier(0x008, 8 * MT - NI, 0);
   }
 
-  // ---- epilogues.  Lane holds column n = n0 + 32wn + 64nt + r32 and rows
-  //      m = m0 + 64wm + 32mt + 8a + 4g + b for element i = 4a + b.
-  const int nb = (int)(n0 / 128);     // output head (HEADS): a tile is 128 columns
+  // ---- epilogues.  Lane holds column n0 + colB + 64 nt + r32 and rows
+  //      m0 + rowA + 32 mt + 8a + 4g + b for element i = 4a + b.
+  const int nb = (int)((n0 + colB) / 128);     // output head (HEADS)
   int grp = 0;
-  if (EPI == GEMM_EPI_HEADS)
+  if (EPI == GEMM_EPI_HEADS) {
+    if (n0 + colB >= N) return;
     while (grp + 1 < E.n_groups && nb >= E.group[grp + 1].first) ++grp;
-  if (EPI == GEMM_EPI_HEADS && E.rope.on && ((E.rope_groups >> grp) & 1)) {
-    // Pair (e, e + 64), e = 32wn + r32, of rows m: acc[mt][0][i], acc[mt][1][i].
-    // The turn of the first row of each 32-row block is reduced in fp64; the
-    // offsets 8a + b (< 28) add at most 28 theta_e / 2 pi turns in fp32.
-    const double f = rope_turns_per_pos(32 * wn + r32, E.rope.log2_base);
-    const float ff = (float)f;
+    if (E.rope.on && ((E.rope_groups >> grp) & 1)) {
+      // Pair (e, e + 64) of rows m: acc[mt][0][i], acc[mt][1][i].  The turn of the
+      // first row of each 32-row block is reduced in fp64; the offsets 8a + b
+      // (< 28) add at most 28 theta_e / 2 pi turns in fp32.
+      const double f = rope_turns_per_pos(32 * (wn & 1) + r32, E.rope.log2_base);
+      const float ff = (float)f;
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt) {
-      const float t0 = rope_turn(E.rope.pos0 + m0 + 64 * wm + 32 * mt + 4 * g, f);
+      for (int mt = 0; mt < MT; ++mt) {
+        const float t0 = rope_turn(E.rope.pos0 + m0 + rowA + 32 * mt + 4 * g, f);
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        float c, s;
-        cos_sin_turns(fmaf((float)(8 * (i >> 2) + (i & 3)), ff, t0), c, s);
-        rope_pair(acc[mt][0], acc[mt][1], i, c, s, false);
+        for (int i = 0; i < 16; ++i) {
+          float c, s;
+          cos_sin_turns(fmaf((float)(8 * (i >> 2) + (i & 3)), ff, t0), c, s);
+          rope_pair(acc[mt][0], acc[mt][1], i, c, s, false);
+        }
       }
     }
   }
 #pragma unroll
-  for (int mt = 0; mt < 2; ++mt)
+  for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
     for (int nt = 0; nt < 2; ++nt) {
-      const int64_t n = n0 + 32 * wn + 64 * nt + r32;
-      const int64_t mb = m0 + 64 * wm + 32 * mt;
+      const int64_t n = n0 + colB + 64 * nt + r32;
+      const int64_t mb = m0 + rowA + 32 * mt + 4 * g;
+      if (EPI != GEMM_EPI_HEADS && n >= N) continue;
       if (EPI == GEMM_EPI_HEADS) {
         const GemmEpilogue::Group& G = E.group[grp];
         bf16* dn = G.p + (nb - G.first) * G.head + n % 128;
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-          const int64_t m = mb + 8 * (i >> 2) + 4 * g + (i & 3);
+          const int64_t m = mb + 8 * (i >> 2) + (i & 3);
           if (m < E.m_store) dn[m * G.row] = (bf16)acc[mt][nt][i];
         }
-      } else if (EPI == GEMM_EPI_ACC32) {
+      } else if (EPI == GEMM_EPI_STORE) {
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-          const int64_t m = mb + 8 * (i >> 2) + 4 * g + (i & 3);
-          if (m < E.m_store) {
-            if (E.last) E.out[m * E.ldo + n] = (bf16)acc[mt][nt][i];
-            else E.c32[m * E.ldc + n] = acc[mt][nt][i];
-          }
+          const int64_t m = mb + 8 * (i >> 2) + (i & 3);
+          if (m < E.m_store) E.out[m * E.ldo + n] = (bf16)acc[mt][nt][i];
         }
       } else {  // GEMM_EPI_PARTIAL
         float* P = E.partial + split * M * N;
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-          const int64_t m = mb + 8 * (i >> 2) + 4 * g + (i & 3);
-          P[m * N + n] = acc[mt][nt][i];
+          const int64_t m = mb + 8 * (i >> 2) + (i & 3);
+          if (m < M) P[m * N + n] = acc[mt][nt][i];
         }
       }
     }
@@ -302,12 +314,12 @@ __global__ __launch_bounds__(256) void reduce_splitk_kernel(const float* __restr
   }
 }
 
-template <bool A_K, bool B_K, int EPI>
+template <bool A_K, bool B_K, int EPI, int BM, int BN>
 hipError_t launch_t(const GemmOperand& A, const GemmOperand& B, const GemmEpilogue& E, int64_t M,
                     int64_t N, int64_t k_begin, int64_t k_len, int splits, hipStream_t st) {
-  dim3 grid((unsigned)((M / BM) * (N / BN)), (unsigned)splits);
-  hipLaunchKernelGGL((gemm_kernel<A_K, B_K, EPI>), grid, dim3(256), 0, st, A, B, E, M, N,
-                     k_begin, k_len);
+  dim3 grid((unsigned)(((M + BM - 1) / BM) * ((N + BN - 1) / BN)), (unsigned)splits);
+  hipLaunchKernelGGL((gemm_kernel<A_K, B_K, EPI, BM, BN>), grid, dim3(64 * Shape<BM, BN>::W), 0, st,
+                     A, B, E, M, N, k_begin, k_len);
   return hipGetLastError();
 }
 
@@ -316,19 +328,27 @@ hipError_t launch_t(const GemmOperand& A, const GemmOperand& B, const GemmEpilog
 hipError_t launch_gemm(const GemmOperand& A, bool a_kmajor, const GemmOperand& B, bool b_kmajor,
                        const GemmEpilogue& E, int epi, int64_t M, int64_t N, int64_t k_begin,
                        int64_t k_len, int splits, hipStream_t st) {
-  // A K-major tile reads 128 consecutive k of each row: the k range must be
+  // A K-major tile reads 64 consecutive k of each row: the k range must be
   // made of whole tiles (an MN-major operand is bounded by its buffer
   // resource instead); pieces must start on tile boundaries.
-  if ((M % BM) || (N % BN) || (k_len % BKG) || (k_begin % BKG)) return hipErrorInvalidValue;
-  if ((a_kmajor || b_kmajor) && (E.k_total % BKG)) return hipErrorInvalidValue;
-#define UPIPE_GEMM_CASE(AK, BK_, EP)                                               \
-  if (a_kmajor == AK && b_kmajor == BK_ && epi == EP)                              \
-    return launch_t<AK, BK_, EP>(A, B, E, M, N, k_begin, k_len, splits, st);
-  UPIPE_GEMM_CASE(true, false, GEMM_EPI_HEADS)     // X . W slice
-  UPIPE_GEMM_CASE(true, false, GEMM_EPI_ACC32)     // O_c . Wo_c
-  UPIPE_GEMM_CASE(true, true, GEMM_EPI_HEADS)      // dY . Wo_c^T
-  UPIPE_GEMM_CASE(true, true, GEMM_EPI_ACC32)      // dQ_c . Wq_c^T, dK . Wk^T
-  UPIPE_GEMM_CASE(false, false, GEMM_EPI_PARTIAL)  // X^T . dQ_c, O^T . dY
+  if ((M % 128) || (N % 128) || (k_len % 128) || (k_begin % 128)) return hipErrorInvalidValue;
+  if ((a_kmajor || b_kmajor) && (E.k_total % 128)) return hipErrorInvalidValue;
+  // Rounds on 256 CUs: a 256 x 256 tile takes 0.8 of four 128 x 128 ones, two of
+  // which run side by side (us, 128 | 256: 8192 x 4096 x 4096 271 | 220; 65536 x 1280 x
+  // 5120 858 | 748; 16384 x 640 x 512 22.1 | 22.8; 8192 x 768 x 4096, 96 large tiles,
+  // 54 | 90; 3072 x 2048 x 1024 20 | 31).  No result depends on it.
+  const int64_t big = ((M + 255) / 256) * ((N + 255) / 256) * splits;
+  const int64_t small = (M / 128) * (N / 128) * splits;
+  const bool large = 1.6 * ((big + 255) / 256) < (small + 511) / 512;
+#define UPIPE_GEMM_CASE(AK, BK_, EP)                                                            \
+  if (a_kmajor == AK && b_kmajor == BK_ && epi == EP)                                           \
+    return large ? launch_t<AK, BK_, EP, 256, 256>(A, B, E, M, N, k_begin, k_len, splits, st)   \
+                 : launch_t<AK, BK_, EP, 128, 128>(A, B, E, M, N, k_begin, k_len, splits, st);
+  UPIPE_GEMM_CASE(true, false, GEMM_EPI_HEADS)     // X . Wqkv
+  UPIPE_GEMM_CASE(true, false, GEMM_EPI_STORE)     // O . Wo
+  UPIPE_GEMM_CASE(true, true, GEMM_EPI_HEADS)      // dY . Wo^T
+  UPIPE_GEMM_CASE(true, true, GEMM_EPI_STORE)      // dQKV . Wqkv^T
+  UPIPE_GEMM_CASE(false, false, GEMM_EPI_PARTIAL)  // X^T . dQKV, O^T . dY
 #undef UPIPE_GEMM_CASE
   return hipErrorInvalidValue;
 }

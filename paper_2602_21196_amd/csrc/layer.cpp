@@ -53,14 +53,24 @@ int check_layer_shape(int64_t S, int d_model, int Hq, int Hkv, int d, int U) {
 }
 
 // Split length of the sequence for the weight gradient of a [M, N] weight: a
-// function of S and the whole weight only (never of U), a multiple of the
-// GEMM k-step.  Two rounds of 128 x 128 tiles on the 256 CUs x 2 workgroups: more
-// pieces cost fp32 partials (4096 x 768, 8192 rows: 32 pieces 116 + 124 us for
-// product and sum, 5 pieces 75 + 18 us), fewer leave CUs idle.
+// function of S and the whole weight only (never of U), a multiple of 256.
+// The pieces that cost least: rounds of 256 x 256 tiles on 256 CUs against tiles,
+// plus the write and read of a piece's fp32 partial, as long as the product
+// over 1200 rows (4096 x 768, 8192 rows: 32 pieces 116 + 124 us for product and
+// sum, 5 pieces 60 + 12).
 int64_t wgrad_split_len(int64_t S, int64_t M, int64_t N) {
-  const int64_t tiles = (M / 128) * (N / 128);
-  const int64_t want = std::min<int64_t>(32, std::max<int64_t>(1, 1024 / tiles));
-  return std::max<int64_t>(256, round_up((S + want - 1) / want, 256));
+  const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256);
+  int64_t best = 1;
+  double best_cost = 0;
+  for (int64_t s = 1; s <= 32; ++s) {
+    const int64_t rounds = (tiles * s + 255) / 256;
+    const double cost = rounds * 256.0 / (tiles * s) + 1200.0 * s / S;
+    if (s == 1 || cost < best_cost) {
+      best = s;
+      best_cost = cost;
+    }
+  }
+  return std::max<int64_t>(256, round_up((S + best - 1) / best, 256));
 }
 
 struct LayerFwdPlan {
@@ -178,14 +188,12 @@ GemmEpilogue qkv_epi(const HeadView& Q, bf16* Kp, bf16* Vp, int Hq, int Hkv, int
   return e;
 }
 
-// bf16 result rows m < m_store into out[m * ldo + n], no fp32 carry.
+// bf16 result rows m < m_store into out[m * ldo + n].
 GemmEpilogue store_epi(bf16* out, int64_t ldo, int64_t m_store) {
   GemmEpilogue e{};
   e.out = out;
   e.ldo = ldo;
   e.m_store = m_store;
-  e.first = 1;
-  e.last = 1;
   return e;
 }
 
@@ -217,7 +225,7 @@ int run_layer_fwd_seq(const bf16* x, const bf16* wqkv, const bf16* wo, bf16* y, 
   // y = final_out Wo.
   UPIPE_LAUNCH(kGemm, st,
                gemm1(operand(o_saved, qw, S, qw), true, operand(wo, dm, dm, qw), false,
-                     store_epi(y, dm, S), GEMM_EPI_ACC32, Sp, dm, qw, st));
+                     store_epi(y, dm, S), GEMM_EPI_STORE, Sp, dm, qw, st));
   return UPIPE_OK;
 }
 
@@ -328,7 +336,7 @@ int run_layer_bwd_seq(const bf16* x, const bf16* wqkv, const bf16* wo, const bf1
   // dx = [dQ | dK | dV] Wqkv^T (head-major A; Wqkv rows are k-contiguous).
   UPIPE_LAUNCH(kGemm, st,
                gemm1(operand(dQKV, HEAD_DIM, S, nqkv, HEAD_DIM, head), true,
-                     operand(wqkv, nqkv, dm, nqkv), true, store_epi(dx, dm, S), GEMM_EPI_ACC32,
+                     operand(wqkv, nqkv, dm, nqkv), true, store_epi(dx, dm, S), GEMM_EPI_STORE,
                      Sp, dm, nqkv, st));
   // dWqkv = x^T [dQ | dK | dV].
   return wgrad(XT, operand(dQKV, HEAD_DIM, nqkv, S, HEAD_DIM, head), dm, nqkv,
@@ -446,7 +454,7 @@ int upipe_gemm_bf16(const void* a, const void* b, void* c, int64_t M, int64_t N,
     // A [M, K] row-major is K-major; B [K, N] row-major is N-major.
     UPIPE_LAUNCH(kGemm, stream,
                  gemm1(operand((const bf16*)a, K, M, K), true, operand((const bf16*)b, N, N, K),
-                       false, store_epi((bf16*)c, N, M), GEMM_EPI_ACC32, M, N, K, stream));
+                       false, store_epi((bf16*)c, N, M), GEMM_EPI_STORE, M, N, K, stream));
     return UPIPE_OK;
   } catch (...) {
     return UPIPE_ERR_HIP;

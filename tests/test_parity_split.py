@@ -7,7 +7,9 @@ and before it; the key ranges are short, so the oracle stays cheap.
 
 Backward: dK/dV cuts the walk over a key block's query tiles into segments,
 with 128 or 64 keys a workgroup, and dQ splits keys like the forward; tensors
-that overlap an output take the path that packs them."""
+that overlap an output take the path that packs them.
+
+Products: 256 x 256 or 128 x 128 tiles by how they fill the chip."""
 
 import numpy as np
 import pytest
@@ -15,6 +17,7 @@ import torch
 
 import workloads as W
 from oracle import attention as A
+from oracle import layer as L
 from oracle import ring as R
 from tol import as64, assert_close
 
@@ -150,3 +153,33 @@ def test_backward_gradient_over_an_input(over):
     torch.cuda.synchronize()
     for name, a, r in zip(("dq", "dk", "dv"), (dq, dk, dv), ref):
         assert_close(name, a.cpu(), r)
+
+
+@pytest.mark.parametrize("M,N,K", [(8320, 4224, 128), (8192, 4096, 384), (16512, 640, 256)])
+def test_product_with_large_tiles(M, N, K):
+    """Half tiles at both edges; against the float64 product (entries grow like
+    sqrt(K): the bar on the rms-scaled error), and bitwise what the first rows
+    alone give, which take the small tiles."""
+    up = _upipe()
+    g = torch.Generator().manual_seed(M + K)
+    a = torch.randn((M, K), generator=g).to(torch.bfloat16)
+    b = torch.randn((K, N), generator=g).to(torch.bfloat16)
+    c = up.gemm(a.to(DEV), b.to(DEV))
+    few = up.gemm(a[:640].to(DEV), b.to(DEV))
+    torch.cuda.synchronize()
+    assert torch.equal(_bits(c[:640]), _bits(few))
+    assert_close("c", c.cpu(), as64(a) @ as64(b), rms_scaled=True)
+
+
+def test_block_projection_with_large_tiles():
+    """16300 rows of 3 + 2 heads: a ragged M and half a tile along N.  The block is
+    causal, so its first rows are those of the sequence's beginning (oracle)."""
+    up = _upipe()
+    S, dm, Hq, Hkv, n = 16300, 256, 3, 1, 700
+    x, wqkv, wo, _ = W.layer_inputs(S, dm, Hq, Hkv, 128, 21, w_std=0.06)
+    y, o, lse = up.layer_fwd(x.to(DEV), wqkv.to(DEV), wo.to(DEV), Hq, Hkv, U=1, rope_base=1e4)
+    torch.cuda.synchronize()
+    y_r, o_r, lse_r = L.layer_fwd(as64(x[:n]), as64(wqkv), as64(wo), Hq, Hkv, 128, rope_base=1e4)
+    assert_close("y", y[:n].cpu(), y_r)
+    assert_close("o", o[:n].cpu(), o_r)
+    assert_close("lse", lse[:, :n].cpu(), lse_r)

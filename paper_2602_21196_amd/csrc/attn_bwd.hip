@@ -54,35 +54,44 @@ constexpr int KV_STAGE = 2 * ROWT + QT * 8;
 constexpr int KV_BLK = ROWT / 1024 / 4;     // 1 KB blocks per wave per array
 
 struct QStageSrc {
-  buf_rsrc q, dO, lse, D;
-  uint32_t q_rowb, do_rowb;   // bytes from one row to the next
+  i32x4 q, dO, lse, D;
+  uint32_t rowb;              // bytes from one row of Q or dO to the next
 };
 
-// This wave's share of one tile's copies: KV_BLK blocks of 1 KB each of Q and
-// dO rows; lanes of wave 0 copy the QT lse values, lanes of wave 1 the QT D
-// values (16 bytes per lane).
-__device__ __forceinline__ void issue_qstage(const QStageSrc& r, uint32_t qb, char* buf, int w,
-                                             int lane) {
-  // The source offsets are recomputed for every tile (a few VALU
-  // instructions) instead of being held in registers across the tile loop,
-  // where the register file is full; the empty asm keeps the compiler from
-  // hoisting them back out of the loop.
-  asm volatile("" : "+v"(lane));
+// The copies of one tile by one wave: KV_BLK blocks of 1 KB each of Q and dO rows,
+// the QT lse values by wave 0 and the QT D values by wave 1 (16 bytes a lane).
+// A CU takes about 20 clocks per 1 KB copy, and a wave that issues more than it
+// takes stands still, products and all: issued together at the top of a tile,
+// the copies of the next one held every wave for 1320 of the tile's 8100 clocks.
+// So they go out in pair_step, in its two regions that are all products.  Against
+// the top of the tile that is, for dK/dV of 4 heads over 1: 202 -> 188 us at
+// S = 8192, 2029 -> 1955 us at 32768, 3 to 6 % at 65536.  Spread over
+// all four regions, or all in one, they gain about half of it.
+struct TileCopy {
+  QStageSrc r;
+  uint32_t row0;    // first query row of the tile
+  uint32_t lds;     // LDS address of the stage
+  int w;
+  uint32_t vb;      // this lane's 16 bytes in the wave's first block: a row (16 lanes each),
+                    // its chunk swizzled for the transposing reads
+
+  // Blocks i0 .. i0 + n - 1 of this wave's (both even).
+  __device__ __forceinline__ void blocks(int i0, int n) const {
 #pragma unroll
-  for (int i = 0; i < KV_BLK; ++i) {
-    const int blk = KV_BLK * w + i;
-    // this lane's 16 bytes: Q / dO row `row` of the tile (16 lanes per row),
-    // chunk swizzled for the transposing reads
-    const int row = 4 * blk + (lane >> 4);
-    const uint32_t c = ((lane & 15) ^ tsw(row)) << 4;
-    dma_buf_b128(r.q, row * r.q_rowb + c, qb * r.q_rowb, buf + OFF_Q + blk * 1024);
-    dma_buf_b128(r.dO, row * r.do_rowb + c, qb * r.do_rowb, buf + OFF_DO + blk * 1024);
+    for (int i = i0; i < i0 + n; i += 2) {
+      const uint32_t off = (vb ^ ((i & 3) << 4)) + 4 * i * r.rowb;
+      const uint32_t off1 = (vb ^ (((i + 1) & 3) << 4)) + 4 * (i + 1) * r.rowb;
+      copy2x2_b128<OFF_DO - OFF_Q>(r.q, r.dO, off, off1, row0 * r.rowb,
+                                   lds + OFF_Q + (KV_BLK * w + i) * 1024);
+    }
   }
-  if (lane < QT / 4) {
-    if (w == 0) dma_buf_b128(r.lse, lane * 16u, qb * 4u, buf + OFF_LSE);
-    else if (w == 1) dma_buf_b128(r.D, lane * 16u, qb * 4u, buf + OFF_D);
+  __device__ __forceinline__ void rows(int lane) const {
+    if (lane < QT / 4) {
+      if (w == 0) copy_b128(r.lse, lane * 16u, row0 * 4u, lds + OFF_LSE);
+      else if (w == 1) copy_b128(r.D, lane * 16u, row0 * 4u, lds + OFF_D);
+    }
   }
-}
+};
 
 // Operand fragments of one block of 16 MFMAs.
 struct Frags {
@@ -228,12 +237,14 @@ __device__ __forceinline__ void interleave_mfma_valu() {
 // The LDS fragments of each block are read one region ahead; fa holds the
 // upper subtile's S / dP fragments on entry, and with PF it is refilled
 // during region D (which has no other LDS reads) with those of the next
-// pair of the tile.  The lower subtile is computed even where only the upper
-// one is needed: the diagonal mask then zeroes all of its P and dS.
-template <bool CAUSAL, bool PF>
-__device__ __forceinline__ void pair_step(const char* buf, int base, uint32_t qb, uint32_t kw,
-                                          uint32_t mykey, int r32, int g, int lane,
-                                          const bf16x8 (&kf)[8], const bf16x8 (&vf)[8],
+// pair of the tile.  Regions A and D each begin with 2 NB blocks of the next
+// tile's copies, from `blk` on.  The lower subtile is computed even where only
+// the upper one is needed: the diagonal mask then zeroes all of its P and dS.
+template <bool CAUSAL, bool PF, int NB>
+__device__ __forceinline__ void pair_step(const TileCopy& next, int blk, const char* buf,
+                                          int base, uint32_t qb, uint32_t kw, uint32_t mykey,
+                                          int r32, int g, int lane, const bf16x8 (&kf)[8],
+                                          const bf16x8 (&vf)[8],
                                           f32x16 (&dva)[4], f32x16 (&dka)[4], Frags& fa) {
   Frags fb;
   f32x16 s1, p1, s0, p0;
@@ -244,6 +255,7 @@ __device__ __forceinline__ void pair_step(const char* buf, int base, uint32_t qb
   __builtin_amdgcn_sched_barrier(0);
   read_sdp(buf, base, r32, g, fb);
   __builtin_amdgcn_sched_barrier(0);
+  next.blocks(blk, 2 * NB);
   subtile_sdp(fa, kf, vf, s1, p1);                                            // A
   read_dvdk(buf, base + 32, lane, fa);
   interleave_mfma_lds<2>();
@@ -259,6 +271,7 @@ __device__ __forceinline__ void pair_step(const char* buf, int base, uint32_t qb
   interleave_mfma_valu();
   __builtin_amdgcn_sched_barrier(0);
   subtile_mask<CAUSAL>(q0, mykey, q0 < kw + 31, g, pf0, sf0);
+  next.blocks(blk + 2 * NB, 2 * NB);
   dvdk_products(fb, pf0, sf0, dva, dka);                                      // D
   if (PF) {   // the next pair's upper subtile
     read_sdp(buf, base - 32, r32, g, fa);
@@ -367,17 +380,19 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkdv_kernel(
   auto srcs = [&](int hh) {
     QStageSrc r;
     const int64_t u = hh - h0;
-    r.q_rowb = (uint32_t)(Q.row * 2);
-    r.do_rowb = (uint32_t)(dO.row * 2);
-    r.q = make_rsrc(Q.p + u * Q.head, (uint32_t)(S - 1) * r.q_rowb + 256u);
-    r.dO = make_rsrc(dO.p + u * dO.head, (uint32_t)(S - 1) * r.do_rowb + 256u);
-    r.lse = make_rsrc(lse_c + u * Sp, Spv * 4u);
-    r.D = make_rsrc(Dc + u * Sp, Spv * 4u);
+    r.rowb = (uint32_t)(Q.row * 2);
+    r.q = rsrc_words(Q.p + u * Q.head, (uint32_t)(S - 1) * r.rowb + 256u);
+    r.dO = rsrc_words(dO.p + u * dO.head, (uint32_t)(S - 1) * r.rowb + 256u);
+    r.lse = rsrc_words(lse_c + u * Sp, Spv * 4u);
+    r.D = rsrc_words(Dc + u * Sp, Spv * 4u);
     return r;
   };
 
-  QStageSrc cur = srcs(hh);
-  issue_qstage(cur, qt * QT, smem, w, lane);
+  const uint32_t lds0 = lds_address(smem);
+  TileCopy next{srcs(hh), (uint32_t)(qt * QT), lds0, w, 0};
+  next.vb = (4 * KV_BLK * w + (lane >> 4)) * next.r.rowb + (((lane & 15) ^ ((lane >> 4) << 2)) << 4);
+  next.rows(lane);
+  next.blocks(0, KV_BLK);
 
   // K and -V B-operand fragments (lane = key column, k = head dim); -V makes
   // the dP products count down from D.  Keys past S repeat the last one; their
@@ -442,31 +457,30 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkdv_kernel(
     }
     wait_vmem();
     __syncthreads();   // this tile landed for all waves; the other buffer is free
-    if (it + 1 < total) {
-      if (nh != hh) cur = srcs(nh);
-      issue_qstage(cur, nq * QT, smem + ((it + 1) & 1) * KV_STAGE, w, lane);
-    }
+    // After the last tile the copies read nothing (a source of no bytes, from
+    // offset 0 on, gives zeros), so that no region has to ask.
+    if (nh != hh) next.r = srcs(nh);
+    if (it + 1 == total)
+      next.r.q[2] = next.r.dO[2] = next.r.lse[2] = next.r.D[2] = 0;
+    next.row0 = it + 1 < total ? nq * QT : 0;
+    next.lds = lds0 + ((it + 1) & 1) * KV_STAGE;
+    next.rows(lane);
+    // Pairs of 32-row subtiles, upper rows first; the upper pair reads the lower
+    // pair's first fragments in its region D.  A pair above the diagonal is
+    // computed too, and masked whole: the waves it concerns would wait for
+    // the others, and a branch round it costs the kernel its registers.
     Frags fa;
     if (QS == 1) {
-      // Pairs of 32-row subtiles, upper rows first; a pair is needed when its
-      // last row reaches this wave's first key.  The upper pair reads the
-      // lower pair's first fragments in its region D.
-      const bool run1 = !CAUSAL || qb + 127 >= kw;
-      const bool run0 = !CAUSAL || qb + 63 >= kw;
-      if (run1) {
-        read_sdp(buf, 96, r32, g, fa);
-        pair_step<CAUSAL, true>(buf, 64, qb, kw, mykey, r32, g, lane, kf, vf, dva, dka, fa);
-      }
-      if (run0) {
-        if (!run1) read_sdp(buf, 32, r32, g, fa);
-        pair_step<CAUSAL, false>(buf, 0, qb, kw, mykey, r32, g, lane, kf, vf, dva, dka, fa);
-      }
+      read_sdp(buf, 96, r32, g, fa);
+      pair_step<CAUSAL, true, 1>(next, 0, buf, 64, qb, kw, mykey, r32, g, lane, kf, vf, dva, dka,
+                                 fa);
+      pair_step<CAUSAL, false, 1>(next, 4, buf, 0, qb, kw, mykey, r32, g, lane, kf, vf, dva, dka,
+                                  fa);
     } else {
       const int base = 64 * qs;
-      if (!CAUSAL || qb + base + 63 >= kw) {
-        read_sdp(buf, base + 32, r32, g, fa);
-        pair_step<CAUSAL, false>(buf, base, qb, kw, mykey, r32, g, lane, kf, vf, dva, dka, fa);
-      }
+      read_sdp(buf, base + 32, r32, g, fa);
+      pair_step<CAUSAL, false, 2>(next, 0, buf, base, qb, kw, mykey, r32, g, lane, kf, vf, dva, dka,
+                                  fa);
     }
     qt = nq;
     hh = nh;
@@ -474,7 +488,8 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkdv_kernel(
 
   if (QS > 1) {   // rows 64.. of the tiles onto rows 0..63, in fp32
     float* fold = reinterpret_cast<float*>(smem) + wk * 8192 + lane * 4;
-    __syncthreads();   // every wave is done reading the last tile
+    wait_vmem();
+    __syncthreads();   // every wave is done reading the last tile, and copying
     if (qs > 0) {
 #pragma unroll
       for (int dt = 0; dt < 4; ++dt)
@@ -799,6 +814,7 @@ hipError_t launch_attn_bwd_dkdv(const HeadView& Q, const HeadView& dO, const flo
                                 const float* D, const HeadView& K, const HeadView& V, float* dK32,
                                 float* dV32, const HeadView& dk, const HeadView& dv, int64_t S,
                                 int64_t Sp, int nh, int h0, int G, int causal, hipStream_t st) {
+  if (Q.row != dO.row) return hipErrorInvalidValue;
   const int kv_lo = h0 / G, kv_hi = (h0 + nh - 1) / G;
   dim3 grid((unsigned)(Sp / 128), (unsigned)(kv_hi - kv_lo + 1));
 #define UPIPE_DKDV(C)                                                                          \
@@ -888,7 +904,7 @@ hipError_t launch_attn_bwd_dkdv_split(const HeadView& Q, const HeadView& dO, con
                                       const HeadView& dk, const HeadView& dv, int64_t S, int64_t Sp,
                                       int Hkv, int G, int causal, const DkdvSplit& p, char* region0,
                                       size_t bytes0, char* region1, hipStream_t st) {
-  if (p.T < 1) return hipErrorInvalidValue;
+  if (p.T < 1 || Q.row != dO.row) return hipErrorInvalidValue;
   const int nqt = (int)(Sp / QT);
   const size_t slot = (size_t)2 * (128 / p.qs) * HEAD_DIM * 4;
   DkdvSlots s;

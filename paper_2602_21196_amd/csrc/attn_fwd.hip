@@ -49,18 +49,6 @@ constexpr int V_TILE = HEAD_DIM * BKS * 2;       // [128][128] bf16 = 32 KB
 constexpr int STAGE = K_TILE + V_TILE;
 constexpr float kSumMax = 256.f;   // lazy-rescale bound on a lane's stage sum (2^8)
 
-// This wave's share of the copies of the 128-key stage at byte offset `soff`:
-// 4 blocks of 1 KB of K rows and 4 of V rows (4 rows of 256 B each, V in the
-// swizzle of transposing reads).  The lane offsets inside a stage are fixed;
-// the stage offset is uniform.
-__device__ __forceinline__ void issue_tile(buf_rsrc rk, buf_rsrc rv, const uint32_t (&offk)[4],
-                                           const uint32_t (&offv)[4], uint32_t soff, char* buf, int w) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i) dma_buf_b128(rk, offk[i], soff, buf + (4 * w + i) * 1024);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) dma_buf_b128(rv, offv[i], soff, buf + K_TILE + (4 * w + i) * 1024);
-}
-
 template <int NT>
 __device__ __forceinline__ float tile_probs(const f32x16 (&st)[NT], bf16x8 (&pf)[NT][2],
                                             float m_ref, float sl2) {
@@ -114,8 +102,8 @@ __global__ __launch_bounds__(512, 1) void attn_fwd_kernel(
   // One head's K and V rows, 32-bit addressed; rows past Skv read as zero.
   const uint32_t rowb = (uint32_t)(K.row * 2);
   const uint32_t kv_bytes = (uint32_t)(Skv - 1) * rowb + 256u;
-  const buf_rsrc rk = make_rsrc(K.p + bi * K.batch + kvh * K.head, kv_bytes);
-  const buf_rsrc rv = make_rsrc(V.p + bi * V.batch + kvh * V.head, kv_bytes);
+  const i32x4 rk = rsrc_words(K.p + bi * K.batch + kvh * K.head, kv_bytes);
+  const i32x4 rv = rsrc_words(V.p + bi * V.batch + kvh * V.head, kv_bytes);
   uint32_t offk[4], offv[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
@@ -137,7 +125,11 @@ __global__ __launch_bounds__(512, 1) void attn_fwd_kernel(
   // Last visible key of this lane's row and of the wave's first row.
   const int lim = CAUSAL ? min(myq + delta, Skv - 1) : Skv - 1;
   const int lim_w = CAUSAL ? min(qw + delta, Skv - 1) : Skv - 1;
-  if (nst > 0) issue_tile(rk, rv, offk, offv, 0, smem, w);
+  const uint32_t lds0 = lds_address(smem);
+  if (nst > 0) {
+    copy4_b128(rk, offk, 0, lds0 + 4096 * w);
+    copy4_b128(rv, offv, 0, lds0 + K_TILE + 4096 * w);
+  }
 
   // Q^T B-operand fragments for the whole key loop: lane = query column,
   // k-group g covers head-dim [16s + 8g, 16s + 8g + 8).
@@ -168,10 +160,15 @@ __global__ __launch_bounds__(512, 1) void attn_fwd_kernel(
     char* buf = smem + (j & 1) * STAGE;
     wait_vmem();
     __syncthreads();   // stage j landed for all waves; stage j-1's buffer is free
-    if (j + 1 < nst)
-      issue_tile(rk, rv, offk, offv, (uint32_t)(j + 1) * BKS * rowb, smem + ((j + 1) & 1) * STAGE,
-                 w);
-    if (j >= nw) continue;                  // whole stage masked for this wave
+    const uint32_t nsoff = j + 1 < nst ? (uint32_t)(j + 1) * BKS * rowb : 0;
+    const uint32_t nlds = lds0 + ((j + 1) & 1) * STAGE;
+    i32x4 nk = rk, nv = rv;
+    if (j + 1 == nst) nk[2] = nv[2] = 0;
+    if (j >= nw) {                          // whole stage masked for this wave
+      copy4_b128(nk, offk, nsoff, nlds + 4096 * w);
+      copy4_b128(nv, offv, nsoff, nlds + K_TILE + 4096 * w);
+      continue;
+    }
     {
       const int kb = j * BKS + k_part;
       f32x16 st[NT];
@@ -195,6 +192,12 @@ __global__ __launch_bounds__(512, 1) void attn_fwd_kernel(
         __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
       }
       __builtin_amdgcn_sched_group_barrier(0x008, 6, 0);
+      // The next stage's copies follow the two blocks of products they can hide
+      // behind: a wave stands still while the CU takes them, and at the top of
+      // the stage nothing of it is under way.  Against there: one head over 4096
+      // keys 43 -> 39 us, 8 heads over 4096 56 -> 52, 4 over 8192 90 -> 86, long
+      // calls, where other waves fill the gap, within 0.5 %.
+      copy4_b128(nk, offk, nsoff, nlds + 4096 * w);
       // Mask keys past the row's last visible key (wave-uniform test first).
       if (kb + 32 * NT - 1 > lim_w) {
 #pragma unroll
@@ -224,6 +227,7 @@ __global__ __launch_bounds__(512, 1) void attn_fwd_kernel(
           for (int i = 0; i < 16; ++i) oacc[dt][i] *= alpha;
         ls = tile_probs(st, pf, m_ref, sl2);
       }
+      copy4_b128(nv, offv, nsoff, nlds + K_TILE + 4096 * w);
       l_run += ls;
 #pragma unroll
       for (int c = 0; c < 2 * NT; ++c)
@@ -250,7 +254,8 @@ __global__ __launch_bounds__(512, 1) void attn_fwd_kernel(
     // 1.. pass (m_ref, l, acc) through the stage buffers (16 KB per wave).
     float* fold = reinterpret_cast<float*>(smem);
     float* fold_ml = fold + (KS - 1) * NQW * 4096;
-    __syncthreads();   // every wave is done reading the last stage
+    wait_vmem();
+    __syncthreads();   // every wave is done reading the last stage, and copying
     if (ks > 0) {
       const int slot = (ks - 1) * NQW + wq;
 #pragma unroll

@@ -50,13 +50,7 @@ __device__ __forceinline__ void lds_write_b128(char* base, uint32_t off, u32x4 v
   *reinterpret_cast<u32x4*>(base + off) = v;
 }
 
-// Direct global -> LDS copy of 16 bytes per lane (global_load_lds_dwordx4):
-// lane L's bytes land at lds_wave_base + 16 * L, where lds_wave_base must be
-// the same for the whole wave.  Completion is tracked by vmcnt.
 typedef __attribute__((address_space(3))) void lds_void;
-__device__ __forceinline__ void dma_b128(const void* g, char* lds_wave_base) {
-  __builtin_amdgcn_global_load_lds(g, (lds_void*)lds_wave_base, 16, 0, 0);
-}
 
 // Raw buffer resource over `bytes` bytes at `base` (stride 0, gfx9 data
 // format word); loads at offsets past `bytes` return zeros instead of faulting.
@@ -71,6 +65,55 @@ __device__ __forceinline__ buf_rsrc make_rsrc(const void* base, uint32_t bytes) 
 __device__ __forceinline__ void dma_buf_b128(buf_rsrc r, uint32_t voff, uint32_t soff,
                                              char* lds_wave_base) {
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)lds_wave_base, 16, voff, soff, 0, 0);
+}
+
+// The same copy written out, for kernels that issue the copies of a later tile
+// between reads of this one: the compiler cannot tell which LDS bytes a copy
+// writes, and would wait for it before the next transposing read.  The wave
+// waits itself (wait_vmem, then a barrier) before the bytes are read, and no
+// one reads or writes them meanwhile.  A buffer instruction may read an SGPR
+// only five wait states after a vector instruction (a readlane, say, of one
+// that was spilled) wrote it; the compiler does not look into the text, so the
+// wait is in it, once for up to four copies (one by one it cost the 8192^3
+// product 861 against 851 us and the dK/dV walks 3 %).  No register results;
+// `lds` is an LDS address (lds_address).  m0 is its own here: a kernel uses
+// these copies or dma_buf_b128, not both.
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ i32x4 rsrc_words(const void* base, uint32_t bytes) {
+  const uint64_t a = (uint64_t)base;
+  return i32x4{(int)a, (int)((a >> 32) & 0xffff), (int)bytes, 0x00020000};
+}
+__device__ __forceinline__ void copy_b128(i32x4 r, uint32_t voff, uint32_t soff, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+               :: "s"(lds), "v"(voff), "s"(r), "s"(soff));
+}
+// Four copies to consecutive 1 KB blocks.
+__device__ __forceinline__ void copy4_b128(i32x4 r, const uint32_t (&voff)[4], uint32_t soff,
+                                           uint32_t lds) {
+  asm volatile(
+      "s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %5, %6 offen lds\n\t"
+      "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %5, %6 offen lds\n\t"
+      "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tbuffer_load_dwordx4 %3, %5, %6 offen lds\n\t"
+      "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tbuffer_load_dwordx4 %4, %5, %6 offen lds"
+      :: "s"(lds), "v"(voff[0]), "v"(voff[1]), "v"(voff[2]), "v"(voff[3]), "s"(r), "s"(soff)
+      : "scc");
+}
+// Two copies from each of two sources, to consecutive 1 KB blocks at lds and at
+// lds + GAP.
+template <int GAP>
+__device__ __forceinline__ void copy2x2_b128(i32x4 r0, i32x4 r1, uint32_t voff0, uint32_t voff1,
+                                             uint32_t soff, uint32_t lds) {
+  asm volatile(
+      "s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %3, %5 offen lds\n\t"
+      "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, %5 offen lds\n\t"
+      "s_add_u32 m0, m0, %6\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %4, %5 offen lds\n\t"
+      "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %4, %5 offen lds"
+      :: "s"(lds), "v"(voff0), "v"(voff1), "s"(r0), "s"(r1), "s"(soff), "n"(GAP - 1024)
+      : "scc");
+}
+__device__ __forceinline__ uint32_t lds_address(const char* p) {
+  typedef __attribute__((address_space(3))) const char lds_char;
+  return (uint32_t)(uintptr_t)(lds_char*)p;
 }
 
 // Wait until every outstanding global load of this wave has completed.

@@ -33,7 +33,6 @@ namespace upipe {
 namespace {
 
 constexpr int BK = 64;
-typedef int i32x4 __attribute__((ext_vector_type(4)));
 
 // Address of operand element (r, k).
 // The block width is a power of two (128, or the unblocked 2^50), so the
@@ -55,17 +54,7 @@ __device__ __forceinline__ i32x4 tile_rsrc(const GemmOperand& o, int64_t r0, int
   const int64_t valid = KMAJOR ? o.rows_valid - r0 : r0 < o.rows_valid ? o.k_valid - k0 : 0;
   const int64_t n = valid > LINES ? LINES : valid;
   const int64_t bytes = n <= 0 ? 0 : ((n - 1) * o.ld + (KMAJOR ? BK : 128)) * 2;
-  const uint64_t a = (uint64_t)elem_ptr(o, KMAJOR, r0, k0);
-  return i32x4{(int)a, (int)((a >> 32) & 0xffff), (int)bytes, 0x00020000};
-}
-
-// Buffer -> LDS copy of 16 bytes per lane to lds + 16 * lane.  Written out, so
-// that the compiler does not wait for the copies of the next stage before the
-// reads of this one (it cannot tell which LDS bytes a copy writes); the k loop
-// waits for them itself.  It has no register results.
-__device__ __forceinline__ void copy_b128(i32x4 r, uint32_t voff, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-               :: "s"(lds), "v"(voff), "s"(r) : "memory", "m0");
+  return rsrc_words(elem_ptr(o, KMAJOR, r0, k0), (uint32_t)bytes);
 }
 
 // One operand's tile of R (m or n) x 64 k, R = 128 or 256, staged by W waves.
@@ -73,6 +62,7 @@ template <bool KMAJOR, int R, int W>
 struct Tile {
   static constexpr int BYTES = R * BK * 2;
   static constexpr int NBLK = BYTES / 1024 / W;        // 1 KB blocks per wave
+  static_assert(NBLK == 4, "copy4_b128");
   static constexpr int WAVES = W * 128 / R;            // that copy one 128-wide block
   uint32_t voff[NBLK];
 
@@ -94,8 +84,7 @@ struct Tile {
   __device__ __forceinline__ void issue(const GemmOperand& o, int64_t r0, int64_t k0, uint32_t lds,
                                         int w) const {
     const i32x4 r = tile_rsrc<KMAJOR, KMAJOR ? R : BK>(o, KMAJOR ? r0 : r0 + 128 * (w / WAVES), k0);
-#pragma unroll
-    for (int i = 0; i < NBLK; ++i) copy_b128(r, voff[i], lds + (NBLK * w + i) * 1024);
+    copy4_b128(r, voff, 0, lds + NBLK * w * 1024);
   }
   // Per-lane base of the fragment reads of this wave's rows (m or n), from w0 on.
   static __device__ __forceinline__ uint32_t base(int w0, int lane) {
@@ -146,8 +135,7 @@ __global__ __launch_bounds__((64 * Shape<BM, BN>::W), 2) void gemm_kernel(
   using TB = Tile<B_K, BN, H::W>;
   constexpr int MT = H::MT;
   __shared__ __attribute__((aligned(1024))) char smem[2 * H::STAGE];
-  typedef __attribute__((address_space(3))) char lds_char;
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char*)smem;
+  const uint32_t lds0 = lds_address(smem);
   const int t = threadIdx.x;
   const int lane = t & 63;
   const int w = __builtin_amdgcn_readfirstlane(t >> 6);

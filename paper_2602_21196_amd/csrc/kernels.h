@@ -66,7 +66,8 @@ hipError_t launch_lse_merge(bf16* o, float* lse, const bf16* o_p,
 // of dK32/dV32 [Hkv, Sp, d] (read unless the launch holds a group's first
 // head; dK32 carries the unscaled sum with its sign flipped, -sum dS^T Q),
 // written back there, or -- when the launch holds the group's last head --
-// scaled and rounded into dk/dv.  The rows of Q and dO are rows_addressable.
+// scaled and rounded into dk/dv.  The rows of Q and dO are rows_addressable,
+// and as far apart in one as in the other.
 hipError_t launch_attn_bwd_dkdv(const HeadView& Q, const HeadView& dO, const float* lse_c,
                                 const float* D, const HeadView& K, const HeadView& V, float* dK32,
                                 float* dV32, const HeadView& dk, const HeadView& dv, int64_t S,

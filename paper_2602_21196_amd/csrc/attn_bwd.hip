@@ -486,9 +486,9 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkdv_kernel(
     hh = nh;
   }
 
+  wait_vmem();      // the last tile's empty copies (to LDS) have ended
   if (QS > 1) {   // rows 64.. of the tiles onto rows 0..63, in fp32
     float* fold = reinterpret_cast<float*>(smem) + wk * 8192 + lane * 4;
-    wait_vmem();
     __syncthreads();   // every wave is done reading the last tile, and copying
     if (qs > 0) {
 #pragma unroll
@@ -608,22 +608,20 @@ struct DqTile {
   static constexpr int STAGE = 2 * T;
   static constexpr int BLK = T / 1024 / 8;          // 1 KB blocks per wave per tile
 };
-constexpr int DQ_LA = 6;                   // K/V fragment reads kept in flight
+// K/V fragment reads kept in flight (backward, us, with 4 | 6 | 8: 4100 rows of 8 heads
+// 177.6 | 179.3 | 179.7, 8192 of 4 309.2 | 311.5 | 309.8).
+constexpr int DQ_LA = 4;
 
-// This wave's share of one tile's copies: BLK blocks of 1 KB each of K rows
-// (transposing-read swizzle) and V rows (4 rows of 256 B per block), at byte
-// offset `soff` of the head's rows.
+// Two of this wave's BLK 1 KB blocks (4 rows of 256 B each) of K rows and the
+// same of V rows, i even, at byte offset `soff` of the head's rows; `lds` is the
+// stage's LDS address.
 template <int KS>
-__device__ __forceinline__ void issue_kstage(buf_rsrc rk, buf_rsrc rv,
-                                             const uint32_t (&offk)[DqTile<KS>::BLK],
-                                             const uint32_t (&offv)[DqTile<KS>::BLK], uint32_t soff,
-                                             char* buf, int w) {
-#pragma unroll
-  for (int i = 0; i < DqTile<KS>::BLK; ++i) {
-    const int blk = DqTile<KS>::BLK * w + i;
-    dma_buf_b128(rk, offk[i], soff, buf + DqTile<KS>::OFF_K + blk * 1024);
-    dma_buf_b128(rv, offv[i], soff, buf + DqTile<KS>::OFF_V + blk * 1024);
-  }
+__device__ __forceinline__ void issue_kblocks(i32x4 rk, i32x4 rv,
+                                              const uint32_t (&off)[DqTile<KS>::BLK], int i,
+                                              uint32_t soff, uint32_t lds, int w) {
+  using T = DqTile<KS>;
+  copy2x2_b128<T::OFF_V - T::OFF_K>(rk, rv, off[i], off[i + 1], soff,
+                                    lds + T::OFF_K + (T::BLK * w + i) * 1024);
 }
 
 // dQ may be the rows of Q or dO: a workgroup reads its rows before it writes
@@ -655,18 +653,19 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dq_kernel(
 
   // One head's K and V rows, 32-bit addressed; rows past S read as zero.
   const uint32_t rowb = (uint32_t)(K.row * 2);
-  const buf_rsrc rk = make_rsrc(K.p + bi * K.batch + kvh * K.head, (Sv - 1) * rowb + 256u);
-  const buf_rsrc rv = make_rsrc(V.p + bi * V.batch + kvh * V.head, (Sv - 1) * rowb + 256u);
-  uint32_t offk[T::BLK], offv[T::BLK];
+  const i32x4 rk = rsrc_words(K.p + bi * K.batch + kvh * K.head, (Sv - 1) * rowb + 256u);
+  const i32x4 rv = rsrc_words(V.p + bi * V.batch + kvh * V.head, (Sv - 1) * rowb + 256u);
+  const uint32_t lds0 = lds_address(smem);
+  uint32_t off[T::BLK];
 #pragma unroll
   for (int i = 0; i < T::BLK; ++i) {
     const int blk = T::BLK * w + i;
     const int r = 4 * blk + (lane >> 4);      // row of the tile, 16 lanes per row
-    offk[i] = r * rowb + (((lane & 15) ^ tsw(r)) << 4);
-    offv[i] = r * rowb + (((lane & 15) ^ (r & 15)) << 4);
+    off[i] = r * rowb + (((lane & 15) ^ tsw(r)) << 4);
   }
   const int nst = (int)(((CAUSAL ? min(q0 + T::BQ, Sv) : Sv) + T::BK - 1) / T::BK);
-  issue_kstage<KS>(rk, rv, offk, offv, 0, smem, w);
+#pragma unroll
+  for (int i = 0; i < T::BLK; i += 2) issue_kblocks<KS>(rk, rv, off, i, 0, lds0, w);
 
   // Rows past S compute on the last row's values and are not written.
   bf16x8 qf[8], df[8];
@@ -692,18 +691,22 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dq_kernel(
 
   const int k_part = 32 * T::NH * ks;        // first key of this wave's part of a stage
   const uint32_t k_lane = T::OFF_K + k_part * 256 + swzt(r32, g);
-  const uint32_t v_lane = T::OFF_V + k_part * 256 + swz256(r32, g);
+  const uint32_t v_lane = T::OFF_V + k_part * 256 + swzt(r32, g);
   const uint32_t t_lane = T::OFF_K + k_part * 256 + tr_base(lane);
-  for (int j = 0; j < nst; ++j) {
+  // Stages with a key of this wave's part that a row of it may see come first.
+  const int nw = !wave_ok ? 0
+                 : CAUSAL ? min(nst, qw + 31 < (uint32_t)k_part ? 0 : (int)((qw + 31 - k_part) / T::BK) + 1)
+                          : nst;
+  int j = 0;
+  for (; j < nw; ++j) {
     const uint32_t boff = (j & 1) * T::STAGE;
     wait_vmem();
     __syncthreads();   // tile j landed for all waves; tile j-1's buffer is free
-    if (j + 1 < nst)
-      issue_kstage<KS>(rk, rv, offk, offv, (uint32_t)(j + 1) * T::BK * rowb,
-                       smem + ((j + 1) & 1) * T::STAGE, w);
-    if (!wave_ok) continue;
+    const uint32_t nsoff = j + 1 < nst ? (uint32_t)(j + 1) * T::BK * rowb : 0;
+    const uint32_t nlds = lds0 + ((j + 1) & 1) * T::STAGE;
+    i32x4 nk = rk, nv = rv;
+    if (j + 1 == nst) nk[2] = nv[2] = 0;     // no next tile: zeros
     const uint32_t kb = (uint32_t)j * T::BK + k_part;
-    if (CAUSAL && kb > qw + 31) continue;    // its keys are masked for this wave
     const bool diag = CAUSAL ? (kb + 32 * T::NH - 1 > qw) : (kb + 32 * T::NH > Sv);
     // 32 keys at a time: one score and one dP accumulator live at a time,
     // which leaves registers for DQ_LA fragment reads in flight ahead of the
@@ -729,6 +732,12 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dq_kernel(
         __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
       }
       __builtin_amdgcn_sched_group_barrier(0x008, DQ_LA, 0);
+      // The next tile's copies go out behind the products they can hide behind
+      // (as in the forward).  Against the top of the tile, whole backward: 4100 rows
+      // of 8 heads 182.7 -> 177.6 us, 2500 of 4 (every key visible) 127.9 -> 126.8, 8192
+      // of 4 310.9 -> 309.2, 32768 of 4 3444 -> 3435.
+      if (hh == 0) issue_kblocks<KS>(nk, nv, off, 0, nsoff, nlds, w);
+      if (T::BLK > 2 && hh == T::NH - 1) issue_kblocks<KS>(nk, nv, off, 2, nsoff, nlds, w);
       bf16x8 sf[2];
       float p[16];
 #pragma unroll
@@ -752,6 +761,17 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dq_kernel(
     }
   }
 
+  // The others: only this wave's share of the copies.
+  for (; j < nst; ++j) {
+    wait_vmem();
+    __syncthreads();
+    if (j + 1 < nst)
+#pragma unroll
+      for (int i = 0; i < T::BLK; i += 2)
+        issue_kblocks<KS>(rk, rv, off, i, (uint32_t)(j + 1) * T::BK * rowb,
+                          lds0 + ((j + 1) & 1) * T::STAGE, w);
+  }
+  wait_vmem();       // the last stage's empty copies (to LDS) have ended
   if (KS > 1) {
     // Add the KS parts' sums in ascending key order: parts 1.. pass theirs
     // through the stage buffers (16 KB per wave).

@@ -248,13 +248,13 @@ __global__ __launch_bounds__(512, 1) void attn_fwd_kernel(
     }
   }
 
+  wait_vmem();       // the last stage's empty copies (to LDS) have ended
   float l_tot = l_run + __shfl_xor(l_run, 32);
   if (KS > 1) {
     // Fold the KS parts of every row in fp32, in ascending key order: parts
     // 1.. pass (m_ref, l, acc) through the stage buffers (16 KB per wave).
     float* fold = reinterpret_cast<float*>(smem);
     float* fold_ml = fold + (KS - 1) * NQW * 4096;
-    wait_vmem();
     __syncthreads();   // every wave is done reading the last stage, and copying
     if (ks > 0) {
       const int slot = (ks - 1) * NQW + wq;

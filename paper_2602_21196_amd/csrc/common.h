@@ -50,24 +50,11 @@ __device__ __forceinline__ void lds_write_b128(char* base, uint32_t off, u32x4 v
   *reinterpret_cast<u32x4*>(base + off) = v;
 }
 
-typedef __attribute__((address_space(3))) void lds_void;
-
-// Raw buffer resource over `bytes` bytes at `base` (stride 0, gfx9 data
-// format word); loads at offsets past `bytes` return zeros instead of faulting.
-typedef __amdgpu_buffer_rsrc_t buf_rsrc;
-__device__ __forceinline__ buf_rsrc make_rsrc(const void* base, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes, 0x00020000);
-}
-
 // Buffer -> LDS copy of 16 bytes per lane (buffer_load_dwordx4 ... lds): the
-// bytes at voff + soff (lane offset + uniform offset) of lane L land at
-// lds_wave_base + 16 * L.  No vector ALU work for the address; tracked by vmcnt.
-__device__ __forceinline__ void dma_buf_b128(buf_rsrc r, uint32_t voff, uint32_t soff,
-                                             char* lds_wave_base) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)lds_wave_base, 16, voff, soff, 0, 0);
-}
-
-// The same copy written out, for kernels that issue the copies of a later tile
+// bytes at voff + soff (lane offset + uniform offset) of lane L land at LDS
+// address lds + 16 * L, zeros where that offset is past the resource's bytes.  No
+// vector ALU work for the address; tracked by vmcnt.  Written out, because the
+// kernels issue the copies of a later tile
 // between reads of this one: the compiler cannot tell which LDS bytes a copy
 // writes, and would wait for it before the next transposing read.  The wave
 // waits itself (wait_vmem, then a barrier) before the bytes are read, and no
@@ -76,8 +63,7 @@ __device__ __forceinline__ void dma_buf_b128(buf_rsrc r, uint32_t voff, uint32_t
 // that was spilled) wrote it; the compiler does not look into the text, so the
 // wait is in it, once for up to four copies (one by one it cost the 8192^3
 // product 861 against 851 us and the dK/dV walks 3 %).  No register results;
-// `lds` is an LDS address (lds_address).  m0 is its own here: a kernel uses
-// these copies or dma_buf_b128, not both.
+// `lds` is an LDS address (lds_address).
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ i32x4 rsrc_words(const void* base, uint32_t bytes) {
   const uint64_t a = (uint64_t)base;

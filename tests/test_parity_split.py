@@ -120,6 +120,27 @@ def test_backward_segments(S, Hq, Hkv, causal):
             assert torch.equal(_bits(a), _bits(b)), U
 
 
+# 256-row blocks x heads on both sides of 224 | 448 (causal) and 64 | 128.
+DQ_PARTS = [(3584, 16, 2, True), (3585, 16, 2, True), (7169, 16, 4, True), (1025, 14, 2, False),
+            (2305, 14, 7, False)]
+
+
+@pytest.mark.parametrize("S,Hq,Hkv,causal", DQ_PARTS)
+def test_dq_key_parts(S, Hq, Hkv, causal):
+    """dQ rows at both ends of the sequence, of 32-row waves and at random; bars: tol.py's."""
+    up = _upipe()
+    cpu = W.attention_inputs(S, Hq, Hkv, 128, 60 + S)
+    rows = np.unique(np.r_[0:34, 223:258, S - 66:S, np.random.default_rng(S).integers(0, S, 60)])
+    q, k, v, do = (t.to(DEV) for t in cpu)
+    print(f"dq parts S={S} Hq={Hq} Hkv={Hkv} causal={causal}", flush=True)
+    o, lse = up.attn_fwd(q, k, v, causal=causal, U=2)
+    dq, _, _ = up.attn_bwd(q, k, v, o, lse, do, causal=causal, U=2)
+    torch.cuda.synchronize()
+    q, k, v, do = cpu
+    _, _, ref, _ = A.attn_rows_at(as64(q[rows]), rows, as64(k), as64(v), as64(do[rows]), causal)
+    assert_close("dq", dq.cpu()[rows], ref)
+
+
 def test_backward_of_a_long_batch_equals_single_sequences():
     """More sequences than rows are kept for at a time."""
     up = _upipe()

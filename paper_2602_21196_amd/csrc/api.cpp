@@ -151,8 +151,8 @@ AttnBwdPlan plan_attn_bwd(int64_t S, int Hq, int Hkv, int U) {
   }
   p.Qc = c.take(U * head);
   p.dOc = c.take(U * head);
-  // D and lse rows: of a chunk, and in the room of its former dQ (now written
-  // in place; the size stays what callers have been told to bring) of all heads
+  // D and lse rows: of a chunk, or, in the room of its dQ too where that is
+  // written in place, of all heads
   p.rows = c.take(U * head);
   c.take(U * row32);
   c.take(U * row32);
@@ -320,13 +320,18 @@ int run_attn_bwd(const bf16* q, const bf16* k, const bf16* v, const bf16* o,
   // against 34.6 ms; rows 1 KB apart use 4 of an L2's 16 channels).  So chunks
   // of U heads are packed for it, and dQ takes all heads in place after the
   // last one, if the rows of all heads fit behind the packed ones.
+  // Where an output overlaps an input (any length), nothing of a chunk may be
+  // read after its first write: its dQ comes from the packed rows too, and goes
+  // through the workspace.
   float* dK32 = p.carry ? (float*)(ws + p.dK32) : nullptr;
   float* dV32 = p.carry ? (float*)(ws + p.dV32) : nullptr;
   bf16* Qc = (bf16*)(ws + p.Qc);
   bf16* dOc = (bf16*)(ws + p.dOc);
-  const bool keep_rows = p.total - p.rows >= row_bytes;
+  bf16* dQc = (bf16*)(ws + p.rows);      // overlap only
+  const size_t dq_bytes = apart ? 0 : (size_t)U * p.Sp * HEAD_DIM * 2;
+  const bool keep_rows = apart && p.total - p.rows >= row_bytes;
   const int64_t n_rows = (keep_rows ? Hq : U) * p.Sp;
-  float* D = (float*)(ws + p.rows);
+  float* D = (float*)(ws + p.rows + dq_bytes);
   float* lse_c = D + n_rows;
   const bool kv_pack = !p.kv_direct && (!rows_addressable(S, K.row) || !apart);
   for (int64_t b = 0; b < B; ++b) {
@@ -350,6 +355,15 @@ int run_attn_bwd(const bf16* q, const bf16* k, const bf16* v, const bf16* o,
       const int rc = run_dkdv(head_major(Qc, p.Sp), head_major(dOc, p.Sp), lh, Dh, Kb, Vb, dK32,
                               dV32, sub(dK, b, 0), sub(dV, b, 0), S, p.Sp, U, h0, G, causal, st);
       if (rc != UPIPE_OK) return rc;
+      if (!apart) {
+        UPIPE_LAUNCH(kAttnBwdDq, st,
+                     launch_attn_bwd_dq(head_major(Qc, p.Sp), head_major(dOc, p.Sp), lh, Dh, Kb, Vb,
+                                        head_major(dQc, p.Sp), S, p.Sp, 1, U, h0, G, causal, parts,
+                                        RopeArgs{}, st));
+        UPIPE_LAUNCH(kUnpackRows, st,
+                     launch_unpack_rows(dQc, S, Hq, h0, U, p.Sp, sub(dQ, b, 0).p, st));
+        continue;
+      }
       const int d0 = keep_rows ? 0 : h0, nh = keep_rows ? Hq : U;
       if (d0 + nh == h0 + U)
         UPIPE_LAUNCH(kAttnBwdDq, st,

@@ -87,7 +87,8 @@ struct AttnBwdPlan {
   bool kv_direct = false;   // keys/values read in place (no Kp, Vp)
   size_t Kp = 0, Vp = 0, dK32 = 0, dV32 = 0;
   size_t Qc = 0, dOc = 0;
-  size_t rows = 0;     // D and lse rows, to the end
+  size_t rows = 0;     // D and lse rows, to the end; dQ of a chunk before them
+                       // where an output overlaps an input
   size_t total = 0;
 };
 

@@ -22,6 +22,9 @@ struct HeadView {
 // src [S, H, d] heads h0..h0+n-1  ->  dst [n, Sp, d]; rows >= S are zero.
 hipError_t launch_pack_rows(const bf16* src, int64_t S, int H, int h0, int n,
                             int64_t Sp, bf16* dst, hipStream_t st);
+// Rows s < S of src [n, Sp, d]  ->  heads h0..h0+n-1 of dst [S, H, d].
+hipError_t launch_unpack_rows(const bf16* src, int64_t S, int H, int h0, int n,
+                              int64_t Sp, bf16* dst, hipStream_t st);
 // D[B, n, Sp] = rowsum(a * b) over the head width and lse_c[B, n, Sp] =
 // -sqrt(d) times the rows of heads h0.. of lse [B, lse_heads, S]; zero for
 // rows >= S.  Head hh of a and b is head h0 + hh.  B <= 65535.

@@ -7,6 +7,8 @@
 // the caller's rows in place, and rows are packed only where that cannot be or
 // is slower:
 //   pack   token-major [S, H, d] (chosen heads)  ->  head-major [n, Sp, d]
+//   unpack head-major [n, Sp, d]                 ->  token-major [S, H, d]
+//          (results that must not be written before every input is read)
 // Rows S..Sp-1 of packed buffers are zero.  All kernels here are HBM-bound.
 #include "common.h"
 #include "kernels.h"
@@ -30,6 +32,23 @@ __global__ __launch_bounds__(256) void pack_rows_kernel(
     if (s < S)
       val = *reinterpret_cast<const u32x4*>(src + (s * H + h) * HEAD_DIM + chunk * 8);
     *reinterpret_cast<u32x4*>(dst + ((int64_t)hh * Sp + s) * HEAD_DIM + chunk * 8) = val;
+  }
+}
+
+// Copies rows [0, S) of head-major [n, Sp, d] into heads h0.. of [S, H, d].
+__global__ __launch_bounds__(256) void unpack_rows_kernel(
+    const bf16* __restrict__ src, int64_t S, int H, int h0, int n, int64_t Sp,
+    bf16* __restrict__ dst) {
+  const int64_t pieces = S * n * 16;
+  for (int64_t pi = (int64_t)blockIdx.x * 256 + threadIdx.x; pi < pieces;
+       pi += (int64_t)gridDim.x * 256) {
+    const int chunk = pi & 15;
+    const int64_t rest = pi >> 4;
+    const int hh = rest % n;
+    const int64_t s = rest / n;
+    const u32x4 val = *reinterpret_cast<const u32x4*>(
+        src + ((int64_t)hh * Sp + s) * HEAD_DIM + chunk * 8);
+    *reinterpret_cast<u32x4*>(dst + (s * H + h0 + hh) * HEAD_DIM + chunk * 8) = val;
   }
 }
 
@@ -161,6 +180,14 @@ hipError_t launch_pack_rows(const bf16* src, int64_t S, int H, int h0, int n,
                             int64_t Sp, bf16* dst, hipStream_t st) {
   dim3 grid((unsigned)(Sp / 64), (unsigned)n);
   hipLaunchKernelGGL(pack_rows_kernel, grid, dim3(256), 0, st, src, S, H, h0, Sp, dst);
+  return hipGetLastError();
+}
+
+hipError_t launch_unpack_rows(const bf16* src, int64_t S, int H, int h0, int n,
+                              int64_t Sp, bf16* dst, hipStream_t st) {
+  const int64_t blocks = (S * n * 16 + 255) / 256;
+  hipLaunchKernelGGL(unpack_rows_kernel, dim3((unsigned)(blocks < 65536 ? blocks : 65536)),
+                     dim3(256), 0, st, src, S, H, h0, n, Sp, dst);
   return hipGetLastError();
 }
 

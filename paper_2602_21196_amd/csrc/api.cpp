@@ -117,14 +117,14 @@ AttnFwdPlan plan_attn_fwd_ring(int64_t Sq, int64_t Skv, int Hq, int Hkv, int U) 
     p.Kp = c.take(Hkv * kvhead);
     p.Vp = c.take(Hkv * kvhead);
   }
-  // The size that callers have been told to bring.  Only Kp and Vp are used
-  // now, where the keys and values cannot be read in place: a chunk's queries
-  // and outputs (and, up to 32768 rows, the two halves of a split key range
-  // with their lse rows) are no longer staged.
-  const int ns = p.Sp <= 128 * 256 && p.Skvp >= 256 ? 2 : 1;
-  c.take(U * qhead);
-  c.take(ns * U * qhead);
-  if (ns > 1) c.take((size_t)ns * U * p.Sp * 4);
+  // The size that callers have been told to bring.  Kp and Vp are used where
+  // the keys and values cannot be read in place, Qc, Oc and lse_part where an
+  // output overlaps an input.  (Up to 32768 rows there is room for two outputs
+  // and lse rows, of a key range split in halves; one of them is used.)
+  p.ns = p.Sp <= 128 * 256 && p.Skvp >= 256 ? 2 : 1;
+  p.Qc = c.take(U * qhead);
+  p.Oc = c.take(p.ns * U * qhead);
+  if (p.ns > 1) p.lse_part = c.take((size_t)p.ns * U * p.Sp * 4);
   p.total = c.used;
   return p;
 }
@@ -202,9 +202,14 @@ int run_attn_fwd_ring(const bf16* q, const bf16* k, const bf16* v, bf16* o, floa
   const int parts = attn_fwd_key_parts(Sq, Skv, delta, Hq, causal);
   const HeadView Q = token_major(q, Sq, Hq), O = token_major(o, Sq, Hq);
   const HeadView K = token_major(k, Skv, Hkv), V = token_major(v, Skv, Hkv);
-  const int64_t o_bytes = B * O.batch * 2, kv_bytes = B * K.batch * 2;
-  const bool apart = kv_in_place(Skv, Hkv) || (!overlap(o, o_bytes, k, kv_bytes) &&
-                                               !overlap(o, o_bytes, v, kv_bytes));
+  // Whether the outputs may be written while others still read the inputs.  o
+  // may be q itself: a workgroup reads its queries before it writes them.
+  const int64_t q_bytes = B * Q.batch * 2, kv_bytes = B * K.batch * 2;
+  const int64_t lse_bytes = B * Hq * Sq * 4;
+  const bool apart = (o == q || !overlap(o, q_bytes, q, q_bytes)) &&
+                     !overlap(o, q_bytes, k, kv_bytes) && !overlap(o, q_bytes, v, kv_bytes) &&
+                     !overlap(lse, lse_bytes, q, q_bytes) &&
+                     !overlap(lse, lse_bytes, k, kv_bytes) && !overlap(lse, lse_bytes, v, kv_bytes);
   if (rows_addressable(Skv, K.row) && apart) {
     // Every tensor in place, all heads of as many sequences as one grid holds.
     const int64_t per_seq = (Sq * parts + 255) / 256 * Hq;
@@ -217,18 +222,46 @@ int run_attn_fwd_ring(const bf16* q, const bf16* k, const bf16* v, bf16* o, floa
     }
     return UPIPE_OK;
   }
-  // Token-major key/value rows of one head span 2^32 bytes or more (or are
-  // overwritten by o): pack them head-major, one sequence after another.
+  // Token-major key/value rows of one head span 2^32 bytes or more, or an
+  // output overlaps an input: pack keys and values head-major (unless they lie
+  // so), one sequence after another.  With an overlap nothing may be read after
+  // the first write, so chunks of U heads go through the workspace: a chunk's
+  // queries are packed, its outputs written back when it is done.
   const AttnFwdPlan p = plan_attn_fwd_ring(Sq, Skv, Hq, Hkv, U);
   bf16* Kp = (bf16*)(ws + p.Kp);
   bf16* Vp = (bf16*)(ws + p.Vp);
+  bf16* Qc = (bf16*)(ws + p.Qc);
+  bf16* Oc = (bf16*)(ws + p.Oc);
   for (int64_t b = 0; b < B; ++b) {
-    UPIPE_LAUNCH(kPackRows, st, launch_pack_rows(sub(K, b, 0).p, Skv, Hkv, 0, Hkv, p.Skvp, Kp, st));
-    UPIPE_LAUNCH(kPackRows, st, launch_pack_rows(sub(V, b, 0).p, Skv, Hkv, 0, Hkv, p.Skvp, Vp, st));
-    UPIPE_LAUNCH(kAttnFwd, st,
-                 launch_attn_fwd(sub(Q, b, 0), head_major(Kp, p.Skvp), head_major(Vp, p.Skvp),
-                                 sub(O, b, 0), lse + b * Hq * Sq, Sq, Skv, delta, 1, Hq, Hq, 0, G,
-                                 causal, parts, st));
+    HeadView Kb = sub(K, b, 0), Vb = sub(V, b, 0);
+    float* lse_b = lse + b * Hq * Sq;
+    if (!kv_in_place(Skv, Hkv)) {
+      UPIPE_LAUNCH(kPackRows, st, launch_pack_rows(Kb.p, Skv, Hkv, 0, Hkv, p.Skvp, Kp, st));
+      UPIPE_LAUNCH(kPackRows, st, launch_pack_rows(Vb.p, Skv, Hkv, 0, Hkv, p.Skvp, Vp, st));
+      Kb = head_major(Kp, p.Skvp);
+      Vb = head_major(Vp, p.Skvp);
+    }
+    if (apart) {
+      UPIPE_LAUNCH(kAttnFwd, st,
+                   launch_attn_fwd(sub(Q, b, 0), Kb, Vb, sub(O, b, 0), lse_b, Sq, Skv, delta, 1, Hq,
+                                   Hq, 0, G, causal, parts, st));
+      continue;
+    }
+    for (int h0 = 0; h0 < Hq; h0 += U) {
+      float* to = lse_b + (int64_t)h0 * Sq;      // the chunk's lse rows
+      float* rows = p.ns > 1 ? (float*)(ws + p.lse_part) : to;
+      UPIPE_LAUNCH(kPackRows, st, launch_pack_rows(sub(Q, b, 0).p, Sq, Hq, h0, U, p.Sp, Qc, st));
+      // The kernel counts lse rows from head 0 on.
+      UPIPE_LAUNCH(kAttnFwd, st,
+                   launch_attn_fwd(head_major(Qc, p.Sp), Kb, Vb, head_major(Oc, p.Sp),
+                                   rows - (int64_t)h0 * Sq, Sq, Skv, delta, 1, Hq, U, h0, G, causal,
+                                   parts, st));
+      UPIPE_LAUNCH(kUnpackRows, st,
+                   launch_unpack_rows(Oc, Sq, Hq, h0, U, p.Sp, sub(O, b, 0).p, st));
+      if (rows != to)
+        UPIPE_LAUNCH(kUnpackRows, st,
+                     hipMemcpyAsync(to, rows, (size_t)U * Sq * 4, hipMemcpyDeviceToDevice, st));
+    }
   }
   return UPIPE_OK;
 }

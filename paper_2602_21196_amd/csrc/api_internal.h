@@ -78,7 +78,10 @@ inline bool kv_in_place(int64_t S, int Hkv) { return Hkv == 1 && S % SEQ_PAD == 
 struct AttnFwdPlan {
   int64_t Sp = 0;     // query rows, padded
   int64_t Skvp = 0;   // key/value rows, padded
-  size_t Kp = 0, Vp = 0, total = 0;
+  size_t Kp = 0, Vp = 0;
+  size_t Qc = 0, Oc = 0, lse_part = 0;   // a chunk's, where an output overlaps an input
+  int ns = 1;
+  size_t total = 0;
 };
 
 struct AttnBwdPlan {

@@ -96,3 +96,73 @@ def test_backward_outputs_over_inputs(S, Hq, Hkv, B, causal, Us, over):
             first = {n: out[n].clone() for n in ("dk", "dv")}
         for n, t in first.items():
             assert torch.equal(_bits(out[n]), _bits(t)), (n, U)
+
+
+# Sq, Skv, Hq, Hkv, B, query offset, causal, chunk sizes, output -> (input, elements
+# behind its start).  What is written over an input that a later chunk reads is
+# right with one chunk only.
+FORWARD = [
+    (384, 384, 1, 1, 1, 0, True, (1,), {"o": ("k", 0)}),          # K, V read in place
+    (384, 384, 1, 1, 1, 0, False, (1,), {"o": ("v", 0)}),
+    (1280, 1280, 3, 1, 1, 0, True, (3,), {"o": ("v", 0)}),        # v is a third of o
+    (300, 300, 3, 3, 1, 0, True, (1, 3), {"o": ("v", 0)}),        # packed
+    (300, 300, 4, 2, 2, 0, True, (1, 2, 4), {"o": ("q", 0)}),     # in place, head by head
+    (700, 700, 4, 1, 1, 0, False, (4,), {"o": ("q", 512)}),       # one row on
+    (513, 513, 2, 2, 3, 0, True, (2,), {"o": ("q", 0), "lse": ("v", 0)}),
+    (384, 384, 1, 1, 1, 0, True, (1,), {"lse": ("k", 0)}),
+    (256, 640, 2, 1, 1, 400, True, (2,), {"o": ("k", 0)}),        # ring step
+    (640, 200, 2, 2, 1, -50, True, (2,), {"o": ("v", 0)}),        # rows that see no key
+    (100, 100, 2, 2, 1, 0, True, (2,), {"o": ("k", 0), "lse": ("q", 0)}),  # one key stage
+]
+
+
+@pytest.mark.parametrize("Sq,Skv,Hq,Hkv,B,off,causal,Us,over", FORWARD)
+def test_forward_outputs_over_inputs(Sq, Skv, Hq, Hkv, B, off, causal, Us, over):
+    """Bitwise what separate tensors give."""
+    up = _upipe()
+    g = torch.Generator().manual_seed(Sq + Skv)
+    cpu = {n: torch.randn((B, S, H, 128), generator=g).to(torch.bfloat16)
+           for n, S, H in (("q", Sq, Hq), ("k", Skv, Hkv), ("v", Skv, Hkv))}
+    lse_n = B * Hq * Sq
+    for U in Us:
+        print(f"overlap fwd Sq={Sq} Skv={Skv} Hq={Hq} Hkv={Hkv} B={B} U={U} {over}", flush=True)
+        room = {n: _room(t, 2048 + max(0, cpu["q"].numel() - t.numel(), 2 * lse_n - t.numel()))
+                for n, t in cpu.items()}
+        outs = {}
+        for way in ("apart", "over"):
+            x = {n: r[0] for n, r in room.items()}
+            o, lse = torch.empty_like(x["q"]), torch.empty((B, Hq, Sq), device=DEV)
+            if way == "over" and "o" in over:
+                o = _at(room[over["o"][0]][1], over["o"][1], o)
+            if way == "over" and "lse" in over:
+                lse = _at(room[over["lse"][0]][1][:2 * lse_n].view(torch.float32), 0, lse)
+            ptrs = [x[n].data_ptr() for n in ("q", "k", "v")] + [o.data_ptr(), lse.data_ptr()]
+            if Sq == Skv and off == 0:
+                ws = up.workspace(up.upipe_attn_fwd_workspace_size(Sq, Hq, Hkv, 128, U), DEV)
+                st = up.upipe_attn_fwd_batch(*ptrs, B, Sq, Hq, Hkv, 128, int(causal), U,
+                                             ws.data_ptr(), ws.numel(), _stream())
+            else:
+                ws = up.workspace(up.upipe_attn_fwd_ring_workspace_size(Sq, Skv, Hq, Hkv, 128, U),
+                                  DEV)
+                st = up.upipe_attn_fwd_ring(*ptrs, Sq, Skv, off, 0, Hq, Hkv, 128, int(causal), U,
+                                            ws.data_ptr(), ws.numel(), _stream())
+            assert st == 0
+            torch.cuda.synchronize()
+            outs[way] = (o.clone(), lse.clone())
+        for a, b in zip(outs["apart"], outs["over"]):
+            assert torch.equal(_bits(a), _bits(b)), U
+
+
+@pytest.mark.parametrize("S,Hq,Hkv,U,src", [(384, 1, 1, 1, "v"), (300, 2, 2, 2, "k")])
+def test_noalloc_output_over_an_input(S, Hq, Hkv, U, src):
+    """The allocation-free forward takes the same route in its own scratch."""
+    up = _upipe()
+    q, k, v, _ = (t.to(DEV) for t in W.attention_inputs(S, Hq, Hkv, 128, 5))
+    o_ref, lse_ref = up.attn_fwd(q, k, v, U=U)
+    lse = torch.empty_like(lse_ref)
+    o = {"k": k, "v": v}[src]
+    print(f"noalloc overlap S={S} over {src}", flush=True)
+    assert up.upipe_attn_fwd_noalloc(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
+                                     lse.data_ptr(), S, Hq, Hkv, 128, 1, U, _stream()) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(_bits(o), _bits(o_ref)) and torch.equal(_bits(lse), _bits(lse_ref))

@@ -189,12 +189,6 @@ int run_dkdv(const HeadView& Q, const HeadView& dO, const float* lse_c, const fl
   return UPIPE_OK;
 }
 
-// Whether an output's bytes touch an input's (both dense, of this many bytes).
-static bool overlap(const void* out, int64_t out_bytes, const void* in, int64_t in_bytes) {
-  const uintptr_t a = (uintptr_t)out, b = (uintptr_t)in;
-  return a < b + (uintptr_t)in_bytes && b < a + (uintptr_t)out_bytes;
-}
-
 int run_attn_fwd_ring(const bf16* q, const bf16* k, const bf16* v, bf16* o, float* lse, int64_t B,
                       int64_t Sq, int64_t Skv, int64_t delta, int Hq, int Hkv, int causal,
                       int U, char* ws, hipStream_t st) {

@@ -50,6 +50,11 @@ class ProfScope {
   } while (0)
 
 bool aligned16(const void* p);
+// Whether an output's bytes touch an input's (both dense, of this many bytes).
+inline bool overlap(const void* out, int64_t out_bytes, const void* in, int64_t in_bytes) {
+  const uintptr_t a = (uintptr_t)out, b = (uintptr_t)in;
+  return a < b + (uintptr_t)in_bytes && b < a + (uintptr_t)out_bytes;
+}
 // B sequences of `per_seq` elements each address below 2^61 elements (so no
 // pointer offset into a batch can overflow); B >= 1.
 inline bool batch_ok(int64_t B, int64_t per_seq) {

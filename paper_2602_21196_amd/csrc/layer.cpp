@@ -75,7 +75,9 @@ int64_t wgrad_split_len(int64_t S, int64_t M, int64_t N) {
 
 struct LayerFwdPlan {
   int64_t Sp = 0;
-  size_t Kp = 0, Vp = 0, total = 0;
+  size_t Kp = 0, Vp = 0;
+  size_t Qc = 0;       // a chunk's queries, where o_saved overlaps x or wqkv
+  size_t total = 0;
 };
 
 struct LayerBwdPlan {
@@ -99,10 +101,8 @@ LayerFwdPlan plan_layer_fwd(int64_t S, int d_model, int Hq, int Hkv, int U) {
   Carver c;
   p.Kp = c.take(Hkv * head);
   p.Vp = c.take(Hkv * head);
-  // A chunk's Q and O, no longer staged: the size that callers have been told
-  // to bring stays.
-  c.take(U * head);
-  c.take(U * head);
+  p.Qc = c.take(U * head);
+  c.take(U * head);     // in the size that callers have been told to bring; unused
   p.total = c.used;
   return p;
 }
@@ -215,13 +215,34 @@ int run_layer_fwd_seq(const bf16* x, const bf16* wqkv, const bf16* wo, bf16* y, 
   const int64_t qw = (int64_t)Hq * HEAD_DIM;
   bf16* Kp = (bf16*)(ws + p.Kp);
   bf16* Vp = (bf16*)(ws + p.Vp);
-  const HeadView QO = token_major(o_saved, S, Hq);
-  UPIPE_LAUNCH(kGemm, st,
-               gemm1(operand(x, dm, S, dm), true, operand(wqkv, nqkv, nqkv, dm), false,
-                     qkv_epi(QO, Kp, Vp, Hq, Hkv, S, Sp, rope), GEMM_EPI_HEADS, Sp, nqkv, dm, st));
-  UPIPE_LAUNCH(kAttnFwd, st,
-               launch_attn_fwd(QO, head_major(Kp, Sp), head_major(Vp, Sp), QO, lse, S, S, 0, 1, Hq,
-                               Hq, 0, Hq / Hkv, 1, attn_fwd_key_parts(S, S, 0, Hq, 1), st));
+  const HeadView QO = token_major(o_saved, S, Hq), K = head_major(Kp, Sp), V = head_major(Vp, Sp);
+  const GemmOperand X = operand(x, dm, S, dm);
+  const int G = Hq / Hkv, parts = attn_fwd_key_parts(S, S, 0, Hq, 1);
+  const int64_t o_bytes = S * qw * 2;
+  if (!overlap(o_saved, o_bytes, x, S * dm * 2) && !overlap(o_saved, o_bytes, wqkv, dm * nqkv * 2)) {
+    UPIPE_LAUNCH(kGemm, st,
+                 gemm1(X, true, operand(wqkv, nqkv, nqkv, dm), false,
+                       qkv_epi(QO, Kp, Vp, Hq, Hkv, S, Sp, rope), GEMM_EPI_HEADS, Sp, nqkv, dm, st));
+    UPIPE_LAUNCH(kAttnFwd, st,
+                 launch_attn_fwd(QO, K, V, QO, lse, S, S, 0, 1, Hq, Hq, 0, G, 1, parts, st));
+  } else {
+    // The queries cannot pass through o_saved while x and wqkv are read: K and V
+    // first, then chunks of U heads, each writing o_saved when its queries are
+    // formed.
+    const int64_t kvw = 2 * (int64_t)Hkv * HEAD_DIM, w = (int64_t)U * HEAD_DIM;
+    const HeadView Qc = head_major((bf16*)(ws + p.Qc), Sp);
+    UPIPE_LAUNCH(kGemm, st,
+                 gemm1(X, true, operand(wqkv + qw, nqkv, kvw, dm), false,
+                       qkv_epi(Qc, Kp, Vp, 0, Hkv, S, Sp, rope), GEMM_EPI_HEADS, Sp, kvw, dm, st));
+    for (int h0 = 0; h0 < Hq; h0 += U) {
+      UPIPE_LAUNCH(kGemm, st,
+                   gemm1(X, true, operand(wqkv + (int64_t)h0 * HEAD_DIM, nqkv, w, dm), false,
+                         qkv_epi(Qc, Kp, Vp, U, Hkv, S, Sp, rope), GEMM_EPI_HEADS, Sp, w, dm, st));
+      UPIPE_LAUNCH(kAttnFwd, st,
+                   launch_attn_fwd(Qc, K, V, sub(QO, 0, h0), lse, S, S, 0, 1, Hq, U, h0, G, 1, parts,
+                                   st));
+    }
+  }
   // y = final_out Wo.
   UPIPE_LAUNCH(kGemm, st,
                gemm1(operand(o_saved, qw, S, qw), true, operand(wo, dm, dm, qw), false,

@@ -166,3 +166,36 @@ def test_noalloc_output_over_an_input(S, Hq, Hkv, U, src):
                                      lse.data_ptr(), S, Hq, Hkv, 128, 1, U, _stream()) == 0
     torch.cuda.synchronize()
     assert torch.equal(_bits(o), _bits(o_ref)) and torch.equal(_bits(lse), _bits(lse_ref))
+
+
+# S, d_model, Hq, Hkv, B, U, rotary base, the tensor that o_saved lies over.  With
+# U < Hq a later chunk would read what an earlier one overwrote.
+BLOCK = [(300, 256, 2, 1, 1, 2, 1e4, "x"), (513, 384, 3, 3, 2, 3, 0.0, "x"),
+         (200, 512, 4, 2, 1, 4, 5e5, "wqkv"), (128, 256, 4, 1, 1, 4, 0.0, "x")]
+
+
+@pytest.mark.parametrize("S,dm,Hq,Hkv,B,U,base,src", BLOCK)
+def test_block_forward_output_over_an_input(S, dm, Hq, Hkv, B, U, base, src):
+    """Bitwise what separate tensors give."""
+    up = _upipe()
+    x, wqkv, wo, _ = W.batch_layer_inputs(S, dm, Hq, Hkv, 128, 3 * S, B)
+    room = {"x": _room(x, 2048 + B * S * Hq * 128), "wqkv": _room(wqkv, 2048 + B * S * Hq * 128)}
+    wo = wo.to(DEV)
+    ws = up.workspace(up.upipe_layer_fwd_workspace_size(S, dm, Hq, Hkv, 128, U), DEV)
+    outs = {}
+    for way in ("apart", "over"):
+        print(f"block {way} S={S} dm={dm} Hq={Hq} Hkv={Hkv} B={B} U={U} over {src}", flush=True)
+        o = torch.empty((B, S, Hq, 128), dtype=torch.bfloat16, device=DEV)
+        if way == "over":
+            o = _at(room[src][1], 0, o)
+        y = torch.empty_like(x, device=DEV)
+        lse = torch.empty((B, Hq, S), device=DEV)
+        st = up.upipe_layer_fwd_ex(room["x"][0].data_ptr(), room["wqkv"][0].data_ptr(),
+                                   wo.data_ptr(), y.data_ptr(), o.data_ptr(), lse.data_ptr(), B, S,
+                                   dm, Hq, Hkv, 128, U, base, 0, ws.data_ptr(), ws.numel(),
+                                   _stream())
+        assert st == 0
+        torch.cuda.synchronize()
+        outs[way] = (y, o.clone(), lse)
+    for a, b in zip(outs["apart"], outs["over"]):
+        assert torch.equal(_bits(a), _bits(b))

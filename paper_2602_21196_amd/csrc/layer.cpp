@@ -109,7 +109,9 @@ LayerFwdPlan plan_layer_fwd(int64_t S, int d_model, int Hq, int Hkv, int U) {
 
 // Bytes of the backward's workspace when the weight gradients were cut into up
 // to 32 pieces and a chunk's Q, O and rows were held: callers have been told to
-// bring these, and the plan below stays within them.
+// bring these, and the plan below stays within them: up to 32 of fewer, longer
+// pieces, and the D and lse rows of up to 64 heads are 512 bytes a row of the
+// sequence, where a chunk's buffers (U >= 1) were 520.
 size_t layer_bwd_budget(int64_t S, int d_model, int Hq, int Hkv, int U) {
   const int64_t Sp = round_up(S, SEQ_PAD);
   const int64_t len = std::max<int64_t>(256, round_up((S + 31) / 32, 256));
@@ -153,13 +155,18 @@ LayerBwdPlan plan_layer_bwd(int64_t S, int d_model, int Hq, int Hkv, int U) {
   p.scratch = c.take(p.scratch_bytes);
   p.dWqkv32 = c.take((size_t)d_model * nqkv * 4);
   p.dWo32 = c.take((size_t)qw * d_model * 4);
-  // The rest of the budget holds as many heads of recomputed attention output
-  // as there are (one at least).
+  // Recomputed attention output: in the rest of the budget, or, where that
+  // holds fewer heads (at 40 heads and U = 1 it may hold none), in the dK | dV
+  // part of dQKV, which is written after the last of them is done with.
   const size_t budget = layer_bwd_budget(S, d_model, Hq, Hkv, U);
   const size_t used = c.used + 256;
-  p.o_heads = budget > used ? (int)std::min<size_t>(Hq, (budget - used) / head) : 0;
-  p.o_heads = std::max(1, p.o_heads);
-  p.Oc = c.take(p.o_heads * head);
+  const int rest = budget > used ? (int)std::min<size_t>(Hq, (budget - used) / head) : 0;
+  p.o_heads = std::min(Hq, 2 * Hkv);
+  p.Oc = p.dQKV + Hq * head;
+  if (rest > p.o_heads) {
+    p.o_heads = rest;
+    p.Oc = c.take(rest * head);
+  }
   p.total = std::max(c.used, budget);
   return p;
 }

@@ -226,6 +226,38 @@ def test_workspace_sizes_follow_the_plan():
         (sizes[3] - sizes[2]) // 4
 
 
+def _block_backward_size(S, dm, Hq, Hkv, U):
+    """The block backward's workspace: what a plan of one chunk of U heads at a time
+    needs, in 256-byte aligned pieces."""
+    Sp = (S + 127) // 128 * 128
+    head = Sp * 256
+    G = Hq // Hkv
+    carry = any((g * G) // U != ((g + 1) * G - 1) // U for g in range(Hkv))
+    piece = max(256, ((S + 31) // 32 + 255) // 256 * 256)
+    widest = (Hq + 2 * Hkv) * 128
+    used = 0
+    for n in ([Hkv * head] * 2 + [2 * Hkv * head] * (2 if carry else 0) +      # K, V, dK32, dV32
+              [U * head, U * Sp * 4, U * Sp * 4, U * head, Hq * S * 4] +       # Q, D, lse, O; lse
+              [Hq * head, (Hq + 2 * Hkv) * head] +                             # dFO, dQKV
+              [(S + piece - 1) // piece * dm * widest * 4] +                   # split-K partials
+              [dm * widest * 4, Hq * 128 * dm * 4]):                           # sums over a batch
+        used = (used + 255) // 256 * 256 + n
+    return used
+
+
+def test_block_backward_size_stays():
+    """Saved sizes stay valid: many heads, chunks of one, short and long, ragged."""
+    shapes = [(100, 2048, 64, 8, 1), (129, 128, 64, 8, 1), (12, 256, 40, 8, 1),
+              (7, 4096, 40, 40, 1), ((1 << 24) - 128, 1024, 64, 64, 1)]
+    for Hq, Hkv in ((1, 1), (4, 1), (8, 2), (33, 3), (40, 1), (40, 8), (48, 16), (64, 1), (64, 64)):
+        for U in (u for u in range(1, Hq + 1) if Hq % u == 0):
+            for S in (1, 255, 256, 257, 1000, 8192, 8193, 65537, 3113162):
+                shapes += [(S, dm, Hq, Hkv, U) for dm in (128, 1024, 8192)]
+    for S, dm, Hq, Hkv, U in shapes:
+        assert upipe.upipe_layer_bwd_workspace_size(S, dm, Hq, Hkv, 128, U) == \
+            _block_backward_size(S, dm, Hq, Hkv, U), (S, dm, Hq, Hkv, U)
+
+
 @pytest.mark.parametrize("H,Hkv,C,U", [(16, 4, 4, 4), (32, 8, 8, 8),
                                        (64, 8, 8, 8), (64, 16, 4, 8),
                                        (32, 8, 8, 16), (8, 2, 2, 2)])

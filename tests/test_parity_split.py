@@ -204,3 +204,25 @@ def test_block_projection_with_large_tiles():
     assert_close("y", y[:n].cpu(), y_r)
     assert_close("o", o[:n].cpu(), o_r)
     assert_close("lse", lse[:, :n].cpu(), lse_r)
+
+
+@pytest.mark.parametrize("S,dm,Hq,Hkv,B", [(150, 256, 40, 1, 1), (129, 128, 40, 8, 2),
+                                           (700, 128, 64, 64, 1)])
+def test_block_recomputes_many_heads_in_little_room(S, dm, Hq, Hkv, B):
+    """At U = 1 and 40 heads or more the workspace has no room of its own for the
+    recomputed attention output: it lies in the dK | dV part of dQKV, twice the
+    key/value heads at a time.  Gradients are bitwise those with the output kept,
+    and a workspace of the size query's bytes is enough."""
+    up = _upipe()
+    x, wqkv, wo, dy = (t.to(DEV) for t in W.batch_layer_inputs(S, dm, Hq, Hkv, 128, 8, B))
+    size = up.upipe_layer_bwd_workspace_size(S, dm, Hq, Hkv, 128, 1)
+    guard = 4096
+    ws = torch.full((size + guard,), 0xA5, dtype=torch.uint8, device=DEV)
+    print(f"recompute S={S} dm={dm} Hq={Hq} Hkv={Hkv} B={B}", flush=True)
+    _, o, lse = up.layer_fwd(x, wqkv, wo, Hq, Hkv, U=1, rope_base=1e4)
+    kept = up.layer_bwd(x, wqkv, wo, o, lse, dy, Hq, Hkv, U=1, rope_base=1e4)
+    full = up.layer_bwd(x, wqkv, wo, None, None, dy, Hq, Hkv, U=1, rope_base=1e4, ws=ws)
+    torch.cuda.synchronize()
+    for a, b in zip(kept, full):
+        assert torch.equal(_bits(a), _bits(b))
+    assert bool((ws[size:] == 0xA5).all())

@@ -240,9 +240,14 @@ __device__ __forceinline__ void interleave_mfma_valu() {
 // pair of the tile.  Regions A and D each begin with 2 NB blocks of the next
 // tile's copies, from `blk` on.  The lower subtile is computed even where only
 // the upper one is needed: the diagonal mask then zeroes all of its P and dS.
+// So is a pair that this wave's keys do not see at all; its dV / dK products then
+// read the tile's upper pair (`dbuf` for `buf`), which the wave computes anyway:
+// what a zero P or dS does to those rows is done already, where a row of the
+// masked pair that holds an infinity or NaN would give 0 x NaN.
 template <bool CAUSAL, bool PF, int NB>
 __device__ __forceinline__ void pair_step(const TileCopy& next, int blk, const char* buf,
-                                          int base, uint32_t qb, uint32_t kw, uint32_t mykey,
+                                          const char* dbuf, int base, uint32_t qb, uint32_t kw,
+                                          uint32_t mykey,
                                           int r32, int g, int lane, const bf16x8 (&kf)[8],
                                           const bf16x8 (&vf)[8],
                                           f32x16 (&dva)[4], f32x16 (&dka)[4], Frags& fa) {
@@ -257,7 +262,7 @@ __device__ __forceinline__ void pair_step(const TileCopy& next, int blk, const c
   __builtin_amdgcn_sched_barrier(0);
   next.blocks(blk, 2 * NB);
   subtile_sdp(fa, kf, vf, s1, p1);                                            // A
-  read_dvdk(buf, base + 32, lane, fa);
+  read_dvdk(dbuf, base + 32, lane, fa);
   interleave_mfma_lds<2>();
   __builtin_amdgcn_sched_barrier(0);
   subtile_sdp(fb, kf, vf, s0, p0);                                            // B
@@ -266,7 +271,7 @@ __device__ __forceinline__ void pair_step(const TileCopy& next, int blk, const c
   __builtin_amdgcn_sched_barrier(0);
   subtile_mask<CAUSAL>(q1, mykey, q1 < kw + 31, g, pf1, sf1);
   dvdk_products(fa, pf1, sf1, dva, dka);                                      // C
-  read_dvdk(buf, base, lane, fb);
+  read_dvdk(dbuf, base, lane, fb);
   subtile_pds(s0, p0, pf0, sf0);
   interleave_mfma_valu();
   __builtin_amdgcn_sched_barrier(0);
@@ -466,21 +471,23 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkdv_kernel(
     next.lds = lds0 + ((it + 1) & 1) * KV_STAGE;
     next.rows(lane);
     // Pairs of 32-row subtiles, upper rows first; the upper pair reads the lower
-    // pair's first fragments in its region D.  A pair above the diagonal is
-    // computed too, and masked whole: the waves it concerns would wait for
-    // the others, and a branch round it costs the kernel its registers.
+    // pair's first fragments in its region D.  A pair above the diagonal (only a
+    // lower one can be) is computed too, and masked whole: the waves it concerns
+    // would wait for the others, and a branch round it costs the kernel its
+    // registers.
+    const char* lower = buf + (CAUSAL && qb + 63 < kw ? 64 * HEAD_DIM * 2 : 0);
     Frags fa;
     if (QS == 1) {
       read_sdp(buf, 96, r32, g, fa);
-      pair_step<CAUSAL, true, 1>(next, 0, buf, 64, qb, kw, mykey, r32, g, lane, kf, vf, dva, dka,
-                                 fa);
-      pair_step<CAUSAL, false, 1>(next, 4, buf, 0, qb, kw, mykey, r32, g, lane, kf, vf, dva, dka,
-                                  fa);
+      pair_step<CAUSAL, true, 1>(next, 0, buf, buf, 64, qb, kw, mykey, r32, g, lane, kf, vf, dva,
+                                 dka, fa);
+      pair_step<CAUSAL, false, 1>(next, 4, buf, lower, 0, qb, kw, mykey, r32, g, lane, kf,
+                                  vf, dva, dka, fa);
     } else {
       const int base = 64 * qs;
       read_sdp(buf, base + 32, r32, g, fa);
-      pair_step<CAUSAL, false, 2>(next, 0, buf, base, qb, kw, mykey, r32, g, lane, kf, vf, dva, dka,
-                                  fa);
+      pair_step<CAUSAL, false, 2>(next, 0, buf, qs == 0 ? lower : buf, base, qb, kw, mykey, r32, g,
+                                  lane, kf, vf, dva, dka, fa);
     }
     qt = nq;
     hh = nh;

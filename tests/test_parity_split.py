@@ -226,3 +226,42 @@ def test_block_recomputes_many_heads_in_little_room(S, dm, Hq, Hkv, B):
     for a, b in zip(kept, full):
         assert torch.equal(_bits(a), _bits(b))
     assert bool((ws[size:] == 0xA5).all())
+
+
+# 64-key workgroups (few key blocks), 128-key ones in segments (8 x 32 key blocks),
+# and the walk of a key block by one workgroup (dq over dout).
+@pytest.mark.parametrize("S,Hq,Hkv,over", [(512, 2, 1, False), (4096, 8, 8, False),
+                                           (1000, 4, 2, True), (384, 2, 2, True)])
+@pytest.mark.parametrize("where,value", [("q", float("nan")), ("q", float("inf")),
+                                         ("dout", float("nan")), ("dout", -float("inf"))])
+def test_nonfinite_rows_stay_in_their_half_tile(S, Hq, Hkv, over, where, value):
+    """A query row that holds an infinity or NaN changes dk and dv only of keys it sees
+    or shares a half tile (64 rows) with; later keys keep every bit."""
+    up = _upipe()
+    q, k, v, do = (t.to(DEV) for t in W.attention_inputs(S, Hq, Hkv, 128, 17))
+    o, lse = up.attn_fwd(q, k, v, U=1)
+    ws = up.workspace(up.upipe_attn_bwd_workspace_size(S, Hq, Hkv, 128, 1), DEV)
+
+    def bwd(q, do):
+        dk, dv = torch.empty_like(k), torch.empty_like(v)
+        do = do.clone()
+        dq = do if over else torch.empty_like(q)
+        st = up.upipe_attn_bwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
+                               lse.data_ptr(), do.data_ptr(), dq.data_ptr(), dk.data_ptr(),
+                               dv.data_ptr(), S, Hq, Hkv, 128, 1, 1, ws.data_ptr(), ws.numel(),
+                               torch.cuda.current_stream().cuda_stream)
+        assert st == 0
+        torch.cuda.synchronize()
+        return dk, dv
+
+    clean = bwd(q, do)
+    for r in (0, 10, 63, 64, 127, 130, 191, 192, 255, S - 65):
+        print(f"nonfinite S={S} Hq={Hq} over={over} {where} row {r} {value}", flush=True)
+        x = {"q": q.clone(), "dout": do.clone()}
+        x[where][r, Hq - 1, 5] = value
+        got = bwd(x["q"], x["dout"])
+        first = (r // 64 + 1) * 64
+        # (with q infinite a score may be -inf: p = 0, and dv does not change)
+        assert not all(bool(torch.isfinite(b[:r + 1].float()).all()) for b in got)
+        for a, b in zip(clean, got):
+            assert torch.equal(_bits(a[first:]), _bits(b[first:])), r

@@ -63,7 +63,10 @@ __device__ __forceinline__ void lds_write_b128(char* base, uint32_t off, u32x4 v
 // that was spilled) wrote it; the compiler does not look into the text, so the
 // wait is in it, once for up to four copies (one by one it cost the 8192^3
 // product 861 against 851 us and the dK/dV walks 3 %).  No register results;
-// `lds` is an LDS address (lds_address).
+// `lds` is an LDS address (lds_address).  m0 is not in the clobber lists: the
+// compiler reserves it, warns of such an entry and does not act on it.  It holds
+// no value there between these texts as long as the kernels use none of the
+// instructions that take it (tests/test_build.py looks through the assembly).
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ i32x4 rsrc_words(const void* base, uint32_t bytes) {
   const uint64_t a = (uint64_t)base;

@@ -204,7 +204,28 @@ int run_attn_fwd_ring(const bf16* q, const bf16* k, const bf16* v, bf16* o, floa
                      !overlap(o, q_bytes, k, kv_bytes) && !overlap(o, q_bytes, v, kv_bytes) &&
                      !overlap(lse, lse_bytes, q, q_bytes) &&
                      !overlap(lse, lse_bytes, k, kv_bytes) && !overlap(lse, lse_bytes, v, kv_bytes);
+  const AttnFwdPlan p = plan_attn_fwd_ring(Sq, Skv, Hq, Hkv, U);
+  // All heads of one sequence, or a chunk of them.
+  const int stage = B == 1 ? attn_fwd_half_stage(Sq, Skv, delta, causal) : 0;
+  auto attend = [&](const HeadView& Qb, const HeadView& Kb, const HeadView& Vb, const HeadView& Ob,
+                    float* rows, int nh, int h0, char* room, size_t room_bytes) -> int {
+    if (stage == 0) {
+      UPIPE_LAUNCH(kAttnFwd, st,
+                   launch_attn_fwd(Qb, Kb, Vb, Ob, rows, Sq, Skv, delta, 1, Hq, nh, h0, G, causal,
+                                   parts, st));
+      return UPIPE_OK;
+    }
+    const FwdHalves hv = attn_fwd_halves(stage, Sq, nh, Ob.p != Qb.p ? room : nullptr, room_bytes);
+    UPIPE_LAUNCH(kAttnFwd, st,
+                 launch_attn_fwd_halves(Qb, Kb, Vb, Ob, rows, Sq, Skv, delta, Hq, nh, h0, G, causal,
+                                        hv, st));
+    if (hv.p0 != nullptr)
+      UPIPE_LAUNCH(kSplitMerge, st,
+                   launch_half_merge(hv, Ob, rows + (int64_t)h0 * Sq, Sq, nh, st));
+    return UPIPE_OK;
+  };
   if (rows_addressable(Skv, K.row) && apart) {
+    if (stage > 0) return attend(Q, K, V, O, lse, Hq, 0, ws, p.total);
     // Every tensor in place, all heads of as many sequences as one grid holds.
     const int64_t per_seq = (Sq * parts + 255) / 256 * Hq;
     const int64_t nb = std::max<int64_t>(1, (int64_t(1) << 22) / per_seq);
@@ -221,7 +242,6 @@ int run_attn_fwd_ring(const bf16* q, const bf16* k, const bf16* v, bf16* o, floa
   // so), one sequence after another.  With an overlap nothing may be read after
   // the first write, so chunks of U heads go through the workspace: a chunk's
   // queries are packed, its outputs written back when it is done.
-  const AttnFwdPlan p = plan_attn_fwd_ring(Sq, Skv, Hq, Hkv, U);
   bf16* Kp = (bf16*)(ws + p.Kp);
   bf16* Vp = (bf16*)(ws + p.Vp);
   bf16* Qc = (bf16*)(ws + p.Qc);
@@ -236,9 +256,9 @@ int run_attn_fwd_ring(const bf16* q, const bf16* k, const bf16* v, bf16* o, floa
       Vb = head_major(Vp, p.Skvp);
     }
     if (apart) {
-      UPIPE_LAUNCH(kAttnFwd, st,
-                   launch_attn_fwd(sub(Q, b, 0), Kb, Vb, sub(O, b, 0), lse_b, Sq, Skv, delta, 1, Hq,
-                                   Hq, 0, G, causal, parts, st));
+      const int rc = attend(sub(Q, b, 0), Kb, Vb, sub(O, b, 0), lse_b, Hq, 0, ws + p.Qc,
+                            p.total - p.Qc);
+      if (rc != UPIPE_OK) return rc;
       continue;
     }
     for (int h0 = 0; h0 < Hq; h0 += U) {
@@ -246,10 +266,9 @@ int run_attn_fwd_ring(const bf16* q, const bf16* k, const bf16* v, bf16* o, floa
       float* rows = p.ns > 1 ? (float*)(ws + p.lse_part) : to;
       UPIPE_LAUNCH(kPackRows, st, launch_pack_rows(sub(Q, b, 0).p, Sq, Hq, h0, U, p.Sp, Qc, st));
       // The kernel counts lse rows from head 0 on.
-      UPIPE_LAUNCH(kAttnFwd, st,
-                   launch_attn_fwd(head_major(Qc, p.Sp), Kb, Vb, head_major(Oc, p.Sp),
-                                   rows - (int64_t)h0 * Sq, Sq, Skv, delta, 1, Hq, U, h0, G, causal,
-                                   parts, st));
+      const int rc = attend(head_major(Qc, p.Sp), Kb, Vb, head_major(Oc, p.Sp),
+                            rows - (int64_t)h0 * Sq, U, h0, nullptr, 0);
+      if (rc != UPIPE_OK) return rc;
       UPIPE_LAUNCH(kUnpackRows, st,
                    launch_unpack_rows(Oc, Sq, Hq, h0, U, p.Sp, sub(O, b, 0).p, st));
       if (rows != to)

@@ -51,6 +51,26 @@ hipError_t launch_attn_fwd(const HeadView& Q, const HeadView& K, const HeadView&
 // Parts (1, 2 or 4) into which the waves of a workgroup split the keys of
 // every stage, for a call over Hq heads.
 int attn_fwd_key_parts(int64_t Sq, int64_t Skv, int64_t delta, int Hq, int causal);
+// The same for few queries and many keys (one sequence, Sq <= 128), in two halves
+// of the keys: side by side and then merged, their fp32 outputs in p0, p1, l0 and
+// in O and lse (O is not Q then), or, without that room (p0 == nullptr), one after
+// the other.  Both give the same bits.
+struct FwdHalves {
+  float* p0 = nullptr;     // [rows][128], rows = heads x Sq
+  float* p1 = nullptr;     // [rows][64]
+  float* l0 = nullptr;     // [rows]
+  int stage = 0;           // the second half's first stage of 128 keys
+};
+// That stage, or 0 for calls that take their keys in one piece.
+int attn_fwd_half_stage(int64_t Sq, int64_t Skv, int64_t delta, int causal);
+// Halves of a call over nh heads, side by side if `room` holds their outputs.
+FwdHalves attn_fwd_halves(int stage, int64_t Sq, int nh, char* room, size_t bytes);
+hipError_t launch_attn_fwd_halves(const HeadView& Q, const HeadView& K, const HeadView& V,
+                                  const HeadView& O, float* lse, int64_t Sq, int64_t Skv,
+                                  int64_t delta, int lse_heads, int nh, int h0, int G, int causal,
+                                  const FwdHalves& hv, hipStream_t st);
+hipError_t launch_half_merge(const FwdHalves& hv, const HeadView& O, float* lse, int64_t Sq, int nh,
+                             hipStream_t st);
 // In place, per row (s, h) of o [S, H, d] and lse [H, S]: fold the partial
 // result (o_p, lse_p) over a disjoint key set into (o, lse).
 hipError_t launch_lse_merge(bf16* o, float* lse, const bf16* o_p,

@@ -265,3 +265,46 @@ def test_nonfinite_rows_stay_in_their_half_tile(S, Hq, Hkv, over, where, value):
         assert not all(bool(torch.isfinite(b[:r + 1].float()).all()) for b in got)
         for a, b in zip(clean, got):
             assert torch.equal(_bits(a[first:]), _bits(b[first:])), r
+
+
+# Sq, Skv, Hq, Hkv, offset of the queries, causal: up to 128 queries and more than
+# 8192 visible keys take the keys in two halves.  One key/value head of a length
+# that is a multiple of 128 leaves little workspace: with few heads a chunk the
+# halves run one after the other, with all of them (and with packed keys' room)
+# side by side.  The last rows end where the second half begins, or see no key.
+HALVES = [(1, 8193, 1, 1, 8192, True), (128, 8320, 4, 1, 8320, True), (33, 8448, 8, 2, 9000, True),
+          (64, 9000, 4, 4, 8200, True), (65, 16384, 2, 1, 8150, True), (128, 8300, 2, 1, 0, False),
+          (100, 8321, 64, 1, 8321, True), (128, 8192, 2, 1, 8192, True),
+          (127, 12288, 2, 1, 8064, True), (128, 30000, 2, 1, -60, True)]
+
+
+@pytest.mark.parametrize("Sq,Skv,Hq,Hkv,off,causal", HALVES)
+def test_forward_key_halves(Sq, Skv, Hq, Hkv, off, causal):
+    """Against the oracle (tol.py's bars), bitwise equal for every U and with o in the
+    place of q, which always takes the halves one after the other."""
+    up = _upipe()
+    q, k, v = _qkv(Sq, Skv, Hq, Hkv, Sq + Skv)
+    o_ref, lse_ref = R.attn_fwd_offset(as64(q), as64(k), as64(v), off, causal)
+    empty = np.isneginf(lse_ref)
+    q, k, v = (t.to(DEV) for t in (q, k, v))
+    first = None
+    for U in [u for u in range(1, Hq + 1) if Hq % u == 0]:
+        print(f"key halves Sq={Sq} Skv={Skv} Hq={Hq} Hkv={Hkv} off={off} U={U}", flush=True)
+        ws = up.workspace(up.upipe_attn_fwd_ring_workspace_size(Sq, Skv, Hq, Hkv, 128, U), DEV)
+        ws.fill_(0xFF)
+        o, lse = up.attn_fwd_ring(q, k, v, off, 0, causal=causal, U=U, ws=ws)
+        qo, lse2 = q.clone(), torch.empty_like(lse)
+        assert up.upipe_attn_fwd_ring(qo.data_ptr(), k.data_ptr(), v.data_ptr(), qo.data_ptr(),
+                                      lse2.data_ptr(), Sq, Skv, off, 0, Hq, Hkv, 128, int(causal),
+                                      U, ws.data_ptr(), ws.numel(),
+                                      torch.cuda.current_stream().cuda_stream) == 0
+        torch.cuda.synchronize()
+        if first is None:
+            first = (o, lse)
+            lse_np = lse.cpu().double().numpy()
+            assert_close("o", o.cpu(), o_ref)
+            assert np.array_equal(np.isneginf(lse_np), empty)
+            assert_close("lse", torch.from_numpy(np.where(empty, 0.0, lse_np)),
+                         np.where(empty, 0.0, lse_ref))
+        for a, b, c in zip(first, (o, lse), (qo, lse2)):
+            assert torch.equal(_bits(a), _bits(b)) and torch.equal(_bits(a), _bits(c)), U

@@ -154,10 +154,10 @@ def test_ring_step_validation_and_workspace():
     assert _ring(k=None) == INV
     assert _ring(lse=FAKE + 4) == INV
     assert _ring(ws_bytes=1024) == WS
-    # K, V packed at the key length; Q, O chunk buffers at the query length.
-    # Few query blocks (at most 128 of 256 rows) and at least two key stages:
-    # the key range is split in two, with a second O buffer and fp32 lse rows
-    # for both halves.
+    # The sizes that callers may have saved: K, V packed at the key length; Q, O
+    # chunk buffers at the query length.  Few query blocks (at most 128 of 256
+    # rows) and at least two key stages: a second O buffer and fp32 lse rows, for
+    # the key range in two halves.
     qh, kh = 512 * 128 * 2, 384 * 128 * 2
     # One key/value head and 384 = 3 x 128 keys: K, V are read in place.
     for U in (1, 2, 4):
@@ -165,7 +165,7 @@ def test_ring_step_validation_and_workspace():
             U * qh + 2 * U * qh + 2 * U * 512 * 4
         assert upipe.upipe_attn_fwd_ring_workspace_size(512, 384, 4, 2, 128, U) == \
             2 * 2 * kh + U * qh + 2 * U * qh + 2 * U * 512 * 4
-    # a single key stage: no split
+    # a single key stage: no second one
     assert upipe.upipe_attn_fwd_ring_workspace_size(512, 128, 4, 1, 128, 1) == 2 * qh
     # a ragged key length is packed (padded) once
     assert upipe.upipe_attn_fwd_ring_workspace_size(512, 100, 4, 1, 128, 1) == \
@@ -203,10 +203,10 @@ def test_workspace_sizes_follow_the_plan():
         carry2 = 8 * head if U < 2 else 0
         assert upipe.upipe_attn_bwd_workspace_size(S, 4, 2, d, U) == \
             4 * head + carry2 + 3 * U * head + 2 * U * Sp * 4
-    # padding of a ragged length to the 128-row granule (one key stage: no split)
+    # padding of a ragged length to the 128-row granule (one key stage)
     assert upipe.upipe_attn_fwd_workspace_size(1, 1, 1, d, 1) == 4 * 128 * d * 2
-    # 32768 rows = 128 query blocks of 256: keys split in two; one row more
-    # makes 129 blocks: no split
+    # 32768 rows = 128 query blocks of 256: room for two halves of the keys; one
+    # row more makes 129 blocks: none
     s32 = 32768 * d * 2
     assert upipe.upipe_attn_fwd_workspace_size(32768, 4, 1, d, 1) == \
         s32 + 2 * s32 + 2 * 32768 * 4

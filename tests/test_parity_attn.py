@@ -68,14 +68,13 @@ SHAPES = [
     (1, 1, 1, True),
     (17, 2, 1, True),
     (129, 4, 1, True),
-    (300, 6, 3, True),      # groups of 2 split by U = 3 (carried dK/dV)
+    (300, 6, 3, True),      # groups of 2 that U = 3 splits (the workspace holds carries)
     (1000, 8, 2, True),
     (200, 4, 4, True),
     (257, 2, 1, False),
     (96, 4, 2, False),
-    (2500, 4, 2, False),    # many tiles, ragged tail; the forward splits its key range
-    (4100, 8, 2, True),     # U = 2: carried per-head dK/dV; U = 4: one group per launch;
-                            # U = 8: two groups per launch
+    (2500, 4, 2, False),    # many tiles, ragged tail; waves split the keys of a stage
+    (4100, 8, 2, True),     # dK/dV of both groups in one launch, in segments, for every U
 ]
 
 

@@ -6,8 +6,7 @@ offsets (rows that see no key, the diagonal, fully visible blocks),
 non-causal blocks, grouped heads and every chunk size U; the merge on random
 partials including empty rows; full causal attention rebuilt on the GPU
 from ring steps over key blocks plus merges; and the full-size ring step of
-the Llama3-8B share (32K queries against 32K keys, the forward's key range
-split in two), on sampled rows."""
+the Llama3-8B share (32K queries against 32K keys), on sampled rows."""
 
 import numpy as np
 import pytest

@@ -2,12 +2,14 @@
 
 Forward: a stage's keys are split into 1, 2 or 4 parts by the number of 256-row
 query blocks times heads, and keys and values are packed only when one head's
-token-major rows span 2^32 bytes.  Query counts end one row into a block, on it
-and before it; the key ranges are short, so the oracle stays cheap.
+token-major rows span 2^32 bytes; up to 128 queries take more than 8192 keys in
+two halves.  Query counts end one row into a block, on it and before it; the key
+ranges are short, so the oracle stays cheap.
 
 Backward: dK/dV cuts the walk over a key block's query tiles into segments,
 with 128 or 64 keys a workgroup, and dQ splits keys like the forward; tensors
-that overlap an output take the path that packs them.
+that overlap an output take the path that packs them (test_parity_overlap.py), and
+so do long ones (test_parity_long.py).
 
 Products: 256 x 256 or 128 x 128 tiles by how they fill the chip."""
 

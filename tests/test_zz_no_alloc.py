@@ -36,8 +36,8 @@ def _noalloc(up, q, k, v, causal, U):
 
 
 @pytest.mark.parametrize("first,second", [
-    ((8192, 4, 1, True, 1), (1000, 2, 1, True, 2)),     # in place K/V, then packed, ragged
-    ((4100, 8, 2, True, 4), (384, 4, 4, False, 1)),     # split key range, then non-causal
+    ((8192, 4, 1, True, 1), (1000, 2, 1, True, 2)),     # one K/V head, then ragged
+    ((4100, 8, 2, True, 4), (384, 4, 4, False, 1)),     # two K/V heads, then non-causal
 ])
 def test_noalloc_matches_workspace_call_twice(first, second):
     up = _upipe()
@@ -55,7 +55,7 @@ def test_noalloc_rejects_shapes_beyond_its_scratch():
     up = _upipe()
     cap = up.upipe_attn_fwd_noalloc_scratch_bytes()
     assert cap == 64 << 20
-    S = 1 << 20   # K, V in place but Q and O chunks alone need 512 MiB
+    S = 1 << 20   # the forward's workspace: 512 MiB for the Q and O of a chunk
     assert up.upipe_attn_fwd_workspace_size(S, 4, 1, 128, 1) > cap
     fake = 1 << 20
     assert up.upipe_attn_fwd_noalloc(fake, fake, fake, fake, fake, S, 4, 1, 128, 1, 1,

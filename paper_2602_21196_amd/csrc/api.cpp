@@ -316,7 +316,9 @@ int run_attn_bwd(const bf16* q, const bf16* k, const bf16* v, const bf16* o,
     apart = apart && !overlap(dq, q_bytes, in, kv_bytes) && !overlap(dk, kv_bytes, in, kv_bytes) &&
             !overlap(dv, kv_bytes, in, kv_bytes);
 
-  if (S < kPerHeadRows && rows_addressable(S, std::max(Q.row, K.row)) && apart) {
+  static_assert(kPerHeadRows * kMaxHeads * HEAD_DIM * 2 < (int64_t(1) << 32),
+                "rows below kPerHeadRows are rows_addressable");
+  if (S < kPerHeadRows && apart) {
     // Every tensor in place.  dK/dV of all heads of a sequence in one launch,
     // cut into segments that run side by side: their slots lie behind the
     // rows and in dq, which is written last.  Cut for the smallest workspace

@@ -46,10 +46,6 @@ __device__ __forceinline__ bf16x8 lds_read_b128(const char* base, uint32_t off) 
   return *reinterpret_cast<const bf16x8*>(base + off);
 }
 
-__device__ __forceinline__ void lds_write_b128(char* base, uint32_t off, u32x4 v) {
-  *reinterpret_cast<u32x4*>(base + off) = v;
-}
-
 // Buffer -> LDS copy of 16 bytes per lane (buffer_load_dwordx4 ... lds): the
 // bytes at voff + soff (lane offset + uniform offset) of lane L land at LDS
 // address lds + 16 * L, zeros where that offset is past the resource's bytes.  No

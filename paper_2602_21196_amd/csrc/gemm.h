@@ -59,25 +59,23 @@ struct GemmEpilogue {
   int64_t m_store;
   // GEMM_EPI_PARTIAL: split s of the k range writes partial[s][M][N] fp32.
   float* partial;
-  // k extent, counted from k_begin (splits beyond it are clamped).
+  // k extent (splits beyond it are clamped).
   int64_t k_total;
 };
 
-// M and N must be multiples of 128.  The k range [k_begin, k_begin + k_total)
-// is cut into `splits` pieces of k_len; k_begin and k_len are multiples of
-// 128, and so is k_total when an operand is K-major (hipErrorInvalidValue
-// otherwise).  Supported
+// M and N must be multiples of 128.  The k range [0, k_total) is cut into
+// `splits` pieces of k_len, a multiple of 128, and so is k_total when an operand
+// is K-major (hipErrorInvalidValue otherwise).  Supported
 // combinations: (A K-major, B MN-major, HEADS | STORE), (A K-major, B K-major,
 // HEADS | STORE), (A MN-major, B MN-major, PARTIAL).
 hipError_t launch_gemm(const GemmOperand& A, bool a_kmajor, const GemmOperand& B, bool b_kmajor,
-                       const GemmEpilogue& E, int epi, int64_t M, int64_t N, int64_t k_begin,
-                       int64_t k_len, int splits, hipStream_t st);
+                       const GemmEpilogue& E, int epi, int64_t M, int64_t N, int64_t k_len,
+                       int splits, hipStream_t st);
 
 // t = sum_s partial[s][m][n] in ascending s, plus acc32[m][n] unless first;
-// t goes to acc32[m][n] unless last, else out[m * ldo + col0 + n] = bf16(t).
+// t goes to acc32[m][n] unless last, else out[m * ldo + n] = bf16(t).
 // (first = last = 1 never touches acc32.)
 hipError_t launch_reduce_splitk(const float* partial, int splits, int64_t M, int64_t N, bf16* out,
-                                int64_t ldo, int64_t col0, float* acc32, int first, int last,
-                                hipStream_t st);
+                                int64_t ldo, float* acc32, int first, int last, hipStream_t st);
 
 }  // namespace upipe

@@ -128,8 +128,7 @@ struct Shape {
 
 template <bool A_K, bool B_K, int EPI, int BM, int BN>
 __global__ __launch_bounds__((64 * Shape<BM, BN>::W), 2) void gemm_kernel(
-    GemmOperand A, GemmOperand B, GemmEpilogue E, int64_t M, int64_t N, int64_t k_begin,
-    int64_t k_len) {
+    GemmOperand A, GemmOperand B, GemmEpilogue E, int64_t M, int64_t N, int64_t k_len) {
   using H = Shape<BM, BN>;
   using TA = Tile<A_K, BM, H::W>;
   using TB = Tile<B_K, BN, H::W>;
@@ -158,9 +157,9 @@ __global__ __launch_bounds__((64 * Shape<BM, BN>::W), 2) void gemm_kernel(
   const int64_t band = tile / (8 * tiles_n), in = tile % (8 * tiles_n);
   const int64_t bh = tiles_m - 8 * band < 8 ? tiles_m - 8 * band : 8;
   const int64_t m0 = (8 * band + in % bh) * BM, n0 = (in / bh) * BN;
-  const int64_t kb0 = k_begin + split * k_len;
+  const int64_t kb0 = split * k_len;
   int64_t kend = kb0 + k_len;
-  if (kend > k_begin + E.k_total) kend = k_begin + E.k_total;
+  if (kend > E.k_total) kend = E.k_total;
   const int nk = kend > kb0 ? (int)((kend - kb0 + BK - 1) / BK) : 0;
 
   f32x16 acc[MT][2];
@@ -278,12 +277,12 @@ __global__ __launch_bounds__((64 * Shape<BM, BN>::W), 2) void gemm_kernel(
 
 // t = sum over splits s = 0.. of partial[s][m][n], summed in ascending s,
 // then added to acc32[m][n] unless `first`; the total goes to acc32 unless
-// `last`, else to out[m * ldo + col0 + n] as bf16.  HBM-bound: a thread has four
+// `last`, else to out[m * ldo + n] as bf16.  HBM-bound: a thread has four
 // consecutive columns (N is a multiple of 128).
 __global__ __launch_bounds__(256) void reduce_splitk_kernel(const float* __restrict__ partial,
                                                             int splits, int64_t M, int64_t N,
                                                             bf16* __restrict__ out, int64_t ldo,
-                                                            int64_t col0, float* __restrict__ acc32,
+                                                            float* __restrict__ acc32,
                                                             int first, int last) {
   const int64_t idx = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
   if (idx >= M * N) return;
@@ -296,7 +295,7 @@ __global__ __launch_bounds__(256) void reduce_splitk_kernel(const float* __restr
     bf16x4 v;
 #pragma unroll
     for (int e = 0; e < 4; ++e) v[e] = (bf16)s[e];
-    *reinterpret_cast<bf16x4*>(out + m * ldo + col0 + n) = v;
+    *reinterpret_cast<bf16x4*>(out + m * ldo + n) = v;
   } else {
     *reinterpret_cast<f32x4*>(acc32 + idx) = s;
   }
@@ -304,22 +303,22 @@ __global__ __launch_bounds__(256) void reduce_splitk_kernel(const float* __restr
 
 template <bool A_K, bool B_K, int EPI, int BM, int BN>
 hipError_t launch_t(const GemmOperand& A, const GemmOperand& B, const GemmEpilogue& E, int64_t M,
-                    int64_t N, int64_t k_begin, int64_t k_len, int splits, hipStream_t st) {
+                    int64_t N, int64_t k_len, int splits, hipStream_t st) {
   dim3 grid((unsigned)(((M + BM - 1) / BM) * ((N + BN - 1) / BN)), (unsigned)splits);
   hipLaunchKernelGGL((gemm_kernel<A_K, B_K, EPI, BM, BN>), grid, dim3(64 * Shape<BM, BN>::W), 0, st,
-                     A, B, E, M, N, k_begin, k_len);
+                     A, B, E, M, N, k_len);
   return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_gemm(const GemmOperand& A, bool a_kmajor, const GemmOperand& B, bool b_kmajor,
-                       const GemmEpilogue& E, int epi, int64_t M, int64_t N, int64_t k_begin,
-                       int64_t k_len, int splits, hipStream_t st) {
+                       const GemmEpilogue& E, int epi, int64_t M, int64_t N, int64_t k_len,
+                       int splits, hipStream_t st) {
   // A K-major tile reads 64 consecutive k of each row: the k range must be
   // made of whole tiles (an MN-major operand is bounded by its buffer
   // resource instead); pieces must start on tile boundaries.
-  if ((M % 128) || (N % 128) || (k_len % 128) || (k_begin % 128)) return hipErrorInvalidValue;
+  if ((M % 128) || (N % 128) || (k_len % 128)) return hipErrorInvalidValue;
   if ((a_kmajor || b_kmajor) && (E.k_total % 128)) return hipErrorInvalidValue;
   // Rounds on 256 CUs: a 256 x 256 tile takes 0.8 of four 128 x 128 ones, two of
   // which run side by side (us, 128 | 256: 8192 x 4096 x 4096 271 | 220; 65536 x 1280 x
@@ -330,8 +329,8 @@ hipError_t launch_gemm(const GemmOperand& A, bool a_kmajor, const GemmOperand& B
   const bool large = 1.6 * ((big + 255) / 256) < (small + 511) / 512;
 #define UPIPE_GEMM_CASE(AK, BK_, EP)                                                            \
   if (a_kmajor == AK && b_kmajor == BK_ && epi == EP)                                           \
-    return large ? launch_t<AK, BK_, EP, 256, 256>(A, B, E, M, N, k_begin, k_len, splits, st)   \
-                 : launch_t<AK, BK_, EP, 128, 128>(A, B, E, M, N, k_begin, k_len, splits, st);
+    return large ? launch_t<AK, BK_, EP, 256, 256>(A, B, E, M, N, k_len, splits, st)            \
+                 : launch_t<AK, BK_, EP, 128, 128>(A, B, E, M, N, k_len, splits, st);
   UPIPE_GEMM_CASE(true, false, GEMM_EPI_HEADS)     // X . Wqkv
   UPIPE_GEMM_CASE(true, false, GEMM_EPI_STORE)     // O . Wo
   UPIPE_GEMM_CASE(true, true, GEMM_EPI_HEADS)      // dY . Wo^T
@@ -342,11 +341,10 @@ hipError_t launch_gemm(const GemmOperand& A, bool a_kmajor, const GemmOperand& B
 }
 
 hipError_t launch_reduce_splitk(const float* partial, int splits, int64_t M, int64_t N, bf16* out,
-                                int64_t ldo, int64_t col0, float* acc32, int first, int last,
-                                hipStream_t st) {
+                                int64_t ldo, float* acc32, int first, int last, hipStream_t st) {
   const int64_t n = M * N;
   hipLaunchKernelGGL(reduce_splitk_kernel, dim3((unsigned)((n + 1023) / 1024)), dim3(256), 0, st,
-                     partial, splits, M, N, out, ldo, col0, acc32, first, last);
+                     partial, splits, M, N, out, ldo, acc32, first, last);
   return hipGetLastError();
 }
 

@@ -208,7 +208,7 @@ GemmEpilogue store_epi(bf16* out, int64_t ldo, int64_t m_store) {
 hipError_t gemm1(const GemmOperand& A, bool ak, const GemmOperand& B, bool bk, GemmEpilogue E,
                  int epi, int64_t M, int64_t N, int64_t K, hipStream_t st) {
   E.k_total = K;
-  return launch_gemm(A, ak, B, bk, E, epi, M, N, 0, round_up(K, 128), 1, st);
+  return launch_gemm(A, ak, B, bk, E, epi, M, N, round_up(K, 128), 1, st);
 }
 
 }  // namespace
@@ -294,10 +294,10 @@ int run_layer_bwd_seq(const bf16* x, const bf16* wqkv, const bf16* wo, const bf1
     e.k_total = S;
     const int splits = (int)((S + len - 1) / len);
     UPIPE_LAUNCH(kGemmWgrad, st,
-                 launch_gemm(A, false, B, false, e, GEMM_EPI_PARTIAL, M, N, 0, len, splits, st));
+                 launch_gemm(A, false, B, false, e, GEMM_EPI_PARTIAL, M, N, len, splits, st));
     UPIPE_LAUNCH(kReduceSplitk, st,
-                 launch_reduce_splitk(e.partial, splits, M, N, out, ldo, 0, (float*)(ws + acc32),
-                                      first, last, st));
+                 launch_reduce_splitk(e.partial, splits, M, N, out, ldo, (float*)(ws + acc32), first,
+                                      last, st));
     return UPIPE_OK;
   };
 

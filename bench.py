@@ -1,8 +1,8 @@
 """Benchmark: head-chunked causal GQA attention fwd+bwd on one MI355X.
 
 One step = one pass of the whole hot path over one batch of synthetic input:
-upipe_attn_fwd followed by upipe_attn_bwd (pack, flash forward, unpack,
-backward pre-pass, dK/dV, dQ, unpack, for every head chunk) on the
+upipe_attn_fwd followed by upipe_attn_bwd (flash forward of all heads; per head
+chunk the packing, row terms and dK/dV; dQ of all heads) on the
 Llama3-8B per-GPU share at 8-way Ulysses (S = 131072, 4 query heads, 1 kv
 head, d = 128), inputs resident in HBM.  Prints one JSON line.
 `--workload qwen32b_share|llama8b_4m|tiny` times the other attention
@@ -192,7 +192,8 @@ def workspace_model_gb(S, Hq, Hkv, d, U):
     workspaces): resident packed K, V (none when one key/value head of a
     length that is a multiple of 128 is read in place), fp32 dK, dV carries
     when a key/value group spans chunks, and, per chunk head, Q, dO, dQ
-    (bf16) and lse, D."""
+    (bf16) and lse, D: the bytes that a call asks for (dQ's room holds the row
+    terms of all heads where dQ is written in place)."""
     Sp = (S + 127) // 128 * 128
     G = Hq // Hkv   # a group spans chunks when its first and last heads differ in h // U
     carry = any((g * G) // U != ((g + 1) * G - 1) // U for g in range(Hkv))
@@ -432,7 +433,8 @@ def main():
                                       "r2": round(r2, 4)}
         out["peak_activation_note"] = (
             "max_memory_allocated during one fwd+bwd above the resident "
-            "inputs, minus the outputs o, lse, dq, dk, dv: the workspaces; "
+            "inputs, minus the outputs o, lse, dq, dk, dv: the workspaces that "
+            "the calls ask for (below 65536 rows chunk buffers are in part unused); "
             "the model drops the fp32 dK/dV carries once U is a multiple of "
             "the group size, so the fit over all U is not exactly linear")
         out["tflops_vs_U"] = sweep_tf
@@ -449,9 +451,10 @@ def layer_sweep(args, w, x, wqkv, wo, dy, rope_base, step_flops):
     the resident inputs (x, weights, dY), minus the caller-owned outputs (y,
     final_out, lse, dX, dWqkv, dWo): the two workspaces and the kept
     attention output's lifetime overlap, as a training step would see them.
-    Only the U-dependent chunk buffers change with U (per chunk head the
-    projected Q, the recomputed output and the fp32 lse, D rows), and the
-    dK/dV fp32 carries while a key/value group spans chunks."""
+    Only the chunk buffers that the size query counts change with U (per chunk
+    head Q, the recomputed output and the fp32 lse, D rows), and the dK/dV fp32
+    carries while a key/value group spans chunks; the block runs all heads
+    together and uses that room for recomputed outputs, if for anything."""
     import torch
     from paper_2602_21196_amd import upipe
     S, Hq, Hkv, d, dm = w.S, w.Hq, w.Hkv, w.d, w.d_model

@@ -6,7 +6,10 @@
  * sequence S for its share of heads: Hq query heads and Hkv key/value heads,
  * head width d.  UPipe (Section 3.3) runs the attention block over those heads
  * in nu = Hq/U chunks of U heads, reusing one chunk-sized set of buffers for
- * every chunk, so activation scratch grows with U rather than with Hq.  Query
+ * every chunk, so activation scratch grows with U rather than with Hq.  On one
+ * GPU no all-to-all stands between the stages: where every head can be read and
+ * written in place, all of them go in one launch, and the library works in
+ * chunks of U only where rows are packed (see each call).  Query
  * head h reads key/value head h / (Hq/Hkv) (grouped-query attention, Section
  * 2.1; chunks follow the GQA schedule of Section 4.1, which on one device is
  * ascending local head order).
@@ -21,26 +24,37 @@
  *    memory in the compute entry points; every kernel is enqueued on the
  *    caller's `stream`, and the calls return as soon as the work is queued.
  *  - Workspace: each compute call takes a caller-allocated device workspace of
- *    at least the size returned by its *_workspace_size query.  It holds the
- *    chunk-sized buffers that are reused for every chunk plus the buffers
- *    that live for the whole call; its contents on entry are ignored.
+ *    at least the size returned by its *_workspace_size query.  It has room for
+ *    chunk-sized buffers that are reused for every chunk plus the buffers that
+ *    live for the whole call; its contents on entry are ignored, and a call
+ *    that works in place may leave part of it, or all, unused.
  *  - Outputs are overwritten, never accumulated into.
+ *  - Outputs in the place of inputs: give separate tensors.  An attention call
+ *    whose output overlaps an input (o over q, dq over dout, dk over q, ...)
+ *    packs its rows and writes the results of one chunk of U heads after the
+ *    next, so it is right as long as no chunk, and no sequence of a batch,
+ *    overwrites what a later one reads: always with U = Hq and B = 1, except
+ *    that with Hkv = 1 and S % 128 == 0, where k and v are not packed, dk and dv
+ *    must not lie over k or v.  (o equal to q costs no packing.)  The block's
+ *    o_saved may lie over x or wqkv with U = Hq.
  *  - Scale: scores are q.k / sqrt(d) (Section 2.1); there is no scale knob.
  *  - Causal: key j is visible to query i iff j <= i.  causal = 0 gives full
  *    (bidirectional) attention over all S keys.
  *  - Determinism: for fixed shapes every output is bitwise identical across
- *    calls and across every valid U (one fixed reduction order: query heads
- *    ascending, then query tiles descending; fp32 partial sums are carried
- *    between chunks through the workspace; whether the forward splits a
- *    query block's key range in two depends on the lengths only).
+ *    calls and across every valid U, and a sequence of a batch gives what it
+ *    gives alone.  The order of the fp32 sums (how a query block's keys and a
+ *    key block's query tiles are split) follows from the lengths and the head
+ *    counts Hq and Hkv, so a head may differ in its last bits between calls
+ *    over different numbers of heads.  dk and dv of a call with an output over
+ *    an input may differ in their last bits from those of separate tensors.
  *  - Errors: arguments are validated on the host before anything is
  *    enqueued; a failing call enqueues nothing and returns a negative
  *    upipe_status.  A launch failure returns UPIPE_ERR_HIP (work queued
  *    before it stays queued).  Faults inside kernels surface at the caller's
  *    next synchronisation.  No C++ exception crosses this interface.
- *  - Supported shapes: d == 128; S >= 1 (any length: rows past the last tile
- *    are padded inside the workspace); 1 <= Hkv <= Hq, Hkv | Hq; 1 <= U,
- *    U | Hq; Hq <= 64; S * max(Hq, d_model/128) * d < 2^40.  The batched
+ *  - Supported shapes: d == 128; S >= 1 (any length: kernels stop at the last
+ *    row, packed rows are padded to 128 with zeros); 1 <= Hkv <= Hq, Hkv | Hq;
+ *    1 <= U, U | Hq; Hq <= 64; S * max(Hq, d_model/128) * d < 2^40.  The batched
  *    calls need B >= 1 and B times one sequence's largest tensor below
  *    2^61 elements (UPIPE_ERR_INVALID_ARG otherwise).
  *  - Thread safety: calls are reentrant across host threads and streams as
@@ -95,12 +109,15 @@ int upipe_gqa_schedule(int H, int Hkv, int C, int U, int* stage_heads,
                        int* kv_stage);
 
 /* ------------------------------------------------------------------------
- * Workspace size queries.  Return the byte count the matching compute call
- * needs for these shapes, or 0 if the shapes are invalid or unsupported.
- * The size is  fixed(S, Hkv[, d_model]) + U * per_head(S)  (chunk buffers).
- * It does not depend on the batch size B: the calls that take a batch of B
- * sequences run them one after another through the same workspace.  The
- * attention calls keep no key/value copy when Hkv == 1 and S % 128 == 0.
+ * Workspace size queries.  Return the byte count that the matching compute
+ * call asks for with these shapes, or 0 if the shapes are invalid or
+ * unsupported.  The size is  fixed(S, Hkv[, d_model]) + U * per_head(S), where
+ * per_head is one head's chunk buffers: reserved for the calls that pack rows
+ * (the forward's and the block's chunks are otherwise unused; the backward
+ * uses the room for row terms and partial sums).  It does not depend on the
+ * batch size B: what a batch needs beyond one sequence's workspace lies in the
+ * caller's tensors.  The attention calls reserve no key/value copy when
+ * Hkv == 1 and S % 128 == 0.
  * ---------------------------------------------------------------------- */
 size_t upipe_attn_fwd_workspace_size(int64_t S, int Hq, int Hkv, int d, int U);
 size_t upipe_attn_bwd_workspace_size(int64_t S, int Hq, int Hkv, int d, int U);
@@ -123,7 +140,8 @@ size_t upipe_layer_bwd_workspace_size(int64_t S, int d_model, int Hq, int Hkv,
  * q, k, v are read and o (`final_out`) is written in place, all heads in one
  * launch, and the result does not depend on U.  Only when the k rows of one
  * head span 2^32 bytes or more (S rounded up to 128, times Hkv * 256 bytes)
- * are k and v packed head-major into the workspace first.
+ * are k and v packed head-major into the workspace first, and chunks of U
+ * heads go through it when an output overlaps an input.
  * ---------------------------------------------------------------------- */
 int upipe_attn_fwd(const void* q, const void* k, const void* v, void* o,
                    float* lse, int64_t S, int Hq, int Hkv, int d, int causal,
@@ -176,10 +194,11 @@ int upipe_attn_fwd_noalloc(const void* q, const void* k, const void* v, void* o,
  *                           scores
  * With causal = 1, key j is visible to query i iff kv_offset + j <=
  * q_offset + i; with causal = 0 every key is.  A row that sees no key gets
- * o = 0 and lse = -inf (the empty set, neutral for the merge).  Head chunking
- * by U as for upipe_attn_fwd; with Sq = Skv and q_offset = kv_offset this is
- * upipe_attn_fwd.  |offsets| <= 2^62 and q_offset - kv_offset < 2^63
- * (UPIPE_ERR_INVALID_ARG otherwise); workspace from
+ * o = 0 and lse = -inf (the empty set, neutral for the merge).  The workspace
+ * and U are as for upipe_attn_fwd (up to 128 queries on more than 8192 keys also
+ * keep fp32 outputs of two halves of the keys in it, and in o); with Sq = Skv
+ * and q_offset = kv_offset this is upipe_attn_fwd.  |offsets| <= 2^62 and
+ * q_offset - kv_offset < 2^63 (UPIPE_ERR_INVALID_ARG otherwise); workspace from
  * upipe_attn_fwd_ring_workspace_size (0 for invalid shapes).
  * ---------------------------------------------------------------------- */
 size_t upipe_attn_fwd_ring_workspace_size(int64_t Sq, int64_t Skv, int Hq, int Hkv,
@@ -215,8 +234,9 @@ int upipe_lse_merge(void* o, float* lse, const void* o_part, const float* lse_pa
  * `lse` must come from upipe_attn_fwd on the same q, k, v (it is used to
  * rebuild the probabilities without a second softmax pass).  Below 65536 rows
  * every tensor is used in place, all heads together, and dq serves as scratch
- * before it is written; from there on, chunks of U heads are packed head-major
- * for dk and dv.
+ * before it is written; from there on, and where an output overlaps an input,
+ * chunks of U heads are packed head-major for dk and dv (and for dq in the
+ * second case).
  * ---------------------------------------------------------------------- */
 int upipe_attn_bwd(const void* q, const void* k, const void* v, const void* o,
                    const float* lse, const void* dout, void* dq, void* dk,

@@ -1,10 +1,11 @@
 // C ABI of the head-chunked attention library (declared in include/upipe.h).
 //
 // Host-side responsibilities: argument validation before anything is
-// enqueued, the workspace plan (one chunk-sized set of buffers reused for
-// every chunk, plus the buffers that live for the whole call), the chunk loop
-// of UPipe (paper Section 3.3: nu = Hq/U stages of U heads), and optional
-// per-kernel event timing.  All kernels run on the caller's stream.
+// enqueued, the workspace plan, the route of a call (all heads in place in one
+// launch; or, for dK/dV from 65536 rows on and wherever an output overlaps an
+// input, the chunks of U heads of UPipe, paper Section 3.3, through one
+// chunk-sized set of buffers), and optional per-kernel event timing.  All
+// kernels run on the caller's stream.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <string.h>
@@ -364,8 +365,9 @@ int run_attn_bwd(const bf16* q, const bf16* k, const bf16* v, const bf16* o,
   }
 
   // Long sequences: dK/dV of one head fills the chip, and walks its Q and dO
-  // rows 1 - 3.5 % faster where they are packed (131072 rows of 4 heads 33.4
-  // against 34.6 ms; rows 1 KB apart use 4 of an L2's 16 channels).  So chunks
+  // rows 1 - 3.5 % faster where they are packed (measured before its copies went
+  // out between products, 131072 rows of 4 heads 33.4 against 34.6 ms; rows 1 KB
+  // apart use 4 of an L2's 16 channels).  So chunks
   // of U heads are packed for it, and dQ takes all heads in place after the
   // last one, if the rows of all heads fit behind the packed ones.
   // Where an output overlaps an input (any length), nothing of a chunk may be

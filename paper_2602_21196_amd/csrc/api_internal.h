@@ -114,7 +114,10 @@ int run_dkdv(const HeadView& Q, const HeadView& dO, const float* lse_c, const fl
 // From this length on a head's 128-key blocks alone fill the 256 CUs evenly
 // (512 of them, the longest running beside the shortest): dK/dV runs head
 // by head.  Below, all heads in one launch, in segments (dkdv_split): 32768
-// rows of 8 heads 7.04 -> 4.40 ms; 65536 rows 17.3 against 17.7 ms in segments.
+// rows of 8 heads 7.0 -> 4.0 ms.  The line was drawn when segments took 17.7 ms
+// at 65536 rows of 8 heads and head by head 17.3; since the copies go out between
+// products it is 15.7 against 16.0 (17.2 for the 8 heads of one group in one
+// launch), and at 131072 rows of 4 heads 31.1 against 31.7 (one box).
 constexpr int64_t kPerHeadRows = 65536;
 // Sequence b and head u of a view, as a view that starts there.
 HeadView sub(HeadView x, int64_t b, int64_t u);

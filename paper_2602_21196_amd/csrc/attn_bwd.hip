@@ -26,7 +26,7 @@
 // What bounds them: at full chip, MFMA issue (dK/dV) and the power limit (dQ);
 // short of 512 key blocks or 256-row blocks, the chip's filling.  Against one
 // launch per chunk on packed copies, whole backward, one key/value head:
-// 8192 rows of 4 heads 1930 -> 335 us, 32768 of 8 14.5 -> 7.1 ms.
+// 8192 rows of 4 heads (U = 1) 1882 -> 304 us, 32768 of 8 (U = 2) 11.1 -> 6.7 ms.
 // Tiles reach LDS through buffer->LDS copies issued one tile ahead.
 // Transposed operands are read out of row-major tiles (common.h, tr_operand).
 #include <algorithm>
@@ -64,9 +64,9 @@ struct QStageSrc {
 // takes stands still, products and all: issued together at the top of a tile,
 // the copies of the next one held every wave for 1320 of the tile's 8100 clocks.
 // So they go out in pair_step, in its two regions that are all products.  Against
-// the top of the tile that is, for dK/dV of 4 heads over 1: 202 -> 188 us at
-// S = 8192, 2029 -> 1955 us at 32768, 3 to 6 % at 65536.  Spread over
-// all four regions, or all in one, they gain about half of it.
+// the top of the tile that is, for dK/dV of 4 heads over 1, 7 % at S = 8192 (202 ->
+// 188 us), 4 % at 32768, 3 to 6 % at 65536.  Spread over all four regions, or all in
+// one, they gain about half of it.
 struct TileCopy {
   QStageSrc r;
   uint32_t row0;    // first query row of the tile
@@ -287,8 +287,8 @@ __device__ __forceinline__ void pair_step(const TileCopy& next, int blk, const c
 // Segments.  The lists of all key blocks are prefixes of one list, the query
 // tiles from the last one down and within a tile the group's heads (beginning
 // at the key block's own); it is cut at every T-th entry, so that the
-// workgroups of one segment walk the same tiles side by side.  A key block (of 128 / QS keys) has whole segments and a
-// last one of any length up to T.
+// workgroups of one segment walk the same tiles side by side.  A key block (of
+// 128 / QS keys) has whole segments and a last one of any length up to T.
 
 // Key blocks whose list is longer than s segments: the first ones.
 template <bool CAUSAL, int QS>
@@ -323,8 +323,8 @@ __device__ inline int by_last_segment(int x, int T, int G, int nqt) {
 template <bool CAUSAL, int QS>
 __global__ __launch_bounds__(256, 1) void attn_bwd_dkdv_kernel(
     HeadView Q, HeadView dO, const float* __restrict__ lse_c, const float* __restrict__ Dc,
-    HeadView K, HeadView V, float* __restrict__ dK32, float* __restrict__ dV32, HeadView dk, HeadView dv, DkdvSlots slots, int64_t S, int64_t Sp,
-    int U, int h0, int G) {
+    HeadView K, HeadView V, float* __restrict__ dK32, float* __restrict__ dV32, HeadView dk,
+    HeadView dv, DkdvSlots slots, int64_t S, int64_t Sp, int U, int h0, int G) {
   constexpr int KB = 128 / QS;           // keys per workgroup
   __shared__ __attribute__((aligned(1024))) char smem[2 * KV_STAGE];
   const int t = threadIdx.x;
@@ -872,7 +872,8 @@ int64_t whole_segments(int causal, int qs, int T, int G, int nqt) {
 
 // Chooses the keys of a workgroup (128 or 64) and the segment length T by the
 // time they are expected to take, in units of one 128 x 128 tile on a full chip
-// (4.1 us).  Measured, causal, d_model 4096 block (T: workgroups, us):
+// (about 4 us).  Measured, causal, d_model 4096 block, with the copies at the top of
+// a tile, where the ratios below come from (T: workgroups, us):
 //   8192 rows, 4 heads    T 20: 442, 207   32: 288, 214   40: 238, 182   64: 160, 258
 //                         128: 96, 463     256: 64, 885 (no segments)
 //   16384 rows, 4 heads   T 80: 476, 684   96: 408, 784   128: 320, 680  192: 240, 772
@@ -885,9 +886,9 @@ int64_t whole_segments(int causal, int qs, int T, int G, int nqt) {
 // that one's shader engine, so a second wave costs 0.3 T more than
 // its longest.  A workgroup costs two tiles besides its list, the fold 1.5 and
 // 0.016 per slot.
-// Against one workgroup per key block: 512 rows, 2 heads 37 -> 25 us; 4096 rows, 8
-// heads on 2 433 -> 112; 8192 rows, 4 heads 848 -> 203; 32768 rows, 8 heads 7.8 -> 4.4
-// ms, where 1028 tiles per CU are 4.2 ms.
+// Against a launch per head with one workgroup per key block (dK/dV with its fold):
+// 512 rows, 2 heads 46 -> 23 us; 4096 rows, 8 heads on 2 935 -> 106; 8192 rows, 4 heads
+// 895 -> 190; 32768 rows, 8 heads 7.0 -> 4.0 ms, 1028 tiles per CU at 3.9 us.
 DkdvSplit dkdv_split(int64_t Sp, int Hkv, int G, int causal, size_t bytes0, size_t bytes1) {
   const int nqt = (int)(Sp / QT);
   DkdvSplit best;

@@ -9,14 +9,16 @@
 // Q, K, V and O are read and written where the caller has them (any row and
 // head stride): one launch covers all heads of all sequences of a call, with
 // no packing.  Against one launch per chunk between pack, merge and unpack
-// kernels: 8192 tokens, 4 heads, one head a chunk 443 -> 91 us (10 % -> 55 % of
+// kernels: 8192 tokens, 4 heads, one head a chunk 408 -> 86 us (12 % -> 58 % of
 // 1378 TFLOP/s, an 8192^3 product's rate); 131072 tokens unchanged.
 //
 // Work decomposition
 //   workgroup = 8 waves of 32 query rows x a part of every stage's keys: 256
 //               rows x 128 keys, 128 x 64 or 64 x 32 (attn_fwd_key_parts), one
 //               query block of one head (two waves per SIMD, one workgroup per
-//               CU); the parts of a row are folded in fp32 through LDS
+//               CU); the parts of a row are folded in fp32 through LDS.  Up to
+//               128 queries on more than 8192 keys: two workgroups, a half of
+//               the keys each (attn_fwd_half_stage)
 //   key stage = 128 keys, double-buffered in LDS (K rows 32 KB, V rows 32 KB),
 //               filled by buffer->LDS copies issued one stage ahead
 //   per wave per stage: S^T = K . Q^T    (4 x 8 MFMA 32x32x16, keys on rows)

@@ -19,8 +19,9 @@
 // B/clk) needs as long as its MFMAs for a 128 x 128 tile, half as long for 256 x
 // 256.  So 256 x 256 wherever its tiles fill the chip, else 128 x 128 (256 x 128
 // was never the fastest); two stages of 64 k each, the next one's copies in
-// flight during the products.  8192 x 4096 x 4096: 288 -> 220 us (955 -> 1249
-// TFLOP/s) against 128 x 128 tiles of 128 k in one stage; 8192^3 1297.  A wave has 64 columns, 32 c + 64 nt + 0..31 of a 128-wide
+// flight during the products.  Against 128 x 128 tiles of 128 k in one stage:
+// 8192 x 4096 x 4096 272 -> 227 us (1011 -> 1210 TFLOP/s), 8192^3 1073 -> 884 us (1025 ->
+// 1244).  A wave has 64 columns, 32 c + 64 nt + 0..31 of a 128-wide
 // block (nt = 0, 1): the coordinate pairs (e, e + 64) of a head sit in one lane,
 // which the rotary embedding of the head epilogue needs.  The k loop runs in
 // ascending order with one fp32 accumulator chain per output element, so no
@@ -205,7 +206,7 @@ __global__ __launch_bounds__((64 * Shape<BM, BN>::W), 2) void gemm_kernel(
     }
     // Keep one k-step's fragment reads in flight ahead of the MFMAs (left to
     // itself the scheduler waits for a step's reads before its first MFMA:
-    // 8192 x 4096 x 4096 230 -> 220 us).
+    // 8192 x 4096 x 4096 -4 %).
     constexpr int NR = MT * (A_K ? 1 : 2) + 2 * (B_K ? 1 : 2);   // reads of a k-step
     constexpr int PER = (NR + 2 * MT - 1) / (2 * MT);             // per MFMA
     constexpr int NI = (3 * NR + PER - 1) / PER;
@@ -321,9 +322,9 @@ hipError_t launch_gemm(const GemmOperand& A, bool a_kmajor, const GemmOperand& B
   if ((M % 128) || (N % 128) || (k_len % 128)) return hipErrorInvalidValue;
   if ((a_kmajor || b_kmajor) && (E.k_total % 128)) return hipErrorInvalidValue;
   // Rounds on 256 CUs: a 256 x 256 tile takes 0.8 of four 128 x 128 ones, two of
-  // which run side by side (us, 128 | 256: 8192 x 4096 x 4096 271 | 220; 65536 x 1280 x
-  // 5120 858 | 748; 16384 x 640 x 512 22.1 | 22.8; 8192 x 768 x 4096, 96 large tiles,
-  // 54 | 90; 3072 x 2048 x 1024 20 | 31).  No result depends on it.
+  // which run side by side (us, 128 | 256: 8192 x 4096 x 4096 252 | 231; 8192^3 1087 | 892;
+  // 65536 x 1280 x 5120 907 | 785; 16384 x 640 x 512 22.2 | 21.6; 8192 x 768 x 4096, 96
+  // large tiles, 56 | 90; 3072 x 2048 x 1024 20 | 30).  No result depends on it.
   const int64_t big = ((M + 255) / 256) * ((N + 255) / 256) * splits;
   const int64_t small = (M / 128) * (N / 128) * splits;
   const bool large = 1.6 * ((big + 255) / 256) < (small + 511) / 512;

@@ -23,6 +23,8 @@
 // Against the products and attention of one chunk of U heads at a time, 8192 tokens
 // of the Llama3-8B share (d_model 4096, 4 heads, U = 1): the five QKV products
 // 2 x 307 -> 2 x 95 us.
+// Where o_saved lies over x or wqkv the forward runs the chunks of U heads (K and
+// V first, then a chunk's Q and attention at a time).
 // Rotary embedding (optional, Section 4 "Implementation"): Q and K are
 // rotated in the projection epilogue, on the fp32 accumulators, before they
 // are rounded and stored -- in place, with no extra pass or fp32 copy.  The

@@ -5,11 +5,12 @@
 // workspace argument.  Its device address is looked up once per device with
 // hipGetSymbolAddress (with that device current) and kept; host code never
 // passes the array's own name to a kernel, copy or memset (in host code that
-// name is a host-side stand-in, not a device address).  The forward's
-// workspace needs no clearing: every byte a kernel reads in it was written
-// earlier in the same call (packed rows and their zero padding, the chunk
-// output, the split lse rows), so what a previous call left there is never
-// seen.
+// name is a host-side stand-in, not a device address).  The forward works in
+// place and touches the array only where an output overlaps an input: then
+// packed rows, a chunk's output and its lse rows lie in it, each written before it is
+// read in the same call, so nothing needs clearing.  (Keys and values whose rows
+// span 2^32 bytes, which are packed too, do not fit.)  The size limit is that of
+// the workspace query.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

@@ -117,7 +117,7 @@ int run_dkdv(const HeadView& Q, const HeadView& dO, const float* lse_c, const fl
 // rows of 8 heads 7.0 -> 4.0 ms.  The line was drawn when segments took 17.7 ms
 // at 65536 rows of 8 heads and head by head 17.3; since the copies go out between
 // products it is 15.7 against 16.0 (17.2 for the 8 heads of one group in one
-// launch), and at 131072 rows of 4 heads 31.1 against 31.7 (one box).
+// launch), and at 131072 rows of 4 heads 31.1 against 31.7 (one machine).
 constexpr int64_t kPerHeadRows = 65536;
 // Sequence b and head u of a view, as a view that starts there.
 HeadView sub(HeadView x, int64_t b, int64_t u);
